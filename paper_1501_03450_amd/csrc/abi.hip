@@ -219,6 +219,63 @@ double design_angle(const st_element& e, const st_beam& b, double r_ref);
 // double precision in ST_MIXED.
 constexpr double kSpin32MaxAngle = 0.02;
 
+// The lane bounds of the short-series bodies (FastParams, lattice_table.h), or
+// flags without F_FAST where the element has no such body or its rotations may
+// leave the quaternion series (ymax: what the launch's series covers).
+void derive_fast(st::DevElem& d, const st_element& e, const st_beam& b, double beta0, double ymax) {
+  if (e.spin_place != ST_SPIN_EDGES || e.fringe) return;
+  const bool bend = e.kind == ST_SBEND && e.orbit == ST_ORB_EXACT;
+  const bool quad = e.kind == ST_QUAD && (e.orbit == ST_ORB_DKD || e.orbit == ST_ORB_MK);
+  if (!bend && !quad) return;
+  const double hw = 0.5 * e.L / e.n_slices;
+  // (1 + G gamma)/P over the momenta of the fast lanes, gamma/P from P² - 1 =
+  // (gamma² - gamma0²)/(beta0 gamma0)², with 0.1 % for the transverse momenta
+  double lo = INFINITY, hi = -INFINITY, a2 = 0.0;   // a2: G (gamma - 1)/P
+  for (double c3 = -st::kFastC3; c3 <= st::kFastC3 * 1.001; c3 += st::kFastC3 / 16.0) {
+    const double bg = beta0 * b.gamma0;
+    const double gamma = std::sqrt(std::max(1.0, b.gamma0 * b.gamma0 + c3 * bg * bg));
+    const double v = (1.0 + b.G * gamma) / std::sqrt(1.0 + c3);
+    a2 = std::max(a2, 1.001 * std::fabs(b.G) * gamma / std::sqrt(1.0 + c3));
+    lo = std::min(lo, v - 1e-3 * std::fabs(v));
+    hi = std::max(hi, v + 1e-3 * std::fabs(v));
+  }
+  if (bend) {
+    const double h = e.angle / e.L, x = 0.02;       // |hX| up to 2 %
+    double w = 0.0;                                 // |1 - eta (1 + hX) (1 + G gamma)/Ps|
+    for (double f : {e.eta * (1.0 - x) * lo, e.eta * (1.0 - x) * hi, e.eta * (1.0 + x) * lo,
+                     e.eta * (1.0 + x) * hi})
+      w = std::max(w, std::fabs(1.0 - f));
+    // the components along x and s stay below eta (1 + hX) a2 |Py|/P² of h,
+    // and so does what Py takes from the one along y
+    const double t = hw * std::fabs(h) * (w + 0.001 * e.eta * a2 * st::kFastMom);
+    const double tz = hw * std::fabs(h) * 1.1 * e.eta * a2 * st::kFastMom;
+    if (!(t * t + 2.0 * tz * tz <= ymax)) return;
+    d.fast.b.x_max = x / std::fabs(h);
+    // Px inside is below |Px| + turn |Ps - eta (1 + hX)| of the entrance, and
+    // |Ps - 1| below (|c3| + 2^-15)/1.9
+    const double turn = std::fabs(e.angle) < 1.5 ? std::fabs(std::sin(e.angle)) : 1.0;
+    d.fast.b.mom = st::kFastMom - turn * (std::fabs(1.0 - e.eta) + 2e-5);
+    d.fast.b.turn_c = turn / 1.9;
+    d.fast.b.turn_x = turn * e.eta * std::fabs(h);
+    d.fast.b.hw_eta_h = hw * e.eta * h;
+    d.fast.b.hw_h = hw * h;
+  } else {
+    // growth through the defocusing plane at the lowest momentum, 1 % over
+    const double pmin = std::sqrt(1.0 - st::kFastC3), kl = std::sqrt(std::fabs(e.k1) / pmin) * e.L;
+    const double ds = e.L / e.n_slices;
+    if (!(kl <= 2.0) || std::fabs(e.k1) * ds * ds > 0.25) return;
+    const double ch = 1.01 * std::cosh(kl), sh = kl > 0.0 ? 1.01 * std::sinh(kl) / kl : 1.01;
+    d.fast.q.mom_p = ch;
+    d.fast.q.mom_x = std::fabs(e.k1) * e.L * sh;
+    d.fast.q.reach = sh / pmin * e.L;
+    const double per_x = hw * std::fabs(e.k1) *
+                         (1.01 * std::max(std::fabs(lo), std::fabs(hi)) + 0.01 * a2);
+    d.fast.q.x_max = st::kFastQuadAngle / std::max(per_x * ch, 1e-300);
+    d.fast.q.hw_k1 = hw * e.k1;
+  }
+  d.flags |= st::F_FAST;
+}
+
 st::DevElem derive(const st_element& e, const st_beam& beam, double beta0) {
   st::DevElem d;
   std::memset(&d, 0, sizeof(d));
@@ -531,8 +588,16 @@ st_status st_load_lattice(st_ctx* c, const st_element* els, int64_t n, const st_
     seq[(size_t)i] = k;
     theta = std::max(theta, design_angle(els[i], *b, 0.02));
   }
+  // series terms: cover the design angles with 10% margin; lanes beyond use sincos
+  const double y = 1.21 * 0.25 * theta * theta;
+  int terms = 16;
+  for (int nt : {5, 6, 8, 12, 16})
+    if (series_ymax(nt) >= y) { terms = nt; break; }
   std::vector<st::DevElem> tab(std::max<size_t>(uniq.size(), 1));
-  for (size_t u = 0; u < uniq.size(); ++u) tab[u] = derive(uniq[u], *b, beta0);
+  for (size_t u = 0; u < uniq.size(); ++u) {
+    tab[u] = derive(uniq[u], *b, beta0);
+    derive_fast(tab[u], uniq[u], *b, beta0, series_ymax(terms));
+  }
 
   DeviceGuard g(c->device);
   if (c->d_tab) { (void)hipFree(c->d_tab); c->d_tab = nullptr; }
@@ -548,12 +613,8 @@ st_status st_load_lattice(st_ctx* c, const st_element* els, int64_t n, const st_
   if (n > 0 && (e = hipMemcpy(c->d_seq, seq.data(), seq.size() * sizeof(uint32_t), hipMemcpyHostToDevice)) != hipSuccess)
     return hip_fail(c, e, "upload lattice sequence");
 
-  // series terms: cover the design angles with 10% margin; lanes beyond use sincos
-  const double y = 1.21 * 0.25 * theta * theta;
-  c->nt = 16;
-  for (int nt : {5, 6, 8, 12, 16})
-    if (series_ymax(nt) >= y) { c->nt = nt; break; }
-  c->ymax = series_ymax(c->nt);
+  c->nt = terms;
+  c->ymax = series_ymax(terms);
   c->beam = *b;
   c->beta0 = beta0;
   c->ext = ext;

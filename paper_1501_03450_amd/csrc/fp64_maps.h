@@ -34,6 +34,11 @@ __device__ __forceinline__ Quat qsquare(const Quat& q) {
   return {fma(q.w, q.w, -fma(q.x, q.x, fma(q.y, q.y, q.z * q.z))), tw * q.x, tw * q.y, tw * q.z};
 }
 
+__device__ __forceinline__ Quat qnormalized(const Quat& q) {
+  const double inv = rsqrt_nr(fma(q.w, q.w, fma(q.x, q.x, fma(q.y, q.y, q.z * q.z))));
+  return {q.w * inv, q.x * inv, q.y * inv, q.z * inv};
+}
+
 // One Romberg step on quaternions: (c A - B) / (c - 1).
 __device__ __forceinline__ Quat qextrapolate(const Quat& A, const Quat& B, double c) {
   const double inv = 1.0 / (c - 1.0);
@@ -384,12 +389,104 @@ __device__ __forceinline__ void bend_yt(const BendParams& e, const BendStep& k, 
   T += fma(-bl.ibh, D, bl.c0);
 }
 
-// Matrix-kick quadrupole constants of one particle (§3.3 eq. quadL over
-// s = ds/2): κ² = |k1|/P; cos, sin(κs)/κ, κP sin(κs) and their hyperbolic
-// twins, all functions of (κs)² = |k1| s²/P.  The flight-time brace of
-// eq. quadL is a quadratic form in (X, Px, Y, Py) at the entrance of the
-// step; its six coefficients, with the factor -1/β = -(1/β0 + Pt)/P
-// folded in, are constants of the particle in the element.
+// Matrix-kick quadrupole (§3.3 eq. quadL over s = ds/2, eq. quadNL): linear
+// part of one particle, κ² = |k1|/P: cos, sin(κs)/κ, κP sin(κs) and their
+// hyperbolic twins, all functions of (κs)² = |k1| s²/P.
+//
+// Flight time.  Along the linear flow over a length s the brace of eq. quadL
+// is half the integral of (px² + py²) ds, p = P(x,y)/P, and with the flow's
+// invariants Ef = px² + κ²x² (focusing plane), Ed = py² - κ²y² that is
+//   [s (Ef + Ed) + Δ(x px + y py)] / 4
+// because (x px)' = px² - κ²x² = 2px² - Ef and (y py)' = 2py² - Ed.  So a whole element needs the
+// invariant once per slice edge (each joins the half steps on both of its
+// sides), and Δ(x px + y py) telescopes to the element's two ends less the
+// jumps ds u (1/Ps - 1/P) P at the position kicks, which join the kicks'
+// own flight time.  Against the six-coefficient quadratic form of every half
+// step this takes 19 operations per slice less.
+struct MKLin {
+  double cf, sfP, kf;    // focusing plane:   cos κs, sin κs /(κ P), κ P sin κs
+  double cd, sdP, kd;    // defocusing plane: cosh κs, sinh κs /(κ P), κ P sinh κs
+};
+
+__device__ __forceinline__ void mk_series(const QuadParams& e, const Particle& p, double& C,
+                                          double& sf, double& Ch, double& sd) {
+  const double t = e.kabs_hds2 * p.invP;       // (κ s)²
+  double Sc, Sh;
+  if (t <= 0.04) {
+    cos_sinc_series<7>(t, C, Sc);
+    cosh_sinhc_series<7>(t, Ch, Sh);
+  } else {
+    halving_series<7, false>(t, 0.04, C, Sc);
+    halving_series<7, true>(t, 0.04, Ch, Sh);
+  }
+  sf = e.hds * Sc;
+  sd = e.hds * Sh;
+}
+
+__device__ __forceinline__ MKLin mk_lin(const QuadParams& e, const Particle& p) {
+  MKLin m;
+  double sf, sd;
+  const double kabs = fabs(e.k1);
+  mk_series(e, p, m.cf, sf, m.cd, sd);
+  m.sfP = sf * p.invP;  m.kf = kabs * sf;
+  m.sdP = sd * p.invP;  m.kd = kabs * sd;
+  return m;
+}
+
+// Linear part over ds/2 in (focusing, defocusing) coordinates, orbit only.
+__device__ __forceinline__ void mk_move(const MKLin& m, double& xf, double& pxf, double& yd,
+                                        double& pyd) {
+  const double x0 = xf, y0 = yd, p0 = pxf, q0 = pyd;
+  xf = fma(x0, m.cf, p0 * m.sfP);
+  pxf = fma(p0, m.cf, -x0 * m.kf);
+  yd = fma(y0, m.cd, q0 * m.sdP);
+  pyd = fma(q0, m.cd, y0 * m.kd);
+}
+
+// P² (Ef + Ed) at a slice edge: Px² + Py² + |k1| P (xf² - yd²).
+__device__ __forceinline__ double mk_invariant(double kP, double pp, double xf, double yd) {
+  return fma(kP, fma(xf, xf, -yd * yd), pp);
+}
+
+// Nonlinear "kick of positions" over ds (§3.3 eq. quadNL).  With
+// u = (Px² + Py²)/P², 1/Ps - 1/P = (u/2 + g)/P, g = P/Ps - 1 - u/2
+// (series_g); a lane with larger angles takes the closed form
+// g = u²(2 + ρ)/(2ρ(1 + ρ)²), ρ = Ps/P.  tk collects g - u (u/2 + g)/4: the
+// kick's flight time -ds g/β with its share of the telescoped sum.
+__device__ __forceinline__ void mk_kick(double ds, double& X, double Px, double& Y, double Py,
+                                        double& tk, const Particle& p) {
+  const double pp = fma(Px, Px, Py * Py);
+  const double u = pp * p.invP2();
+  double g, d;
+  if (u <= kSeriesMaxU) {
+    g = series_g(u);
+    d = fma(u, 0.5, g) * p.invP;         // 1/Ps - 1/P
+  } else {
+    const double ps2 = p.P2() - pp;
+    const double r = rsqrt_nr(ps2);
+    d = r - p.invP;
+    const double rho = ps2 * r * p.invP;
+    const double opr = 1.0 + rho;
+    g = u * u * (2.0 + rho) * (p.P() * r) * 0.5 * rcp_nr(opr * opr);
+  }
+  X = fma(ds * Px, d, X);
+  Y = fma(ds * Py, d, Y);
+  tk = tk + fma(-0.25 * u, fma(u, 0.5, g), g);
+}
+
+// Flight time of a whole element of n slices: sum = Σ invariants (the end
+// edges halved), dxp = Δ(X Px + Y Py), tk from the kicks.
+__device__ __forceinline__ double mk_flight(double ds, double n, double sum, double dxp, double tk,
+                                            const Particle& p) {
+  const double lin = p.invP * fma(ds * p.invP, sum, dxp);
+  return -fma(p.invbeta(), fma(0.25, lin, ds * tk), n * ds * p.dib);
+}
+
+// Matrix-kick constants of one step taken by itself (the composed
+// fourth-order slices, whose steps differ in length): the flight-time brace
+// of eq. quadL as a quadratic form in (X, Px, Y, Py) at the entrance of the
+// step; its six coefficients, with the factor -1/β = -(1/β0 + Pt)/P folded
+// in, are constants of the particle in the element.
 struct MKConst {
   double cf, sfP, kf;    // focusing plane:   cos κs, sin κs /(κ P), κ P sin κs
   double cd, sdP, kd;    // defocusing plane: cosh κs, sinh κs /(κ P), κ P sinh κs
@@ -400,18 +497,9 @@ struct MKConst {
 
 __device__ __forceinline__ MKConst mk_const(const QuadParams& e, const Particle& p) {
   MKConst m;
-  double t = e.kabs_hds2 * p.invP;       // (κ s)²
-  double kabs = fabs(e.k1);
-  double C, Sc, Ch, Sh;
-  if (t <= 0.04) {
-    cos_sinc_series<7>(t, C, Sc);
-    cosh_sinhc_series<7>(t, Ch, Sh);
-  } else {
-    halving_series<7, false>(t, 0.04, C, Sc);
-    halving_series<7, true>(t, 0.04, Ch, Sh);
-  }
-  const double hs = e.hds;
-  const double sf = hs * Sc, sd = hs * Sh;
+  const double kabs = fabs(e.k1), hs = e.hds;
+  double C, sf, Ch, sd;
+  mk_series(e, p, C, sf, Ch, sd);
   m.cf = C;  m.sfP = sf * p.invP;  m.kf = kabs * sf;
   m.cd = Ch; m.sdP = sd * p.invP;  m.kd = kabs * sd;
   const double kap2 = kabs * p.invP;

@@ -82,8 +82,41 @@ static_assert(sizeof(RbendParams) <= sizeof(BendParams), "element union size");
 static_assert(sizeof(Quad4Params) <= sizeof(BendParams), "element union size");
 
 // element flags: single-precision spin arithmetic; thin-fringe spin kicks at
-// both faces (sector bends and quadrupoles, extended kernels only)
-enum : int32_t { F_SPIN32 = 1, F_FRINGE = 2 };
+// both faces (sector bends and quadrupoles, extended kernels only); the
+// short-series body is available (see FastParams)
+enum : int32_t { F_SPIN32 = 1, F_FRINGE = 2, F_FAST = 4 };
+
+// Short-series bodies of sector bends and second-order quadrupoles (F_FAST): a
+// lane takes them when its particle is within kFastC3 of the reference
+// momentum, its transverse momenta (scaled by p0) stay below a bound through
+// the element, and its offsets below one that keeps the slice rotations inside
+// the quaternion series.  Both are decided at the entrance from these bounds
+// on the motion inside:
+// bends       |Px| + turn_c |P² - 1| + turn_x |X| <= mom (so that |Px| stays
+//             below kFastMom), |Py| <= kFastMom, |X| <= x_max
+//             (each of (Px/P)², (Py/P)² <= 2^-16)
+// quadrupoles mom_p Q + mom_x R <= 2 kFastMom, R + reach Q <= x_max, with
+//             R = |X| + |Y| and Q = |Px| + |Py|: (Px² + Py²)/P² <= 2^-14 (a
+//             quadrupole's kick of 2.5 mrad at 3 cm takes 1.3 % of a Gaussian
+//             bunch's passages beyond kFastMom, which would send half of the
+//             waves through both bodies; 3e-6 beyond twice that)
+struct FastBendParams {
+  double x_max, mom, turn_c, turn_x;
+  double hw_eta_h, hw_h;                // (ds/2) η h and (ds/2) h
+};
+struct FastQuadParams {
+  double x_max, mom_p, mom_x, reach;
+  double hw_k1;                         // (ds/2) k1
+};
+constexpr int kFastWords = sizeof(FastBendParams) / sizeof(double);
+union FastParams {
+  FastBendParams b;
+  FastQuadParams q;
+  double v[kFastWords];
+};
+constexpr double kFastC3 = 0.125;       // |P² - 1|
+constexpr double kFastMom = 0.0036;     // below 2^-8 sqrt(1 - kFastC3)
+constexpr double kFastQuadAngle = 0.029; // half the slice rotation of a quadrupole edge
 
 struct DevElem {
   int32_t kind, orbit, nsl, K;   // K = R_e - 1: Romberg levels minus one
@@ -92,6 +125,7 @@ struct DevElem {
   // Romberg edge rotations of sliced elements: half the step w ds of an end
   // edge (w = 1/2) and of an interior edge (w = 1), and their squares
   double hw_end, hw_in, hw2_end, hw2_in;
+  FastParams fast;         // (F_FAST)
   union {
     BendParams b;
     TeapotParams tp;
