@@ -26,14 +26,15 @@ struct st_ctx {
   bool have_lattice = false;
   st_beam beam{};
   double beta0 = 0.0;
-  int n_elems = 0;
-  int n_unique = 0;
+  int n_records = 0;
   int nt = 16;             // quaternion series terms
   bool ext = false;        // lattice needs the extended kernel (TEAPOT, PWC placements,
                            // solenoids, rectangular bends, fringe spin kicks)
   double ymax = 0.0;
-  st::DevElem* d_tab = nullptr;
-  uint32_t* d_seq = nullptr;
+  char* d_lattice = nullptr;               // one allocation: records, elements, sequence
+  const st::Record* d_rec = nullptr;
+  const st::DevElem* d_tab = nullptr;
+  const uint32_t* d_seq = nullptr;
   // particles
   int64_t n = 0;
   double* z = nullptr;
@@ -219,14 +220,25 @@ double design_angle(const st_element& e, const st_beam& b, double r_ref);
 // double precision in ST_MIXED.
 constexpr double kSpin32MaxAngle = 0.02;
 
-// The lane bounds of the short-series bodies (FastParams, lattice_table.h), or
-// flags without F_FAST where the element has no such body or its rotations may
-// leave the quaternion series (ymax: what the launch's series covers).
-void derive_fast(st::DevElem& d, const st_element& e, const st_beam& b, double beta0, double ymax) {
+// What the record runs (d.op), and the lane bounds of its short-series body
+// (FastParams, lattice_table.h) unless the element has none or its rotations
+// may leave the quaternion series (ymax: what the launch's series covers).
+void derive_record(st::Record& r, const st::DevElem& d, const st_element& e, const st_beam& b, double beta0,
+                   double ymax) {
+  r.flags = d.flags & st::F_SPIN32;
+  switch (e.kind) {
+    case ST_MARKER: case ST_DRIFT: r.op = st::OP_NONE; return;
+    case ST_THIN:                  r.op = st::OP_THIN; r.t = d.t; return;
+    case ST_SNAKE:                 r.op = st::OP_SNAKE; r.s = d.s; return;
+    default:                       r.op = st::OP_EXT; break;
+  }
   if (e.spin_place != ST_SPIN_EDGES || e.fringe) return;
   const bool bend = e.kind == ST_SBEND && e.orbit == ST_ORB_EXACT;
   const bool quad = e.kind == ST_QUAD && (e.orbit == ST_ORB_DKD || e.orbit == ST_ORB_MK);
   if (!bend && !quad) return;
+  r.op = st::OP_THICK;
+  if (bend ? d.nsl != 8 || (d.K != 3 && d.K != 2) : d.K != 2 || d.nsl != (e.orbit == ST_ORB_MK ? 4 : 8))
+    return;
   const double hw = 0.5 * e.L / e.n_slices;
   // (1 + G gamma)/P over the momenta of the fast lanes, gamma/P from P² - 1 =
   // (gamma² - gamma0²)/(beta0 gamma0)², with 0.1 % for the transverse momenta
@@ -250,30 +262,37 @@ void derive_fast(st::DevElem& d, const st_element& e, const st_beam& b, double b
     const double t = hw * std::fabs(h) * (w + 0.001 * e.eta * a2 * st::kFastMom);
     const double tz = hw * std::fabs(h) * 1.1 * e.eta * a2 * st::kFastMom;
     if (!(t * t + 2.0 * tz * tz <= ymax)) return;
-    d.fast.b.x_max = x / std::fabs(h);
+    r.b.cs = d.b.slice.cs; r.b.sn = d.b.slice.sn; r.b.omc = d.b.slice.omc;
+    r.b.w_cs = d.b.whole.cs; r.b.w_sn = d.b.whole.sn; r.b.w_omc = d.b.whole.omc;
+    r.b.s_eta = d.b.whole.s_eta; r.b.tconst = d.b.whole.tconst;
+    r.b.h = d.b.h; r.b.eta_h = d.b.eta_h; r.b.inv_eta_h = d.b.inv_eta_h;
+    r.b.eta = d.b.eta; r.b.one_m_eta2 = d.b.one_m_eta2;
+    r.b.x_max = x / std::fabs(h);
     // Px inside is below |Px| + turn |Ps - eta (1 + hX)| of the entrance, and
     // |Ps - 1| below (|c3| + 2^-15)/1.9
     const double turn = std::fabs(e.angle) < 1.5 ? std::fabs(std::sin(e.angle)) : 1.0;
-    d.fast.b.mom = st::kFastMom - turn * (std::fabs(1.0 - e.eta) + 2e-5);
-    d.fast.b.turn_c = turn / 1.9;
-    d.fast.b.turn_x = turn * e.eta * std::fabs(h);
-    d.fast.b.hw_eta_h = hw * e.eta * h;
-    d.fast.b.hw_h = hw * h;
+    r.b.mom = st::kFastMom - turn * (std::fabs(1.0 - e.eta) + 2e-5);
+    r.b.turn_c = turn / 1.9;
+    r.b.turn_x = turn * e.eta * std::fabs(h);
+    r.b.hw_eta_h = hw * e.eta * h;
+    r.b.hw_h = hw * h;
+    r.op = d.K == 3 ? st::OP_BEND83 : st::OP_BEND82;
   } else {
     // growth through the defocusing plane at the lowest momentum, 1 % over
     const double pmin = std::sqrt(1.0 - st::kFastC3), kl = std::sqrt(std::fabs(e.k1) / pmin) * e.L;
     const double ds = e.L / e.n_slices;
     if (!(kl <= 2.0) || std::fabs(e.k1) * ds * ds > 0.25) return;
     const double ch = 1.01 * std::cosh(kl), sh = kl > 0.0 ? 1.01 * std::sinh(kl) / kl : 1.01;
-    d.fast.q.mom_p = ch;
-    d.fast.q.mom_x = std::fabs(e.k1) * e.L * sh;
-    d.fast.q.reach = sh / pmin * e.L;
+    r.q.q = d.q;
+    r.q.mom_p = ch;
+    r.q.mom_x = std::fabs(e.k1) * e.L * sh;
+    r.q.reach = sh / pmin * e.L;
     const double per_x = hw * std::fabs(e.k1) *
                          (1.01 * std::max(std::fabs(lo), std::fabs(hi)) + 0.01 * a2);
-    d.fast.q.x_max = st::kFastQuadAngle / std::max(per_x * ch, 1e-300);
-    d.fast.q.hw_k1 = hw * e.k1;
+    r.q.x_max = st::kFastQuadAngle / std::max(per_x * ch, 1e-300);
+    r.q.hw_k1 = hw * e.k1;
+    r.op = e.orbit == ST_ORB_DKD ? st::OP_DKD82 : e.k1 >= 0.0 ? st::OP_MKX : st::OP_MKY;
   }
-  d.flags |= st::F_FAST;
 }
 
 st::DevElem derive(const st_element& e, const st_beam& beam, double beta0) {
@@ -389,8 +408,6 @@ st::DevElem derive(const st_element& e, const st_beam& beam, double beta0) {
     sp.eta = 0.5 * e.ks;
     sp.inv_eta = 2.0 / e.ks;
     sp.eta_q = 0.25 * e.ks;
-  } else if (e.kind == ST_DRIFT) {
-    d.d.L = e.L;
   } else if (e.kind == ST_THIN) {
     d.t.k1l = e.k1l;
     d.t.k2l = e.k2l;
@@ -441,9 +458,10 @@ st::TrackArgs track_args(const st_ctx* c) {
   a.spin = c->spin;
   a.alive = c->alive;
   a.n = c->n;
+  a.rec = c->d_rec;
   a.tab = c->d_tab;
   a.seq = c->d_seq;
-  a.n_elems = c->n_elems;
+  a.n_records = c->n_records;
   a.n_blocks = (int32_t)((c->n + st::track_block_size() - 1) / st::track_block_size());
   a.beta0 = c->beta0;
   a.inv_beta0 = 1.0 / c->beta0;
@@ -526,8 +544,7 @@ st_status st_destroy(st_ctx* c) {
   if (!c) return ST_OK;
   {
     DeviceGuard g(c->device);
-    if (c->d_tab) (void)hipFree(c->d_tab);
-    if (c->d_seq) (void)hipFree(c->d_seq);
+    if (c->d_lattice) (void)hipFree(c->d_lattice);
     if (c->d_partials) (void)hipFree(c->d_partials);
     if (c->d_pol) (void)hipFree(c->d_pol);
     for (void* p : {(void*)c->d_feat, (void*)c->d_qnn, (void*)c->d_q64, (void*)c->d_ck,
@@ -561,13 +578,13 @@ st_status st_load_lattice(st_ctx* c, const st_element* els, int64_t n, const st_
   }
   const double beta0 = std::sqrt(1.0 - 1.0 / (b->gamma0 * b->gamma0));
 
-  // compress: unique elements (equal bytes: st_element has no padding) and
-  // the index sequence
+  // compress: unique elements (equal bytes: st_element has no padding), then
+  // unique records of an element with the drift after it, and their sequence
   static_assert(sizeof(st_element) == 6 * sizeof(int32_t) + 10 * sizeof(double),
                 "st_element must have no padding bytes");
   std::vector<st_element> uniq;
   std::unordered_map<std::string, uint32_t> index;
-  std::vector<uint32_t> seq((size_t)n);
+  std::vector<uint32_t> elem((size_t)n);
   double theta = 0.0;
   bool ext = false;
   for (int64_t i = 0; i < n; ++i) {
@@ -585,41 +602,73 @@ st_status st_load_lattice(st_ctx* c, const st_element* els, int64_t n, const st_
       uniq.push_back(els[i]);
       index.emplace(key, k);
     }
-    seq[(size_t)i] = k;
+    elem[(size_t)i] = k;
     theta = std::max(theta, design_angle(els[i], *b, 0.02));
   }
   // series terms: cover the design angles with 10% margin; lanes beyond use sincos
   const double y = 1.21 * 0.25 * theta * theta;
   int terms = 16;
-  for (int nt : {5, 6, 8, 12, 16})
+  for (int nt : {5, 6, 8, 9, 12, 16})
     if (series_ymax(nt) >= y) { terms = nt; break; }
   std::vector<st::DevElem> tab(std::max<size_t>(uniq.size(), 1));
-  for (size_t u = 0; u < uniq.size(); ++u) {
-    tab[u] = derive(uniq[u], *b, beta0);
-    derive_fast(tab[u], uniq[u], *b, beta0, series_ymax(terms));
+  for (size_t u = 0; u < uniq.size(); ++u) tab[u] = derive(uniq[u], *b, beta0);
+  std::vector<st::Record> recs;
+  std::unordered_map<uint64_t, uint32_t> record;
+  std::vector<uint32_t> seq;
+  for (int64_t i = 0; i < n;) {
+    const uint32_t k = elem[(size_t)i];
+    const bool lone = uniq[k].kind == ST_DRIFT;
+    const bool tail = lone || (i + 1 < n && uniq[elem[(size_t)i + 1]].kind == ST_DRIFT);
+    const uint32_t kt = !tail ? UINT32_MAX : lone ? k : elem[(size_t)i + 1];
+    const uint64_t key = ((uint64_t)k << 32) | kt;
+    const auto it = record.find(key);
+    const int count = tail && !lone ? 2 : 1;
+    if (it != record.end()) {
+      seq.push_back(it->second);
+    } else {
+      st::Record r;
+      std::memset(&r, 0, sizeof(r));
+      derive_record(r, tab[k], uniq[k], *b, beta0, series_ymax(terms));
+      r.elem = (int32_t)k;
+      r.count = count;
+      if (tail) {
+        r.flags |= st::F_TAIL;
+        r.tail = uniq[kt].L;
+      }
+      seq.push_back((uint32_t)recs.size());
+      record.emplace(key, (uint32_t)recs.size());
+      recs.push_back(r);
+    }
+    i += count;
   }
+  seq.push_back(0);                        // the kernels read one index ahead
+  if (recs.empty()) recs.resize(1);
+  // one block of device memory: records, elements, sequence
+  const size_t rec_bytes = recs.size() * sizeof(st::Record), tab_bytes = tab.size() * sizeof(st::DevElem);
+  const size_t seq_bytes = seq.size() * sizeof(uint32_t);
+  std::vector<char> image(rec_bytes + tab_bytes + seq_bytes);
+  std::memcpy(image.data(), recs.data(), rec_bytes);
+  std::memcpy(image.data() + rec_bytes, tab.data(), tab_bytes);
+  std::memcpy(image.data() + rec_bytes + tab_bytes, seq.data(), seq_bytes);
 
   DeviceGuard g(c->device);
-  if (c->d_tab) { (void)hipFree(c->d_tab); c->d_tab = nullptr; }
-  if (c->d_seq) { (void)hipFree(c->d_seq); c->d_seq = nullptr; }
+  if (c->d_lattice) { (void)hipFree(c->d_lattice); c->d_lattice = nullptr; }
   c->have_lattice = false;
   hipError_t e;
-  if ((e = hipMalloc(&c->d_tab, tab.size() * sizeof(st::DevElem))) != hipSuccess)
-    return fail(c, ST_ENOMEM, std::string("lattice table: ") + hipGetErrorString(e));
-  if ((e = hipMalloc(&c->d_seq, std::max<size_t>(seq.size(), 1) * sizeof(uint32_t))) != hipSuccess)
-    return fail(c, ST_ENOMEM, std::string("lattice sequence: ") + hipGetErrorString(e));
-  if ((e = hipMemcpy(c->d_tab, tab.data(), tab.size() * sizeof(st::DevElem), hipMemcpyHostToDevice)) != hipSuccess)
-    return hip_fail(c, e, "upload lattice table");
-  if (n > 0 && (e = hipMemcpy(c->d_seq, seq.data(), seq.size() * sizeof(uint32_t), hipMemcpyHostToDevice)) != hipSuccess)
-    return hip_fail(c, e, "upload lattice sequence");
+  if ((e = hipMalloc((void**)&c->d_lattice, image.size())) != hipSuccess)
+    return fail(c, ST_ENOMEM, std::string("lattice tables: ") + hipGetErrorString(e));
+  if ((e = hipMemcpy(c->d_lattice, image.data(), image.size(), hipMemcpyHostToDevice)) != hipSuccess)
+    return hip_fail(c, e, "upload lattice tables");
+  c->d_rec = (const st::Record*)c->d_lattice;
+  c->d_tab = (const st::DevElem*)(c->d_lattice + rec_bytes);
+  c->d_seq = (const uint32_t*)(c->d_lattice + rec_bytes + tab_bytes);
 
   c->nt = terms;
   c->ymax = series_ymax(terms);
   c->beam = *b;
   c->beta0 = beta0;
   c->ext = ext;
-  c->n_elems = (int)n;
-  c->n_unique = (int)uniq.size();
+  c->n_records = (int)seq.size() - 1;
   c->have_lattice = true;
   c->err.clear();
   return ST_OK;
@@ -850,16 +899,21 @@ extern "C" st_status st_track_surrogate(st_ctx* c, st_mlp* m, int64_t turns, int
       a.turns = (int)k;
       a.report_every = 0;
       a.partials = nullptr;
-      a.fallback = d_fallback;
       a.perm = c->d_perm;
-      a.feat = n_net > 0 ? c->d_feat : nullptr;
-      a.turns_done = n_net > 0 ? c->d_done : nullptr;
+      a.feat = c->d_feat;
+      a.turns_done = c->d_done;
       a.feat_n = n_net;
       a.feat_n_in = st_mlp_inputs_of(m);
       for (int i = 0; i < 6; ++i) { a.feat_center[i] = center[i]; a.feat_inv_scale[i] = inv_scale[i]; }
       a.feat_extra = extra;
-      if ((e = st::launch_track(a, c->nt, false, c->ext, s)) != hipSuccess)
-        return hip_fail(c, e, "surrogate turns");
+      if (n_net > 0 && (e = st::launch_orbit(a, c->nt, c->ext, s)) != hipSuccess)
+        return hip_fail(c, e, "surrogate orbits");
+      if (n_net < n) {      // the particles that fall back, and the lost ones
+        a.lane0 = n_net;
+        a.n_blocks = (int32_t)((n - n_net + bs - 1) / bs);
+        if ((e = st::launch_track(a, c->nt, false, c->ext, s)) != hipSuccess)
+          return hip_fail(c, e, "surrogate turns");
+      }
       if (n_net > 0) {
         const st_status ms = st_mlp_infer(m, c->d_feat, c->d_qnn, k * n_net, stream);
         if (ms != ST_OK) return fail(c, ms, std::string("network: ") + st_mlp_last_error(m));

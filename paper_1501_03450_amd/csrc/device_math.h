@@ -142,9 +142,14 @@ __device__ __forceinline__ double rsqrt_omega(double x) {
 
 // Quaternion terms of a rotation by θ = |ω|, ω = f Ω: with y = (θ/2)²,
 // cos(θ/2) and sin(θ/2)/(θ/2).  NT series terms cover y <= ymax.
+// Four terms cover y <= kShortY (y^4/8! < 2^-56): quadrupoles in a ring whose
+// bends need many terms.
+constexpr double kShortY = 8.6e-4;
 template <int NT>
 __device__ __forceinline__ void rot_half_series(double y, double ymax, double& c, double& s) {
-  if (y <= ymax) {
+  if (NT > 6 && y <= kShortY) {
+    cos_sinc_series<4>(y, c, s);
+  } else if (y <= ymax) {
     cos_sinc_series<NT>(y, c, s);
   } else {
     halving_series<NT, false>(y, ymax, c, s);

@@ -69,6 +69,10 @@ struct Particle {
   double invP2_, invbeta_, a1_, a2_;
   // beam constants (kernel arguments, uniform)
   double ib0, beta0, ig2;
+  // 3/8, 1/8 and 1/4, held in registers: an instruction takes one scalar
+  // operand, and the compiler would otherwise write these two-word constants
+  // anew before each use (18 to 20 moves per bend or quadrupole)
+  double k38, k18, k14;
 
   __device__ __forceinline__ double P2() const { return 1.0 + c3; }
   __device__ __forceinline__ double P() const { return (1.0 + c3) * invP; }
@@ -91,6 +95,10 @@ __device__ __forceinline__ Particle make_particle(double Pt, const TrackArgs& a)
   p.a1_ = fma(Gg0b0, Pt, fma(a.G, a.gamma0, 1.0));
   p.a2_ = fma(Gg0b0, Pt, a.G * (a.gamma0 - 1.0));
   p.c3 = Pt * fma(2.0, a.inv_beta0, Pt);
+  p.k38 = 0.375;
+  p.k18 = 0.125;
+  p.k14 = 0.25;
+  asm("" : "+v"(p.k38), "+v"(p.k18), "+v"(p.k14));
   p.invP = rsqrt_nr(p.P2());
   p.invP2_ = p.invP * p.invP;
   p.invbeta_ = (a.inv_beta0 + Pt) * p.invP;
@@ -134,6 +142,36 @@ __device__ __forceinline__ void drift(double L, double& X, double Px, double& Y,
   }
 }
 
+// 1/Ps and e = P/Ps - 1 from pp = Px² + Py², by the same series; a lane with
+// larger angles takes e = u/(ρ (1 + ρ)), ρ = Ps/P (from 1 - ρ² = u).
+struct PsInv {
+  double r, e;
+};
+__device__ __forceinline__ PsInv ps_inverse(double pp, const Particle& p) {
+  PsInv f;
+  const double u = pp * p.invP2();
+  if (u <= kSeriesMaxU) {
+    f.e = fma(u, 0.5, series_g(u));
+    f.r = fma(p.invP, f.e, p.invP);
+  } else {
+    const double ps2 = p.P2() - pp;
+    f.r = rsqrt_nr(ps2);
+    f.e = u * (p.P() * f.r) * rcp_nr(fma(ps2 * f.r, p.invP, 1.0));
+  }
+  return f;
+}
+
+// 1/(1 - x): (1 + x)(1 + x²)(1 + x⁴) for |x| <= 2^-7 (the rest is x^8), the
+// refined hardware estimate beyond.
+__device__ __forceinline__ double rcp_one_minus(double x) {
+  if (fabs(x) <= 0.0078125) {
+    const double x2 = x * x;
+    const double f = fma(x, x2, x2) + x;      // (1 + x)(1 + x²) - 1
+    return 1.0 + fma(1.0 + f, x2 * x2, f);
+  }
+  return rcp_nr(1.0 - x);
+}
+
 // Precession vector of eq. t-bmt.so for a field b = (bx, by, 0) without
 // curvature (quadrupoles, thin multipoles):
 // Ω = -(1/Ps) [a1 b - a2 (ũ·b)/P² ũ], ũ = (Px, Py, Ps).  r = 1/Ps.
@@ -173,23 +211,21 @@ __device__ __forceinline__ void omega_bend(const BendParams& e, double X, double
 //   path  = (1/h + X) tan(a) / D
 //   ΔT    = (ds/2)/β0 - (1/β0 + Pt) path/Ps           (the Pt/β0 term of
 //           eq. generalH adds (ds/2)/β0)
-//         = (1/β0) { [(ds/2 - tan(a)/h) - tan(a)(u ds/2 + X)] / D
-//                    + path (Ps² - (1 + β0 Pt)²) / (Ps (Ps + 1 + β0 Pt)) }.
+//         = (1/β0) [(ds/2 - tan(a)/h) - tan(a)(u ds/2 + X)] / D
+//           - path [(1/β - 1/β0) + (P/Ps - 1)/β].
 __device__ __forceinline__ void teapot_drift(const TeapotParams& t, double& X, double& Px, double& Y,
                                              double Py, double& T, const Particle& p) {
   const double pp = fma(Px, Px, Py * Py);
-  const double ps2 = p.P2() - pp;
-  const double r = rsqrt_nr(ps2);
-  const double ps = ps2 * r;
-  const double u = Px * r;
-  const double inv_den = rcp_nr(fma(-u, t.tn, 1.0));
+  const PsInv f = ps_inverse(pp, p);
+  const double ps = (p.P2() - pp) * f.r;
+  const double u = Px * f.r;
+  const double inv_den = rcp_one_minus(u * t.tn);
   const double path = fma(X, t.tn, t.tn_h) * inv_den;
   const double short_path = fma(-t.tn, fma(t.half, u, X), t.d0) * inv_den;   // ds/2 - path
-  const double slow = path * (p.c1() - pp) * r * rcp_nr(ps + p.c2());
-  T = fma(short_path + slow, p.ib0, T);
+  T = fma(short_path, p.ib0, T) - path * fma(p.invbeta(), f.e, p.dib);
   X = fma(X, t.sec, fma(u, t.tn_h, t.omc_h)) * inv_den;
   Px = fma(Px, t.c, ps * t.sn);
-  Y = fma(Py * r, path, Y);
+  Y = fma(Py * f.r, path, Y);
 }
 
 // Dipole kick of a TEAPOT bend over a length len: Px -= ηh (1 + hX) len.

@@ -2,11 +2,16 @@
 // tracking kernels.
 //
 // A ring of ~1.7k elements repeats a handful of distinct magnets, so the
-// lattice is stored as a small table of unique elements with every per-element
-// constant precomputed on the host (trigonometry of the bend angle per slice,
-// reciprocals, snake quaternions), plus a 32-bit index sequence.  The kernels
-// walk the sequence with wave-uniform loads, so the table is read through the
-// scalar cache and every branch on the element kind is uniform.
+// lattice is stored as small tables with every per-element constant precomputed
+// on the host (trigonometry of the bend angle per slice, reciprocals, snake
+// quaternions), plus a 32-bit index sequence.  The kernels walk the sequence
+// with wave-uniform loads, so the tables are read through the scalar cache and
+// every branch on the element kind is uniform.  A record is one element with
+// the drift that follows it, if one does (a ring alternates magnets and drifts,
+// so this halves the records).  It holds what the standard bodies use of the
+// element, in few enough words that the scalar registers take the next record
+// while the current one finishes; the general bodies read the whole element
+// (DevElem) where they run.
 #pragma once
 
 #include <stdint.h>
@@ -71,7 +76,6 @@ struct RbendParams {        // rectangular bend (§3.2, §4.5)
   double larc_ib0;          // design arc length / β0 (eq. Toffset)
   RbendFace in, out;        // rotations by φ^entr and by -φ^exit
 };
-struct DriftParams { double L; };
 struct ThinParams { double k1l, k2l; };             // thin multipole (§3.5)
 struct SnakeParams { double qw, qx, qy, qz; };      // fixed rotation quaternion
 
@@ -82,12 +86,20 @@ static_assert(sizeof(RbendParams) <= sizeof(BendParams), "element union size");
 static_assert(sizeof(Quad4Params) <= sizeof(BendParams), "element union size");
 
 // element flags: single-precision spin arithmetic; thin-fringe spin kicks at
-// both faces (sector bends and quadrupoles, extended kernels only); the
-// short-series body is available (see FastParams)
-enum : int32_t { F_SPIN32 = 1, F_FRINGE = 2, F_FAST = 4 };
+// both faces (sector bends and quadrupoles, extended kernels only); a drift of
+// length `tail` follows the element
+enum : int32_t { F_SPIN32 = 1, F_FRINGE = 2, F_TAIL = 4 };
 
-// Short-series bodies of sector bends and second-order quadrupoles (F_FAST): a
-// lane takes them when its particle is within kFastC3 of the reference
+// What a record runs, chosen on the host.  From OP_THICK on: elements whose
+// general bodies the standard kernel has; from OP_BEND83 on: those with a
+// short-series body as well (sector bends with 8 slices and 4 or 3 rows, MK
+// quadrupoles with 4 slices and 3 rows, focusing in x or in y, DKD ones with 8
+// slices and 3 rows; the loops of those bodies are unrolled).
+enum : int32_t { OP_NONE = 0, OP_THIN = 1, OP_SNAKE = 2, OP_EXT = 3, OP_THICK = 4, OP_BEND83 = 5,
+                 OP_BEND82 = 6, OP_MKX = 7, OP_MKY = 8, OP_DKD82 = 9 };
+
+// Short-series bodies of sector bends and second-order quadrupoles: a lane
+// takes them when its particle is within kFastC3 of the reference
 // momentum, its transverse momenta (scaled by p0) stay below a bound through
 // the element, and its offsets below one that keeps the slice rotations inside
 // the quaternion series.  Both are decided at the entrance from these bounds
@@ -100,20 +112,6 @@ enum : int32_t { F_SPIN32 = 1, F_FRINGE = 2, F_FAST = 4 };
 //             quadrupole's kick of 2.5 mrad at 3 cm takes 1.3 % of a Gaussian
 //             bunch's passages beyond kFastMom, which would send half of the
 //             waves through both bodies; 3e-6 beyond twice that)
-struct FastBendParams {
-  double x_max, mom, turn_c, turn_x;
-  double hw_eta_h, hw_h;                // (ds/2) η h and (ds/2) h
-};
-struct FastQuadParams {
-  double x_max, mom_p, mom_x, reach;
-  double hw_k1;                         // (ds/2) k1
-};
-constexpr int kFastWords = sizeof(FastBendParams) / sizeof(double);
-union FastParams {
-  FastBendParams b;
-  FastQuadParams q;
-  double v[kFastWords];
-};
 constexpr double kFastC3 = 0.125;       // |P² - 1|
 constexpr double kFastMom = 0.0036;     // below 2^-8 sqrt(1 - kFastC3)
 constexpr double kFastQuadAngle = 0.029; // half the slice rotation of a quadrupole edge
@@ -125,7 +123,6 @@ struct DevElem {
   // Romberg edge rotations of sliced elements: half the step w ds of an end
   // edge (w = 1/2) and of an interior edge (w = 1), and their squares
   double hw_end, hw_in, hw2_end, hw2_in;
-  FastParams fast;         // (F_FAST)
   union {
     BendParams b;
     TeapotParams tp;
@@ -133,10 +130,40 @@ struct DevElem {
     RbendParams rb;
     QuadParams q;
     Quad4Params q4;
-    DriftParams d;
     ThinParams t;
     SnakeParams s;
     double v[kElemWords];
+  };
+};
+
+struct HotBend {           // short-series sector bend (OP_BEND83, OP_BEND82)
+  double cs, sn, omc;      // one slice
+  double h, eta_h, inv_eta_h, eta, one_m_eta2;
+  double s_eta, tconst;    // the whole bend
+  double x_max, mom, turn_c, turn_x;
+  double hw_eta_h, hw_h;   // (ds/2) η h and (ds/2) h
+  double w_cs, w_sn, w_omc;  // the whole bend (orbit-only passes)
+};
+struct HotQuad {           // short-series quadrupole (OP_MKX, OP_MKY, OP_DKD82)
+  QuadParams q;
+  double hw_k1;            // (ds/2) k1
+  double x_max, mom_p, mom_x, reach;
+};
+constexpr int kHotWords = sizeof(HotBend) / sizeof(double);
+static_assert(sizeof(HotQuad) <= sizeof(HotBend), "record size");
+
+struct Record {
+  int32_t op, flags;
+  int32_t count;           // lattice elements of the record (1 or 2)
+  int32_t elem;            // index of the element in the table of elements
+  double tail;             // length of the drift after the element (F_TAIL); a drift by itself is
+                           // OP_NONE with a tail
+  union {
+    HotBend b;
+    HotQuad q;
+    ThinParams t;
+    SnakeParams s;
+    double v[kHotWords];
   };
 };
 
@@ -146,27 +173,25 @@ struct TrackArgs {
   int32_t* alive;     // n
   double* qout;       // 4 × n SoA or null
   int64_t n;
+  const Record* rec;
   const DevElem* tab;
-  const uint32_t* seq;
-  int32_t n_elems;
+  const uint32_t* seq;   // n_records indices and one more, 0 (read ahead, not used)
+  int32_t n_records;
   int32_t turns;
   int32_t report_every;
   int32_t n_blocks;
   double* partials;   // [n_reports][n_blocks][4]
   double beta0, inv_beta0, gamma0, inv_gamma0_sq, G, aperture;
   double ymax;        // largest (θ/2)² the quaternion polynomial covers
-  // surrogate tracking: lanes with fallback[j] == 0 skip the spin arithmetic
-  const int32_t* fallback;
+  int64_t lane0;      // first lane of the launch in the lane order
   // optional lane order: lane g works on particle perm[g] (a permutation of
   // 0..n-1), so that particles taking the same path share waves
   const int32_t* perm;
-  // surrogate tracking over several turns (null otherwise): the particles on
-  // the network are lanes g < feat_n (the lane order puts them first); such a
-  // lane writes its network inputs at the start of every turn,
-  // feat[(turn * feat_n + g) * feat_n_in + i] = (z_i - center_i) *
-  // inv_scale_i (i < 6) and extra (i = 6), and the number of turns it
-  // completes alive, turns_done[g]; these lanes run on an orbit-only kernel,
-  // the lanes from feat_n on (the particles that fall back) on the full one
+  // orbit-only launches: the particles on the network are lanes g < feat_n
+  // (the lane order puts them first); such a lane writes its network inputs at
+  // the start of every turn, feat[(turn * feat_n + g) * feat_n_in + i] =
+  // (z_i - center_i) * inv_scale_i (i < 6) and extra (i = 6), and the number of
+  // turns it completes alive, turns_done[g]
   float* feat;
   int32_t* turns_done;
   int64_t feat_n;

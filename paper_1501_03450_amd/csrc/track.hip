@@ -27,6 +27,7 @@ namespace {
 constexpr int kBlock = 256;
 
 typedef const DevElem __attribute__((address_space(4))) ConstElem;
+typedef const Record __attribute__((address_space(4))) ConstRecord;
 typedef const uint32_t __attribute__((address_space(4))) ConstSeq;
 
 // Member-wise copy of one element record out of the constant address space
@@ -44,10 +45,20 @@ __device__ __forceinline__ DevElem load_elem(const ConstElem* p) {
   d.hw2_end = p->hw2_end;
   d.hw2_in = p->hw2_in;
   #pragma unroll
-  for (int i = 0; i < kFastWords; ++i) d.fast.v[i] = p->fast.v[i];
-#pragma unroll
   for (int i = 0; i < kElemWords; ++i) d.v[i] = p->v[i];
   return d;
+}
+
+__device__ __forceinline__ Record load_record(const ConstRecord* p) {
+  Record r;
+  r.op = p->op;
+  r.flags = p->flags;
+  r.count = p->count;
+  r.elem = p->elem;
+  r.tail = p->tail;
+#pragma unroll
+  for (int i = 0; i < kHotWords; ++i) r.v[i] = p->v[i];
+  return r;
 }
 
 // Waves per SIMD the register allocation aims at: two, for every variant.
@@ -62,7 +73,7 @@ __device__ __forceinline__ DevElem load_elem(const ConstElem* p) {
 #define ST_WAVES_PER_EU_WIDE 2
 #endif
 #ifndef ST_WAVES_PER_EU_ORBIT
-#define ST_WAVES_PER_EU_ORBIT 3
+#define ST_WAVES_PER_EU_ORBIT 4
 #endif
 
 // Romberg spin integration through one thick element, fused with its orbit
@@ -356,7 +367,8 @@ struct RombergWeights {
 
 // Level products over the slice edges of an element with NS slices and KS + 1
 // rows, from o = (ds/2) Ω: NT series terms, or single precision (S32).
-template <int NT, int NS, int KS, bool S32>
+// SPIN false: the orbit only.
+template <int NT, int NS, int KS, bool S32, bool SPIN>
 struct SpinLevels {
   static_assert(KS >= 0 && KS < kMaxRows && NS % (1 << KS) == 0, "NS slices divisible by 2^KS");
   Quat q[KS + 1];
@@ -367,6 +379,7 @@ struct SpinLevels {
       for (int m = 0; m <= KS; ++m) c[m] = qc_ident();
   }
   __device__ __forceinline__ void fold(int j, double ox, double oy, double oz) {
+    if constexpr (!SPIN) return;
     const bool end = j == 0 || j == NS;
     const double y = (end ? 0.25 : 1.0) * fma(ox, ox, fma(oy, oy, oz * oz));
     if constexpr (S32) {
@@ -398,6 +411,7 @@ struct SpinLevels {
   }
   // V_K[0] over its weight of level 0
   __device__ __forceinline__ Quat limit() {
+    if constexpr (!SPIN) return Quat{};
     constexpr RombergWeights<KS> w{};
     if constexpr (S32)
       for (int m = 0; m <= KS; ++m) q[m] = qc_to_double(c[m]);
@@ -414,65 +428,71 @@ struct SpinLevels {
 };
 
 // v = Px²/Pα² and F = Ps - Pα at a bend's edge.
-__device__ __forceinline__ void fast_bend_edge(double Px, double invPa, double& v, double& F) {
+__device__ __forceinline__ void fast_bend_edge(double Px, double invPa, const Particle& p, double& v,
+                                               double& F) {
   const double t = Px * Px * invPa;
   v = t * invPa;
-  F = -t * fma(v, fma(v, 0.0625, 0.125), 0.5);
+  F = -t * fma(v, fma(v, 0.0625, p.k18), 0.5);
 }
 
-template <int NT, int NS, int KS, bool S32>
-__device__ __forceinline__ Quat fast_bend(const DevElem& el, double& X, double& Px, double& Y,
+// Without spin the bend is crossed in one step.
+template <int NT, int NS, int KS, bool S32, bool SPIN = true>
+__device__ __forceinline__ Quat fast_bend(const HotBend& el, double& X, double& Px, double& Y,
                                           double& Py, double& T, const Particle& p) {
-  SpinLevels<NT, NS, KS, S32> lev;
-  const BendStep& k = el.b.slice;
+  SpinLevels<NT, NS, KS, S32, SPIN> lev;
+  const double cs = SPIN ? el.cs : el.w_cs, sn = SPIN ? el.sn : el.w_sn;
+  const double omc = SPIN ? el.omc : el.w_omc;
   const double w = Py * Py * p.invP2();
-  const double invPa = fma(p.invP * w, fma(w, fma(w, 0.3125, 0.375), 0.5), p.invP);
+  const double invPa = fma(p.invP * w, fma(w, fma(w, 0.3125, p.k38), 0.5), p.invP);
   const double Pa = fma(-Py, Py, p.P2()) * invPa;
   double v, F;
-  fast_bend_edge(Px, invPa, v, F);
+  fast_bend_edge(Px, invPa, p, v, F);
   const double Px_in = Px, W_in = Pa + F;
-  double wme = (el.b.one_m_eta2 + ((p.c3 - Py * Py) - Px * Px)) * rcp_nr(W_in + el.b.eta);
+  double wme = (el.one_m_eta2 + ((p.c3 - Py * Py) - Px * Px)) * rcp_nr(W_in + el.eta);
   const double b = p.a2() * Py * p.invP2();                     // Ω without its path factor
-  const double kf = el.fast.b.hw_eta_h * invPa;
-  const double ky = kf * fma(-b, Py, p.a1()), kx = kf * b, kz = el.fast.b.hw_eta_h * b;
+  const double kf = el.hw_eta_h * invPa;
+  const double ky = kf * fma(-b, Py, p.a1()), kx = kf * b, kz = el.hw_eta_h * b;
 #pragma unroll
-  for (int j = 0; j <= NS; ++j) {
+  for (int j = 0; j <= (SPIN ? NS : 1); ++j) {
     if (j > 0) {
-      const double A = fma(-el.b.eta_h, X, wme), F0 = F;
-      const double px1 = fma(Px, k.cs, A * k.sn);
-      fast_bend_edge(px1, invPa, v, F);
+      const double A = fma(-el.eta_h, X, wme), F0 = F;
+      const double px1 = fma(Px, cs, A * sn);
+      fast_bend_edge(px1, invPa, p, v, F);
       const double dW = F - F0;
-      X = fma(X, k.cs, fma(wme, k.omc, fma(Px, k.sn, dW)) * el.b.inv_eta_h);
+      X = fma(X, cs, fma(wme, omc, fma(Px, sn, dW)) * el.inv_eta_h);
       wme += dW;
       Px = px1;
     }
-    const double path = fma(el.b.h, X, 1.0);
-    const double g = path * fma(v, fma(v, 0.375, 0.5), 1.0);     // path Pα/Ps
-    lev.fold(j, (g * kx) * Px, fma(-g, ky, el.fast.b.hw_h), path * kz);
+    const double path = fma(el.h, X, 1.0);
+    const double g = path * fma(v, fma(v, p.k38, 0.5), 1.0);     // path Pα/Ps
+    lev.fold(j, (g * kx) * Px, fma(-g, ky, el.hw_h), path * kz);
   }
   // the slices' angle differences telescope; |sin| < 0.008 here
   const double sd = fma(Px_in, Pa + F, -Px * W_in) * (invPa * invPa);
   const double s2 = sd * sd;
   const double D = fma(sd * s2, fma(s2, fma(s2, AC<3>::v, AC<2>::v), AC<1>::v), sd);
-  const BendLane bl = bend_lane(el.b, el.b.whole, p);
-  Y = fma(Py, fma(D, el.b.inv_eta_h, el.b.whole.s_eta), Y);
-  T += fma(-bl.ibh, D, bl.c0);
+  Y = fma(Py, fma(D, el.inv_eta_h, el.s_eta), Y);
+  T += fma(-(p.ib() * el.inv_eta_h), D, fma(-p.Pt, el.s_eta, el.tconst));
   return lev.limit();
 }
 
-// Whether a lane takes the element's short-series body (FastParams).
-__device__ __forceinline__ bool fast_lane(const DevElem& el, double X, double Px, double Y,
+// Whether a lane takes the element's short-series body (FastParams).  The
+// conditions are combined without branches.
+__device__ __forceinline__ bool fast_lane(const Record& r, double X, double Px, double Y,
                                           double Py, const Particle& p) {
-  if (!(el.flags & F_FAST)) return false;
-  if (el.kind == K_SBEND) {
-    if (el.nsl != 8 || (el.K != 3 && el.K != 2)) return false;
-    return fma(el.fast.b.turn_x, fabs(X), fma(el.fast.b.turn_c, fabs(p.c3), fabs(Px))) <= el.fast.b.mom &&
-           fabs(Py) <= kFastMom && fabs(X) <= el.fast.b.x_max && fabs(p.c3) <= kFastC3;
+  bool in = fabs(p.c3) <= kFastC3;
+  if (r.op < OP_MKX) {
+    const HotBend& f = r.b;
+    in &= fma(f.turn_x, fabs(X), fma(f.turn_c, fabs(p.c3), fabs(Px))) <= f.mom;
+    in &= fabs(Py) <= kFastMom;
+    in &= fabs(X) <= f.x_max;
+  } else {
+    const HotQuad& f = r.q;
+    const double R = fabs(X) + fabs(Y), Q = fabs(Px) + fabs(Py);
+    in &= fma(f.mom_x, R, f.mom_p * Q) <= 2.0 * kFastMom;
+    in &= fma(f.reach, Q, R) <= f.x_max;
   }
-  if (el.K != 2 || el.nsl != (el.orbit == M_MK ? 4 : 8)) return false;
-  const double R = fabs(X) + fabs(Y), Q = fabs(Px) + fabs(Py);
-  return fma(el.fast.q.mom_x, R, el.fast.q.mom_p * Q) <= 2.0 * kFastMom &&
-         fma(el.fast.q.reach, Q, R) <= el.fast.q.x_max && fabs(p.c3) <= kFastC3;
+  return in;
 }
 
 // (ds/2) Ω at an edge of a quadrupole: rho = P/Ps, ka = -(ds/2) k1 a1/P,
@@ -490,12 +510,12 @@ __device__ __forceinline__ void fast_quad_omega(double ka, double kg, double inv
 constexpr int kFastQuadTerms = 4;
 
 // Matrix-kick quadrupole (KIND 1 focusing in x, 3 in y).
-template <int KIND, int NS, int KS, bool S32>
-__device__ __forceinline__ Quat fast_mk(const DevElem& el, double& X, double& Px, double& Y,
+template <int KIND, int NS, int KS, bool S32, bool SPIN = true>
+__device__ __forceinline__ Quat fast_mk(const HotQuad& el, double& X, double& Px, double& Y,
                                         double& Py, double& T, const Particle& p, MKCache* mkc) {
-  SpinLevels<kFastQuadTerms, NS, KS, S32> lev;
+  SpinLevels<kFastQuadTerms, NS, KS, S32, SPIN> lev;
   const MKLin m = mk_cached(el.q, p, mkc);
-  const double ka = -el.fast.q.hw_k1 * p.a1() * p.invP, kg = el.fast.q.hw_k1 * p.a2() * p.invP2();
+  const double ka = -el.hw_k1 * p.a1() * p.invP, kg = el.hw_k1 * p.a2() * p.invP2();
   const double kP = fabs(el.q.k1) * p.P(), xp_in = fma(X, Px, Y * Py);
   const double dsp = el.q.ds * p.invP;
   double esum = 0.0, tk = 0.0;
@@ -505,10 +525,10 @@ __device__ __forceinline__ Quat fast_mk(const DevElem& el, double& X, double& Px
       if (KIND == 1) mk_move(m, X, Px, Y, Py);
       else           mk_move(m, Y, Py, X, Px);
       const double u = fma(Px, Px, Py * Py) * p.invP2(), u2 = u * u;
-      const double d = dsp * (u * fma(u, fma(u, 0.3125, 0.375), 0.5));   // ds (1/Ps - 1/P)
+      const double d = dsp * (u * fma(u, fma(u, 0.3125, p.k38), 0.5));   // ds (1/Ps - 1/P)
       X = fma(Px, d, X);
       Y = fma(Py, d, Y);
-      tk = fma(u2, fma(u, 0.21875, 0.25), tk);                   // g - u (u/2 + g)/4
+      tk = fma(u2, fma(u, 0.21875, p.k14), tk);                   // g - u (u/2 + g)/4
       if (KIND == 1) mk_move(m, X, Px, Y, Py);
       else           mk_move(m, Y, Py, X, Px);
     }
@@ -517,7 +537,7 @@ __device__ __forceinline__ Quat fast_mk(const DevElem& el, double& X, double& Px
     esum = (j == 0 || j == NS) ? fma(0.5, inv, esum) : esum + inv;
     const double u = pp * p.invP2();
     double ox, oy, oz;
-    fast_quad_omega(ka, kg, p.invP, fma(u, fma(u, fma(u, 0.3125, 0.375), 0.5), 1.0), X, Px, Y, Py,
+    fast_quad_omega(ka, kg, p.invP, fma(u, fma(u, fma(u, 0.3125, p.k38), 0.5), 1.0), X, Px, Y, Py,
                     ox, oy, oz);
     lev.fold(j, ox, oy, oz);
   }
@@ -527,11 +547,11 @@ __device__ __forceinline__ Quat fast_mk(const DevElem& el, double& X, double& Px
 
 // Drift-kick-drift quadrupole: the two half drifts that meet at an interior
 // edge have the same momenta, which Ω at that edge uses too.
-template <int NS, int KS, bool S32>
-__device__ __forceinline__ Quat fast_dkd(const DevElem& el, double& X, double& Px, double& Y,
+template <int NS, int KS, bool S32, bool SPIN = true>
+__device__ __forceinline__ Quat fast_dkd(const HotQuad& el, double& X, double& Px, double& Y,
                                          double& Py, double& T, const Particle& p) {
-  SpinLevels<kFastQuadTerms, NS, KS, S32> lev;
-  const double ka = -el.fast.q.hw_k1 * p.a1() * p.invP, kg = el.fast.q.hw_k1 * p.a2() * p.invP2();
+  SpinLevels<kFastQuadTerms, NS, KS, S32, SPIN> lev;
+  const double ka = -el.hw_k1 * p.a1() * p.invP, kg = el.hw_k1 * p.a2() * p.invP2();
   double esum = 0.0, e = 0.0, c = 0.0;          // e = P/Ps - 1, c = (ds/2)/Ps
 #pragma unroll
   for (int j = 0; j <= NS; ++j) {
@@ -543,7 +563,7 @@ __device__ __forceinline__ Quat fast_dkd(const DevElem& el, double& X, double& P
     }
     const double u = fma(Px, Px, Py * Py) * p.invP2();
     const double e0 = e;
-    e = u * fma(u, fma(u, 0.3125, 0.375), 0.5);
+    e = u * fma(u, fma(u, 0.3125, p.k38), 0.5);
     if (j > 0) esum += e0;
     c = el.q.hds * fma(p.invP, e, p.invP);
     if (j > 0) {
@@ -631,8 +651,26 @@ __device__ __forceinline__ Quat pwc_element(const DevElem& el, double& X, double
     W = ps2 * r;
     wme = (el.b.one_m_eta2 + ((p.c3 - Py * Py) - Px * Px)) * rcp_nr(W + el.b.eta);
   }
+  // drift-kick half slices: the two drifts that meet between kicks have the
+  // same momenta, which Ω there uses too
+  constexpr bool DKD = KIND == 2 && PLACE == P_MIDPOINT && !Y4;
+  PsInv ps{0.0, 0.0};
+  double esum = 0.0;
+  if constexpr (DKD) ps = ps_inverse(fma(Px, Px, Py * Py), p);
   for (int j = 1; j <= el.nsl; ++j) {
-    if (PLACE == P_KICK) {
+    if constexpr (DKD) {
+      double c = el.q.hds * ps.r;
+      X = fma(c, Px, X);
+      Y = fma(c, Py, Y);
+      esum += ps.e;
+      Px = fma(-el.q.k1ds, X, Px);
+      Py = fma(el.q.k1ds, Y, Py);
+      ps = ps_inverse(fma(Px, Px, Py * Py), p);
+      c = el.q.hds * ps.r;
+      X = fma(c, Px, X);
+      Y = fma(c, Py, Y);
+      esum += ps.e;
+    } else if (PLACE == P_KICK) {
       if (KIND == 4) {
         teapot_drift(el.tp, X, Px, Y, Py, T, p);
         teapot_kick(el.tp, 0.5 * el.tp.ds, X, Px);
@@ -651,7 +689,8 @@ __device__ __forceinline__ Quat pwc_element(const DevElem& el, double& X, double
       quad_step2<KIND>(el.q, mc, X, Px, Y, Py, T, p, a);
     }
     if (PLACE == P_KICK || (j & 1)) {
-      if (KIND != 0) r = rsqrt_nr(p.P2() - fma(Px, Px, Py * Py));
+      if constexpr (DKD) r = ps.r;
+      else if (KIND != 0) r = ps_inverse(fma(Px, Px, Py * Py), p).r;
       double ox, oy, oz;
       if (KIND == 0)      omega_bend(el.b, X, Px, Py, r, p, ox, oy, oz);
       else if (KIND == 4) omega_dipole(el.tp.h, el.tp.eta_h, X, Px, Py, r, p, ox, oy, oz);
@@ -672,6 +711,8 @@ __device__ __forceinline__ Quat pwc_element(const DevElem& el, double& X, double
       }
     }
   }
+  if constexpr (DKD)
+    T -= el.q.hds * fma(p.invbeta(), esum, 2.0 * el.nsl * p.dib);
   const double inv = rsqrt_near_one(fma(Q.w, Q.w, fma(Q.x, Q.x, fma(Q.y, Q.y, Q.z * Q.z))));
   return {Q.w * inv, Q.x * inv, Q.y * inv, Q.z * inv};
 }
@@ -893,15 +934,15 @@ __device__ __forceinline__ Quat thick_ext(const DevElem& el, double& X, double& 
 }
 
 template <int NT>
-__device__ __forceinline__ Quat thin_element(const DevElem& e, double X, double& Px, double Y,
+__device__ __forceinline__ Quat thin_element(const ThinParams& e, double X, double& Px, double Y,
                                              double& Py, const Particle& p, const TrackArgs& a) {
-  const double hk1 = 0.5 * e.t.k1l, hk2 = 0.5 * e.t.k2l;
+  const double hk1 = 0.5 * e.k1l, hk2 = 0.5 * e.k2l;
   Px -= fma(hk1, X, 0.5 * hk2 * (X * X - Y * Y));
   Py += fma(hk1, Y, hk2 * X * Y);
   double ps2 = p.P2() - fma(Px, Px, Py * Py);
   double r = rsqrt_omega(ps2);
-  double bx = fma(e.t.k2l * X, Y, e.t.k1l * Y);
-  double by = fma(e.t.k1l, X, 0.5 * e.t.k2l * (X * X - Y * Y));
+  double bx = fma(e.k2l * X, Y, e.k1l * Y);
+  double by = fma(e.k1l, X, 0.5 * e.k2l * (X * X - Y * Y));
   double ox, oy, oz;
   omega_straight(bx, by, Px, Py, r, p, ox, oy, oz);
   const double y = 0.25 * fma(ox, ox, fma(oy, oy, oz * oz));
@@ -912,72 +953,115 @@ __device__ __forceinline__ Quat thin_element(const DevElem& e, double X, double&
   return {c, sfac * ox, sfac * oy, sfac * oz};
 }
 
-// Products of a particle's constants are formed where an element uses them: the
-// compiler would otherwise move all of them out of the element loop, keep them
-// in registers for every kind of element, and spill (124 B a lane).
-__device__ __forceinline__ void keep_in_loop(Particle& p) {
-  asm volatile("" : "+v"(p.c3), "+v"(p.invP), "+v"(p.invP2_), "+v"(p.invbeta_), "+v"(p.a1_),
-                    "+v"(p.a2_), "+v"(p.Pt));
-}
-
 __device__ __forceinline__ double wave_sum(double v) {
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
   return v;
 }
 
-// SURR: surrogate tracking; lanes with fallback[j] == 0 leave the spin to the
-// network (the caller rotates it), and waves without a fallback lane skip the
-// spin arithmetic altogether.
-// Sector bends and DKD/MK quadrupoles of the standard rings: the short-series
-// bodies are unrolled for sector bends with 8 slices and 3 or 4 rows, MK
-// quadrupoles with 4 slices and 3 rows, DKD quadrupoles with 8 slices and 3
-// rows; other elements and lanes take the general body.
-// S32: the element's spin edges in single precision (mixed mode).
-template <int NT, bool S32>
-__device__ __forceinline__ Quat standard_thick(const DevElem& e, double& X, double& Px, double& Y,
-                                               double& Py, double& T, const Particle& p,
-                                               const TrackArgs& a, MKCache* mkc) {
-  Quat q;
-  const bool fast = fast_lane(e, X, Px, Y, Py, p);
-  if (fast) {
-    if (e.kind == K_SBEND) {
-      if (e.K == 3) q = fast_bend<NT, 8, 3, S32>(e, X, Px, Y, Py, T, p);
-      else          q = fast_bend<NT, 8, 2, S32>(e, X, Px, Y, Py, T, p);
-    } else if (e.orbit != M_MK) {
-      q = fast_dkd<8, 2, S32>(e, X, Px, Y, Py, T, p);
-    } else if (e.q.k1 >= 0.0) {
-      q = fast_mk<1, 4, 2, S32>(e, X, Px, Y, Py, T, p, mkc);
-    } else {
-      q = fast_mk<3, 4, 2, S32>(e, X, Px, Y, Py, T, p, mkc);
-    }
-  }
-  if (!fast) {
-    if (e.kind == K_SBEND)    q = thick_element<NT, 0, S32>(e, X, Px, Y, Py, T, p, a);
-    else if (e.orbit != M_MK) q = thick_element<NT, 2, S32>(e, X, Px, Y, Py, T, p, a);
-    else if (e.q.k1 >= 0.0)   q = thick_element<NT, 1, S32>(e, X, Px, Y, Py, T, p, a, mkc);
-    else                      q = thick_element<NT, 3, S32>(e, X, Px, Y, Py, T, p, a, mkc);
-  }
-  return q;
+// The short-series body of a record (op from OP_BEND83 on).
+template <int NT, bool S32, bool SPIN>
+__device__ __forceinline__ Quat fast_thick(const Record& r, double& X, double& Px, double& Y,
+                                           double& Py, double& T, const Particle& p,
+                                           MKCache* mkc) {
+  if (r.op == OP_MKX) return fast_mk<1, 4, 2, S32, SPIN>(r.q, X, Px, Y, Py, T, p, mkc);
+  if (r.op == OP_MKY) return fast_mk<3, 4, 2, S32, SPIN>(r.q, X, Px, Y, Py, T, p, mkc);
+  if (r.op == OP_BEND83) return fast_bend<NT, 8, 3, S32, SPIN>(r.b, X, Px, Y, Py, T, p);
+  if (r.op == OP_DKD82) return fast_dkd<8, 2, S32, SPIN>(r.q, X, Px, Y, Py, T, p);
+  return fast_bend<NT, 8, 2, S32, SPIN>(r.b, X, Px, Y, Py, T, p);
 }
 
-// EXT: the kernel also knows the drift-kick sector bend and the piece-wise
-// constant spin placements (kept out of the other instantiations so that
-// their register allocation is not shaped by code they never run).
+// The general body of a sector bend or a second-order quadrupole with the spin
+// at the slice edges.
+template <int NT, bool S32, bool SPIN>
+__device__ __forceinline__ Quat general_thick(const DevElem& e, double& X, double& Px, double& Y,
+                                              double& Py, double& T, const Particle& p,
+                                              const TrackArgs& a, MKCache* mkc) {
+  if constexpr (SPIN) {
+    if (e.kind == K_SBEND)    return thick_element<NT, 0, S32>(e, X, Px, Y, Py, T, p, a);
+    if (e.orbit != M_MK)      return thick_element<NT, 2, S32>(e, X, Px, Y, Py, T, p, a);
+    if (e.q.k1 >= 0.0)        return thick_element<NT, 1, S32>(e, X, Px, Y, Py, T, p, a, mkc);
+    return thick_element<NT, 3, S32>(e, X, Px, Y, Py, T, p, a, mkc);
+  } else {
+    if (e.kind == K_SBEND)    thick_orbit<0>(e, X, Px, Y, Py, T, p, a);
+    else if (e.orbit != M_MK) thick_orbit<2>(e, X, Px, Y, Py, T, p, a);
+    else if (e.q.k1 >= 0.0)   thick_orbit<1>(e, X, Px, Y, Py, T, p, a, mkc);
+    else                      thick_orbit<3>(e, X, Px, Y, Py, T, p, a, mkc);
+    return Quat{};
+  }
+}
+
+// Elements of the extended kernels (OP_EXT).
+template <int NT>
+__device__ __forceinline__ Quat ext_element(const DevElem& e, double& X, double& Px, double& Y,
+                                            double& Py, double& T, const Particle& p,
+                                            const TrackArgs& a) {
+  if (e.kind == K_RBEND) {
+    if (e.place == P_MIDPOINT) return rbend_element<NT, P_MIDPOINT>(e, X, Px, Y, Py, T, p, a);
+    return rbend_element<NT, P_EDGES>(e, X, Px, Y, Py, T, p, a);
+  }
+  if (e.kind == K_SOLENOID) {
+    if (e.place == P_MIDPOINT) return solenoid_element<NT, P_MIDPOINT>(e, X, Px, Y, Py, T, p, a);
+    return solenoid_element<NT, P_EDGES>(e, X, Px, Y, Py, T, p, a);
+  }
+  if (e.kind == K_SBEND) {
+    if (e.orbit == M_TEAPOT) return thick_ext<NT, 4>(e, X, Px, Y, Py, T, p, a);
+    return thick_ext<NT, 0>(e, X, Px, Y, Py, T, p, a);
+  }
+  if (e.orbit == M_DKD || e.orbit == M_DKD4) return thick_ext<NT, 2>(e, X, Px, Y, Py, T, p, a);
+  if (e.q.k1 >= 0.0) return thick_ext<NT, 1>(e, X, Px, Y, Py, T, p, a);
+  return thick_ext<NT, 3>(e, X, Px, Y, Py, T, p, a);
+}
+
+template <int NT>
+__device__ __forceinline__ void ext_orbit(const DevElem& e, double& X, double& Px, double& Y,
+                                          double& Py, double& T, const Particle& p,
+                                          const TrackArgs& a) {
+  if (e.kind == K_RBEND) {
+    rbend_rotate(e.rb.in, X, Px, Y, Py, T, p);
+    rbend_fringe(e.rb, 1.0, X, Px, Y, Py, T, p);
+    rbend_body(e.rb, e.rb.L, X, Px, Y, Py, T, p);
+    X -= e.rb.xoff;
+    rbend_fringe(e.rb, -1.0, X, Px, Y, Py, T, p);
+    rbend_rotate(e.rb.out, X, Px, Y, Py, T, p);
+    T += e.rb.larc_ib0;
+  } else if (e.kind == K_SOLENOID) {
+    const SolState st = sol_state<NT>(e.sol, X, Px, Y, Py, p, a.ymax, a.inv_beta0);
+    for (int jj = 0; jj < e.nsl; ++jj) solenoid_slice(e.sol, st, X, Px, Y, Py, T);
+  } else if (e.kind == K_SBEND) {
+    if (e.orbit == M_TEAPOT) thick_orbit<4>(e, X, Px, Y, Py, T, p, a);
+    else                     thick_orbit<0>(e, X, Px, Y, Py, T, p, a);
+  } else if (e.orbit == M_DKD4) {
+    thick_orbit<2, true>(e, X, Px, Y, Py, T, p, a);
+  } else if (e.orbit == M_MK4) {
+    if (e.q.k1 >= 0.0) thick_orbit<1, true>(e, X, Px, Y, Py, T, p, a);
+    else               thick_orbit<3, true>(e, X, Px, Y, Py, T, p, a);
+  } else if (e.orbit == M_DKD) {
+    thick_orbit<2>(e, X, Px, Y, Py, T, p, a);
+  } else if (e.q.k1 >= 0.0) {
+    thick_orbit<1>(e, X, Px, Y, Py, T, p, a);
+  } else {
+    thick_orbit<3>(e, X, Px, Y, Py, T, p, a);
+  }
+}
+
+// EXT: the kernel also knows the drift-kick sector bend, the piece-wise
+// constant spin placements, solenoids and rectangular bends (kept out of the
+// other instantiations so that their register allocation is not shaped by code
+// they never run).
 // ORBIT: the network turns of the particles on the network, the first
 // a.feat_n lanes of the lane order: the orbit only, with the network's inputs
-// written at the start of each turn. With ORBIT false, SURR launches leave
-// those lanes to the ORBIT launch and take the particles that fall back.
-template <int NT, bool MIXED, bool SURR, bool EXT, bool ORBIT>
+// written at the start of each turn.
+template <int NT, bool MIXED, bool EXT, bool ORBIT>
 __device__ __forceinline__ void track_body(const TrackArgs a) {
   __shared__ double red[kBlock / 64][4];
   // Cold per-lane data in LDS: the spin (touched once per turn) and the
   // orbit at the current element's entrance (read back only on a loss).
   __shared__ double cold[8][kBlock];
-  __shared__ double mk_slot[EXT ? 1 : kMKWords][kBlock];
+  __shared__ double mk_slot[kMKWords][kBlock];
   const int tid = threadIdx.x;
-  const int64_t g = (int64_t)blockIdx.x * kBlock + tid;
-  const bool valid = ORBIT ? g < a.feat_n : (g < a.n && !(SURR && g < a.feat_n));
+  const int64_t g = a.lane0 + (int64_t)blockIdx.x * kBlock + tid;
+  const bool valid = g < (ORBIT ? a.feat_n : a.n);
   const int64_t j = (valid && a.perm) ? (int64_t)a.perm[g] : g;
   int32_t status = valid ? a.alive[j] : 0;
   bool live = status == 1;
@@ -993,16 +1077,16 @@ __device__ __forceinline__ void track_body(const TrackArgs a) {
   // Without reports the kernel has no barrier, so a wave with no live lane
   // (a replay of a few particles) may leave at once.
   if (a.report_every == 0 && !__any(live)) {
-    if (ORBIT && a.turns_done && g < a.feat_n) a.turns_done[g] = 0;
+    if (ORBIT && a.turns_done && valid) a.turns_done[g] = 0;
     return;
   }
-  Particle p = make_particle(Pt, a);
+  const Particle p = make_particle(Pt, a);
   MKCache mkc{mk_slot, tid, __builtin_nan(""), __builtin_nan("")};
   Quat qturn = qident();
-  const bool spin_lane = !ORBIT && (!SURR || (valid && a.fallback[j] != 0));
   // The lattice is read-only for the whole launch: reading it through the
   // constant address space lets the uniform loads go through the scalar cache.
   const ConstElem* tab = (const ConstElem*)(a.tab);
+  const ConstRecord* rec = (const ConstRecord*)(a.rec);
   const ConstSeq* seq = (const ConstSeq*)(a.seq);
 
   int turns_done = 0;
@@ -1020,109 +1104,93 @@ __device__ __forceinline__ void track_body(const TrackArgs a) {
       f[5] = (float)((Pt - a.feat_center[5]) * a.feat_inv_scale[5]);
       if (a.feat_n_in == 7) f[6] = (float)a.feat_extra;
     }
-    for (int ie = 0; ie < a.n_elems; ++ie) {
-      const DevElem e = load_elem(tab + seq[ie]);
-      if (!live) continue;
-      keep_in_loop(p);
-      if (e.kind == K_DRIFT) {           // no spin; the entrance state is cheap to keep
-        const double X0 = X, Y0 = Y, T0 = T;
-        drift(e.d.L, X, Px, Y, Py, T, p, a.inv_beta0);
-        if (!(fabs(X) <= a.aperture && fabs(Y) <= a.aperture && isfinite(T))) {
-          X = X0; Y = Y0; T = T0;
-          live = false;
-          status = -(1 + ie);
-        }
-        continue;
-      }
-      cold[3][tid] = X; cold[4][tid] = Px; cold[5][tid] = Y; cold[6][tid] = Py; cold[7][tid] = T;
+    // A record is loaded while the one before it finishes (its loss check, the
+    // composition and the drift behind it), and its index one record earlier:
+    // loaded where they were used, the four dependent scalar loads of a record
+    // took a lone wave 0.59 of 3.0 million cycles a turn on the RHIC-scale ring.
+    Record r = load_record(rec + seq[0]);
+    uint32_t next = seq[min(1, a.n_records)];
+    int ie = 0;                  // lattice index of the record's first element
+    for (int ir = 0; ir < a.n_records; ++ir) {
+      const int op = r.op, flags = r.flags, count = r.count;
+      const double tail = r.tail;
       Quat q;
-      bool spin = true;
-      if (SURR && !__any(spin_lane)) {   // no lane of this wave needs the spin
-        spin = false;
-        if (e.kind == K_SBEND) {
-          if (EXT && e.orbit == M_TEAPOT) thick_orbit<4>(e, X, Px, Y, Py, T, p, a);
-          else                            thick_orbit<0>(e, X, Px, Y, Py, T, p, a);
-        } else if (EXT && e.kind == K_QUAD && (e.orbit == M_DKD4 || e.orbit == M_MK4)) {
-          if (e.orbit == M_DKD4)  thick_orbit<2, true>(e, X, Px, Y, Py, T, p, a);
-          else if (e.q.k1 >= 0.0) thick_orbit<1, true>(e, X, Px, Y, Py, T, p, a);
-          else                    thick_orbit<3, true>(e, X, Px, Y, Py, T, p, a);
-        } else if (e.kind == K_QUAD) {
-          MKCache* const c = EXT ? nullptr : &mkc;   // (the extended kernels keep no cache)
-          if (e.orbit != M_MK)    thick_orbit<2>(e, X, Px, Y, Py, T, p, a);
-          else if (e.q.k1 >= 0.0) thick_orbit<1>(e, X, Px, Y, Py, T, p, a, c);
-          else                    thick_orbit<3>(e, X, Px, Y, Py, T, p, a, c);
-        } else if (EXT && e.kind == K_RBEND) {
-          rbend_rotate(e.rb.in, X, Px, Y, Py, T, p);
-          rbend_fringe(e.rb, 1.0, X, Px, Y, Py, T, p);
-          rbend_body(e.rb, e.rb.L, X, Px, Y, Py, T, p);
-          X -= e.rb.xoff;
-          rbend_fringe(e.rb, -1.0, X, Px, Y, Py, T, p);
-          rbend_rotate(e.rb.out, X, Px, Y, Py, T, p);
-          T += e.rb.larc_ib0;
-        } else if (EXT && e.kind == K_SOLENOID) {
-          const SolState st = sol_state<NT>(e.sol, X, Px, Y, Py, p, a.ymax, a.inv_beta0);
-          for (int jj = 0; jj < e.nsl; ++jj) solenoid_slice(e.sol, st, X, Px, Y, Py, T);
-        } else if (e.kind == K_THIN) {
-          const double hk1 = 0.5 * e.t.k1l, hk2 = 0.5 * e.t.k2l;
-          for (int h = 0; h < 2; ++h) {
-            Px -= fma(hk1, X, 0.5 * hk2 * (X * X - Y * Y));
-            Py += fma(hk1, Y, hk2 * X * Y);
+      if (live && op != OP_NONE) {
+        cold[3][tid] = X; cold[4][tid] = Px; cold[5][tid] = Y; cold[6][tid] = Py;
+        cold[7][tid] = T;
+        if (op >= OP_THICK) {
+          // the mixed kernel carries both precisions; an element runs one
+          const bool s32 = MIXED && (flags & F_SPIN32);
+          bool fast = false;
+          if (op > OP_THICK) fast = fast_lane(r, X, Px, Y, Py, p);
+          if (fast) {
+            if (s32) q = fast_thick<NT, MIXED, !ORBIT>(r, X, Px, Y, Py, T, p, &mkc);
+            else     q = fast_thick<NT, false, !ORBIT>(r, X, Px, Y, Py, T, p, &mkc);
+          }
+          if (!fast) {
+            const DevElem e = load_elem(tab + r.elem);
+            if (s32) q = general_thick<NT, MIXED, !ORBIT>(e, X, Px, Y, Py, T, p, a, &mkc);
+            else     q = general_thick<NT, false, !ORBIT>(e, X, Px, Y, Py, T, p, a, &mkc);
+          }
+        } else if (EXT && op == OP_EXT) {
+          const DevElem e = load_elem(tab + r.elem);
+          if (ORBIT) ext_orbit<NT>(e, X, Px, Y, Py, T, p, a);
+          else       q = ext_element<NT>(e, X, Px, Y, Py, T, p, a);
+        } else if (op == OP_THIN) {
+          if (ORBIT) {
+            const double hk1 = 0.5 * r.t.k1l, hk2 = 0.5 * r.t.k2l;
+            for (int h = 0; h < 2; ++h) {
+              Px -= fma(hk1, X, 0.5 * hk2 * (X * X - Y * Y));
+              Py += fma(hk1, Y, hk2 * X * Y);
+            }
+          } else {
+            q = thin_element<NT>(r.t, X, Px, Y, Py, p, a);
+          }
+        } else {
+          q = {r.s.qw, r.s.qx, r.s.qy, r.s.qz};
+        }
+      }
+      r = load_record(rec + next);
+      next = seq[min(ir + 2, a.n_records)];
+      if (live) {
+        if (op != OP_NONE) {
+          bool ok = fabs(X) <= a.aperture;
+          ok &= fabs(Y) <= a.aperture;
+          ok &= isfinite(Px);
+          ok &= isfinite(Py);
+          ok &= isfinite(T);
+          if (!ok) {
+            X = cold[3][tid]; Px = cold[4][tid]; Y = cold[5][tid]; Py = cold[6][tid];
+            T = cold[7][tid];
+            live = false;
+            status = -(1 + ie);
+          } else if (!ORBIT) {
+            qturn = qmul(q, qturn);
           }
         }
-      } else if (EXT && e.kind == K_RBEND) {
-        if (e.place == P_MIDPOINT) q = rbend_element<NT, P_MIDPOINT>(e, X, Px, Y, Py, T, p, a);
-        else                       q = rbend_element<NT, P_EDGES>(e, X, Px, Y, Py, T, p, a);
-      } else if (EXT && e.kind == K_SOLENOID) {
-        if (e.place == P_MIDPOINT) q = solenoid_element<NT, P_MIDPOINT>(e, X, Px, Y, Py, T, p, a);
-        else                       q = solenoid_element<NT, P_EDGES>(e, X, Px, Y, Py, T, p, a);
-      } else if (EXT && (e.kind == K_SBEND || e.kind == K_QUAD)) {
-        if (e.kind == K_SBEND) {
-          if (e.orbit == M_TEAPOT) q = thick_ext<NT, 4>(e, X, Px, Y, Py, T, p, a);
-          else                     q = thick_ext<NT, 0>(e, X, Px, Y, Py, T, p, a);
-        } else {
-          if (e.orbit == M_DKD || e.orbit == M_DKD4) q = thick_ext<NT, 2>(e, X, Px, Y, Py, T, p, a);
-          else if (e.q.k1 >= 0.0) q = thick_ext<NT, 1>(e, X, Px, Y, Py, T, p, a);
-          else                    q = thick_ext<NT, 3>(e, X, Px, Y, Py, T, p, a);
+        if ((flags & F_TAIL) && live) {
+          cold[3][tid] = X; cold[5][tid] = Y; cold[7][tid] = T;
+          drift(tail, X, Px, Y, Py, T, p, a.inv_beta0);
+          bool ok = fabs(X) <= a.aperture;
+          ok &= fabs(Y) <= a.aperture;
+          ok &= isfinite(T);
+          if (!ok) {
+            X = cold[3][tid]; Y = cold[5][tid]; T = cold[7][tid];
+            live = false;
+            status = -(ie + count);
+          }
         }
-      } else switch (e.kind) {
-        case K_SBEND:
-        case K_QUAD:
-          // the mixed kernel carries both instantiations; an element runs one
-          if (MIXED && (e.flags & F_SPIN32))
-            q = standard_thick<NT, MIXED>(e, X, Px, Y, Py, T, p, a, &mkc);
-          else
-            q = standard_thick<NT, false>(e, X, Px, Y, Py, T, p, a, &mkc);
-          break;
-        case K_THIN:
-          q = thin_element<NT>(e, X, Px, Y, Py, p, a);
-          break;
-        case K_SNAKE:
-          q = {e.s.qw, e.s.qx, e.s.qy, e.s.qz};
-          break;
-        default:
-          spin = false;
-          break;
       }
-      const bool ok = fabs(X) <= a.aperture && fabs(Y) <= a.aperture && isfinite(Px) &&
-                      isfinite(Py) && isfinite(T);
-      if (!ok) {
-        X = cold[3][tid]; Px = cold[4][tid]; Y = cold[5][tid]; Py = cold[6][tid]; T = cold[7][tid];
-        live = false;
-        status = -(1 + ie);
-        continue;
-      }
-      if (spin) {
-        qturn = qmul(q, qturn);
-        // the short-series bodies leave their common factor (0.69 or more) in
-        if ((ie & 63) == 63) qturn = qnormalized(qturn);
-      }
+      ie += count;
+      // the short-series bodies leave their common factor (0.69 or more) in
+      if (!ORBIT && (ir & 31) == 31 && was_live) qturn = qnormalized(qturn);
     }
     if (was_live && live) ++turns_done;
-    if (!ORBIT && was_live) qturn = qnormalized(qturn);
     // A particle lost during this turn still receives the rotation of the
     // elements it completed before the loss.
     double sx = cold[0][tid], sy = cold[1][tid], sz = cold[2][tid];
-    if (was_live && spin_lane) {
+    if (!ORBIT && was_live) {
+      qturn = qnormalized(qturn);
       qrotate(qturn, sx, sy, sz);
       cold[0][tid] = sx; cold[1][tid] = sy; cold[2][tid] = sz;
     }
@@ -1143,7 +1211,7 @@ __device__ __forceinline__ void track_body(const TrackArgs a) {
     }
   }
 
-  if (ORBIT && a.turns_done && g < a.feat_n) a.turns_done[g] = turns_done;
+  if (ORBIT && a.turns_done && valid) a.turns_done[g] = turns_done;
   if (valid && a.alive[j] == 1) {
     a.z[j] = X; a.z[n + j] = Px; a.z[2 * n + j] = Y; a.z[3 * n + j] = Py; a.z[4 * n + j] = T;
     if (!ORBIT) {
@@ -1157,20 +1225,20 @@ __device__ __forceinline__ void track_body(const TrackArgs a) {
   }
 }
 
-template <int NT, bool MIXED, bool SURR, bool EXT>
+template <int NT, bool MIXED, bool EXT>
 __global__ void __launch_bounds__(kBlock)
-__attribute__((amdgpu_waves_per_eu((MIXED || SURR || EXT) ? ST_WAVES_PER_EU_WIDE : ST_WAVES_PER_EU)))
+__attribute__((amdgpu_waves_per_eu((MIXED || EXT) ? ST_WAVES_PER_EU_WIDE : ST_WAVES_PER_EU)))
 track_kernel(const TrackArgs a) {
-  track_body<NT, MIXED, SURR, EXT, false>(a);
+  track_body<NT, MIXED, EXT, false>(a);
 }
 
 // Without the spin arithmetic the orbit push needs about 140 registers, so
 // three waves share a SIMD (the LDS of three workgroups fits a CU).
 template <int NT, bool EXT>
 __global__ void __launch_bounds__(kBlock)
-__attribute__((amdgpu_waves_per_eu(ST_WAVES_PER_EU_ORBIT)))
+__attribute__((amdgpu_waves_per_eu(EXT ? 2 : ST_WAVES_PER_EU_ORBIT)))
 orbit_kernel(const TrackArgs a) {
-  track_body<NT, false, true, EXT, true>(a);
+  track_body<NT, false, EXT, true>(a);
 }
 
 // Deterministic second pass of the polarization reduction: one block per
@@ -1203,52 +1271,41 @@ __global__ void __launch_bounds__(256) reduce_polarization_kernel(const double* 
 
 int track_block_size() { return kBlock; }
 
-template <bool MIXED, bool SURR, bool EXT>
+template <bool MIXED, bool EXT>
 hipError_t launch_nt(const TrackArgs& a, int nt, hipStream_t stream) {
   const dim3 grid((unsigned)a.n_blocks), block(kBlock);
   switch (nt) {
-    case 5:  hipLaunchKernelGGL((track_kernel<5, MIXED, SURR, EXT>), grid, block, 0, stream, a); break;
-    case 6:  hipLaunchKernelGGL((track_kernel<6, MIXED, SURR, EXT>), grid, block, 0, stream, a); break;
-    case 8:  hipLaunchKernelGGL((track_kernel<8, MIXED, SURR, EXT>), grid, block, 0, stream, a); break;
-    case 12: hipLaunchKernelGGL((track_kernel<12, MIXED, SURR, EXT>), grid, block, 0, stream, a); break;
-    default: hipLaunchKernelGGL((track_kernel<16, MIXED, SURR, EXT>), grid, block, 0, stream, a); break;
+    case 5:  hipLaunchKernelGGL((track_kernel<5, MIXED, EXT>), grid, block, 0, stream, a); break;
+    case 6:  hipLaunchKernelGGL((track_kernel<6, MIXED, EXT>), grid, block, 0, stream, a); break;
+    case 8:  hipLaunchKernelGGL((track_kernel<8, MIXED, EXT>), grid, block, 0, stream, a); break;
+    case 9:  hipLaunchKernelGGL((track_kernel<9, MIXED, EXT>), grid, block, 0, stream, a); break;
+    case 12: hipLaunchKernelGGL((track_kernel<12, MIXED, EXT>), grid, block, 0, stream, a); break;
+    default: hipLaunchKernelGGL((track_kernel<16, MIXED, EXT>), grid, block, 0, stream, a); break;
   }
   return hipGetLastError();
 }
 
-template <bool EXT>
-hipError_t launch_orbit(const TrackArgs& a, int nt, hipStream_t stream) {
+hipError_t launch_orbit(const TrackArgs& a, int nt, bool ext, hipStream_t stream) {
   const dim3 grid((unsigned)((a.feat_n + kBlock - 1) / kBlock)), block(kBlock);
-  switch (nt) {
-    case 5:  hipLaunchKernelGGL((orbit_kernel<5, EXT>), grid, block, 0, stream, a); break;
-    case 6:  hipLaunchKernelGGL((orbit_kernel<6, EXT>), grid, block, 0, stream, a); break;
-    case 8:  hipLaunchKernelGGL((orbit_kernel<8, EXT>), grid, block, 0, stream, a); break;
-    case 12: hipLaunchKernelGGL((orbit_kernel<12, EXT>), grid, block, 0, stream, a); break;
-    default: hipLaunchKernelGGL((orbit_kernel<16, EXT>), grid, block, 0, stream, a); break;
+  if (!ext) {           // no rotation is formed
+    hipLaunchKernelGGL((orbit_kernel<5, false>), grid, block, 0, stream, a);
+    return hipGetLastError();
+  }
+  switch (nt) {         // (the solenoid's own rotation)
+    case 5:  hipLaunchKernelGGL((orbit_kernel<5, true>), grid, block, 0, stream, a); break;
+    case 6:  hipLaunchKernelGGL((orbit_kernel<6, true>), grid, block, 0, stream, a); break;
+    case 8:  hipLaunchKernelGGL((orbit_kernel<8, true>), grid, block, 0, stream, a); break;
+    case 9:  hipLaunchKernelGGL((orbit_kernel<9, true>), grid, block, 0, stream, a); break;
+    case 12: hipLaunchKernelGGL((orbit_kernel<12, true>), grid, block, 0, stream, a); break;
+    default: hipLaunchKernelGGL((orbit_kernel<16, true>), grid, block, 0, stream, a); break;
   }
   return hipGetLastError();
-}
-
-// Surrogate turns: the particles on the network (the first a.feat_n lanes of
-// the lane order) on the orbit-only kernel, then the ones that fall back on
-// the full kernel, whose workgroups below a.feat_n leave at once.
-template <bool EXT>
-hipError_t launch_surrogate(const TrackArgs& a, int nt, hipStream_t stream) {
-  if (a.feat_n > 0) {
-    const hipError_t e = launch_orbit<EXT>(a, nt, stream);
-    if (e != hipSuccess) return e;
-  }
-  if (a.feat_n >= a.n) return hipSuccess;
-  return launch_nt<false, true, EXT>(a, nt, stream);
 }
 
 hipError_t launch_track(const TrackArgs& a, int nt, bool mixed, bool ext, hipStream_t stream) {
   // the extended methods run in double precision only
-  if (ext) return a.fallback ? launch_surrogate<true>(a, nt, stream)
-                             : launch_nt<false, false, true>(a, nt, stream);
-  if (a.fallback) return launch_surrogate<false>(a, nt, stream);
-  return mixed ? launch_nt<true, false, false>(a, nt, stream)
-               : launch_nt<false, false, false>(a, nt, stream);
+  if (ext) return launch_nt<false, true>(a, nt, stream);
+  return mixed ? launch_nt<true, false>(a, nt, stream) : launch_nt<false, false>(a, nt, stream);
 }
 
 hipError_t launch_reduce_polarization(const double* partials, int n_blocks, int n_reports,

@@ -10,14 +10,15 @@ namespace st {
 int track_block_size();
 
 // nt: number of series terms of the double-precision quaternion half-angle
-// series (5, 6, 8, 12, 16); mixed: the kernel with single-precision spin
+// series (5, 6, 8, 9, 12, 16); mixed: the kernel with single-precision spin
 // arithmetic in the elements flagged for it.
 // ext: the lattice uses drift-kick (TEAPOT) bends or piece-wise constant
 // spin placements (run in double precision).
 hipError_t launch_track(const TrackArgs& a, int nt, bool mixed, bool ext, hipStream_t stream);
 
-// a.fallback non-null selects surrogate tracking: an orbit-only launch for the
-// a.feat_n particles on the network, then the full kernel for the others.
+// Surrogate tracking: the orbit only, for the a.feat_n particles on the
+// network (the first lanes of the lane order).
+hipError_t launch_orbit(const TrackArgs& a, int nt, bool ext, hipStream_t stream);
 
 hipError_t launch_surrogate_spin(double* spin, const int32_t* alive, const int32_t* fallback,
                                  const float* qnn, int64_t n, hipStream_t s);
