@@ -324,12 +324,13 @@ typedef struct {
  * d_x [n][n_in] (device floats) plus a constant: the affine map ref + lin x
  * that minimises the summed squared residual of every component, from the
  * normal equations summed on the device in double (fixed order) and solved
- * on the host by Cholesky, with a ridge of 1e-12 of the mean diagonal on the
+ * there by Cholesky, with a ridge of 1e-12 of the mean diagonal on the
  * input columns.  Then it sets the network's whole frame: ref and lin as
  * fitted, scale = max(RMS residual, floor) per component, so that the network
  * learns only what the affine map leaves.  *out (host, may be NULL) receives
- * the fit.  Synchronous on `stream` (returns after the fit); allocates and
- * frees about 0.5 MB of device memory.  ST_EINVAL for NULL inputs, n <
+ * the fit.  Synchronous on `stream` (returns after the fit); the first
+ * call on a network allocates 0.6 MB of device memory and a page of pinned host
+ * memory, kept until the network is destroyed.  ST_EINVAL for NULL inputs, n <
  * n_in + 1, floor <= 0, or inputs whose normal equations are not positive
  * definite; ST_ENOMEM, ST_EDEVICE on device failures. */
 st_status st_mlp_fit_frame(st_mlp* m, const float* d_x, const float* d_t, int64_t n, double floor,

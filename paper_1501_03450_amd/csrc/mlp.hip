@@ -31,6 +31,8 @@
 #include <hip/hip_runtime.h>
 #include <hip/hip_bf16.h>
 
+#include <algorithm>
+
 #include "mlp_kernels.h"
 
 namespace st {
@@ -833,79 +835,224 @@ __global__ void __launch_bounds__(256) targets_kernel(const double* q, int64_t n
   t[j * 4 + 3] = (float)(s * z);
 }
 
-// Normal equations of the frame fit, one block per contiguous range of
-// samples: rows [1, x, t] of 256 samples at a time in LDS, thread v owns one
-// entry of [1,x][1,x]ᵀ (v < D*D) or of [1,x] tᵀ and sums it over the range in
-// sample order.
-__global__ void __launch_bounds__(256) fit_normal_kernel(const float* x, const float* t, int64_t n,
-                                                         int n_in, double* partials) {
-  constexpr int C = kMlpMaxIn + 1 + 4;
-  __shared__ double rows[256][C];
-  const int D = n_in + 1, V = D * D + 4 * D, tid = threadIdx.x;
-  const int64_t per = (n + kFitBlocks - 1) / kFitBlocks;
-  const int64_t lo = (int64_t)blockIdx.x * per, hi = min(n, lo + per);
-  const int p = tid < D * D ? tid / D : (tid - D * D) / 4;
-  const int q = tid < D * D ? tid % D : D + (tid - D * D) % 4;
-  double acc = 0.0;
-  for (int64_t c0 = lo; c0 < hi; c0 += 256) {
-    const int64_t j = c0 + tid;
-    const bool in = j < hi;
-    rows[tid][0] = in ? 1.0 : 0.0;
-    for (int k = 0; k < n_in; ++k) rows[tid][1 + k] = in ? (double)x[j * n_in + k] : 0.0;
-    for (int c = 0; c < 4; ++c) rows[tid][D + c] = in ? (double)t[j * 4 + c] : 0.0;
-    __syncthreads();
-    if (tid < V) {
-      const int m = (int)min((int64_t)256, hi - c0);
-      for (int i = 0; i < m; ++i) acc = fma(rows[i][p], rows[i][q], acc);
+// Frame fit.  Four launches with one wait at their end: moments, solve,
+// residuals, finish; what bounds it is the two passes over x and t (42 MB for
+// 2^20 samples of six inputs: 15.6 and 12.3 us) and the launches themselves (12
+// us in the solve, one wave's chain).  2^20 samples: 142 -> 64 us a call against
+// two launches with an allocation, two copies and the solve on the host between
+// them.
+//
+// Moments.  With Z = [1, x, t] (1 + n_in + 4 <= 13 columns, zero-padded to 16)
+// the normal equations are parts of ZᵀZ, a sum over samples of outer products:
+// v_mfma_f64_16x16x4 takes four samples per instruction, and since A = Zᵀ and
+// B = Z the same register is both operands (lane l holds column l & 15 of
+// sample l >> 4).  A wave sums a contiguous range of samples in order over four
+// accumulators, with the next 32 samples' loads in flight, a block its sixteen
+// waves in order.
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+constexpr int kFitWaves = 16;
+
+__global__ void __launch_bounds__(64 * kFitWaves) fit_moments_kernel(const float* x, const float* t,
+                                                                     int64_t n, int n_in,
+                                                                     double* part) {
+  __shared__ double sum[kFitWaves][256];
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int col = lane & 15, k = lane >> 4, C = 1 + n_in + 4;
+  const int64_t waves = (int64_t)gridDim.x * kFitWaves, w = (int64_t)blockIdx.x * kFitWaves + wv;
+  const int64_t per = ((n + waves - 1) / waves + 3) / 4 * 4;
+  const int64_t lo = min(n, w * per), hi = min(n, lo + per);
+  const bool from_x = col >= 1 && col <= n_in, from_t = col > n_in && col < C;
+  const float* src = from_x ? x + (col - 1) : from_t ? t + (col - 1 - n_in) : x;
+  const int64_t stride = from_t ? 4 : n_in;
+  const float scale = from_x || from_t ? 1.0f : 0.0f, shift = col == 0 ? 1.0f : 0.0f;
+  f64x4 acc[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) acc[u] = f64x4{0.0, 0.0, 0.0, 0.0};
+  const int64_t full = lo + (hi - lo) / 32 * 32;
+  const float* at = src + (lo + k) * stride;
+  float v[8];
+  if (lo < full)
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = at[4 * u * stride];
+  for (int64_t s = lo; s < full; s += 32) {
+    if (s + 32 < full) at += 32 * stride;     // (the last round loads its own samples again)
+    float next[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) next[u] = at[4 * u * stride];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const double z = (double)fmaf(v[u], scale, shift);
+      acc[u & 3] = __builtin_amdgcn_mfma_f64_16x16x4f64(z, z, acc[u & 3], 0, 0, 0);
+      v[u] = next[u];
     }
-    __syncthreads();
   }
-  if (tid < V) partials[(int64_t)blockIdx.x * V + tid] = acc;
+  for (int64_t s = full; s < hi; s += 4) {
+    const double z = s + k < hi ? (double)fmaf(src[(s + k) * stride], scale, shift) : 0.0;
+    acc[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(z, z, acc[0], 0, 0, 0);
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i)      // entry (4 i + lane / 16, lane % 16)
+    sum[wv][(4 * i + k) * 16 + col] = (acc[0][i] + acc[1][i]) + (acc[2][i] + acc[3][i]);
+  __syncthreads();
+  if (threadIdx.x < 256) {
+    double v = 0.0;
+    for (int q = 0; q < kFitWaves; ++q) v += sum[q][threadIdx.x];
+    part[(int64_t)blockIdx.x * 256 + threadIdx.x] = v;
+  }
+}
+
+// The blocks' partials summed in block order (seven groups of rows, then the
+// groups), and the least-squares coefficients: elimination of the symmetric
+// equations [G | R] without pivoting (its pivots are the squared diagonal of the
+// Cholesky factor, all positive where the equations are positive definite), one
+// row per lane in registers, with a ridge of 1e-12 of the mean diagonal on the
+// input columns, which keeps a constant-zero input (a band of one energy)
+// solvable with coefficient 0.
+__global__ void __launch_bounds__(1024) fit_solve_kernel(const double* part, int nb, int n_in,
+                                                         FitResult* out) {
+  constexpr int M = kMlpMaxIn + 1, kGroups = 1024 / (16 * M);
+  __shared__ double red[kGroups][16 * M];
+  __shared__ double G[M][16];
+  const int tid = threadIdx.x, D = n_in + 1, e = tid % (16 * M), g = tid / (16 * M);
+  const int per = (nb + kGroups - 1) / kGroups, b1 = min(nb, (g + 1) * per);
+  if (g < kGroups) {
+    double s = 0.0;
+    if (e < 16 * D)
+#pragma unroll 20
+      for (int b = g * per; b < b1; ++b) s += part[(int64_t)b * 256 + e];
+    red[g][e] = s;
+  }
+  __syncthreads();
+  if (tid < 16 * M) {
+    double v = red[0][tid];
+    for (int q = 1; q < kGroups; ++q) v += red[q][tid];
+    G[tid >> 4][tid & 15] = v;
+  }
+  __syncthreads();
+  if (tid >= 64) return;
+  // lane p: row p, the right-hand sides in the last four columns; rows past D
+  // are those of the identity
+  const int p = min(tid, M - 1);
+  double row[M + 4], trace = 0.0;
+  for (int k = 0; k < D; ++k) trace += G[k][k];
+#pragma unroll
+  for (int k = 0; k < M; ++k) row[k] = p < D && k < D ? G[p][k] : p == k ? 1.0 : 0.0;
+#pragma unroll
+  for (int c = 0; c < 4; ++c) row[M + c] = p < D ? G[p][D + c] : 0.0;
+#pragma unroll
+  for (int k = 1; k < M; ++k)
+    if (p == k && k < D) row[k] += 1e-12 * trace / D;
+  bool bad = false;
+#pragma unroll
+  for (int k = 0; k < M; ++k) {
+    const double pivot = __shfl(row[k], k, 64);
+    bad |= !(pivot > 0.0);
+    const double f = tid == k ? 0.0 : row[k] / pivot;
+#pragma unroll
+    for (int q = k; q < M + 4; ++q) row[q] = fma(-f, __shfl(row[q], k, 64), row[q]);
+  }
+#pragma unroll
+  for (int k = 0; k < M; ++k)
+    if (tid == k && k < D)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) out->coef[c][k] = row[M + c] / row[k];
+  if (tid == 0) out->bad = bad;
 }
 
 // Squared residuals of each component and their largest magnitude over one
-// block's range; tree reduction in a fixed order.
+// block's range of samples; sums in a fixed order (a thread's samples, the
+// wave's lanes by halving, the waves).
+template <int NIN>
 __global__ void __launch_bounds__(256) fit_residual_kernel(const float* x, const float* t, int64_t n,
-                                                           int n_in, FitCoef cf, double* partials) {
-  __shared__ double red[256][8];
-  const int tid = threadIdx.x;
-  const int64_t per = (n + kFitBlocks - 1) / kFitBlocks;
-  const int64_t lo = (int64_t)blockIdx.x * per, hi = min(n, lo + per);
-  double ss[4] = {0.0, 0.0, 0.0, 0.0}, mx[4] = {0.0, 0.0, 0.0, 0.0};
-  for (int64_t j = lo + tid; j < hi; j += 256) {
+                                                           const FitResult* fit, double* part) {
+  __shared__ double red[4][8];
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  double cf[4][NIN + 1];
+#pragma unroll
+  for (int c = 0; c < 4; ++c)
+#pragma unroll
+    for (int k = 0; k <= NIN; ++k) cf[c][k] = fit->coef[c][k];
+  double v[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+  for (int64_t j = (int64_t)blockIdx.x * 256 + tid; j < n; j += (int64_t)gridDim.x * 256) {
+    float xv[NIN], tv[4];
+#pragma unroll
+    for (int k = 0; k < NIN; ++k) xv[k] = x[j * NIN + k];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) tv[c] = t[j * 4 + c];
+#pragma unroll
     for (int c = 0; c < 4; ++c) {
-      double f = cf.c[c][0];
-      for (int k = 0; k < n_in; ++k) f = fma(cf.c[c][1 + k], (double)x[j * n_in + k], f);
-      const double r = (double)t[j * 4 + c] - f;
-      ss[c] = fma(r, r, ss[c]);
-      mx[c] = fmax(mx[c], fabs(r));
+      double f = cf[c][0];
+#pragma unroll
+      for (int k = 0; k < NIN; ++k) f = fma(cf[c][1 + k], (double)xv[k], f);
+      const double r = (double)tv[c] - f;
+      v[c] = fma(r, r, v[c]);
+      v[4 + c] = fmax(v[4 + c], fabs(r));
     }
   }
-  for (int c = 0; c < 4; ++c) { red[tid][c] = ss[c]; red[tid][4 + c] = mx[c]; }
+  for (int w = 32; w > 0; w >>= 1)
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+      const double o = __shfl_xor(v[c], w, 64);
+      v[c] = c < 4 ? v[c] + o : fmax(v[c], o);
+    }
+  if (lane == 0)
+    for (int c = 0; c < 8; ++c) red[wv][c] = v[c];
   __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if (tid < w)
-      for (int c = 0; c < 4; ++c) {
-        red[tid][c] += red[tid + w][c];
-        red[tid][4 + c] = fmax(red[tid][4 + c], red[tid + w][4 + c]);
-      }
-    __syncthreads();
+  if (tid < 8) {
+    double r = red[0][tid];
+    for (int q = 1; q < 4; ++q) r = tid < 4 ? r + red[q][tid] : fmax(r, red[q][tid]);
+    part[(int64_t)blockIdx.x * 8 + tid] = r;
   }
-  if (tid < 8) partials[(int64_t)blockIdx.x * 8 + tid] = red[0][tid];
+}
+
+// The residuals' partials in block order, and the whole result into host memory.
+__global__ void __launch_bounds__(256) fit_finish_kernel(const double* part, int nb,
+                                                         const FitResult* fit, FitResult* host) {
+  __shared__ double red[32][8];
+  const int tid = threadIdx.x, c = tid & 7, g = tid >> 3;
+  const int per = (nb + 31) / 32, b1 = min(nb, (g + 1) * per);
+  double r = 0.0;
+#pragma unroll 8
+  for (int b = g * per; b < b1; ++b) {
+    const double o = part[(int64_t)b * 8 + c];
+    r = c < 4 ? r + o : fmax(r, o);
+  }
+  red[g][c] = r;
+  __syncthreads();
+  if (tid < 8) {
+    r = red[0][tid];
+    for (int q = 1; q < 32; ++q) r = tid < 4 ? r + red[q][tid] : fmax(r, red[q][tid]);
+    if (tid < 4) host->ss[tid] = r;
+    else         host->mx[tid - 4] = r;
+  }
+  if (tid >= 64 && tid < 64 + 4 * (kMlpMaxIn + 1))
+    (&host->coef[0][0])[tid - 64] = (&fit->coef[0][0])[tid - 64];
+  if (tid == 128) host->bad = fit->bad;
 }
 
 }  // namespace
 
-hipError_t launch_fit_normal(const float* x, const float* t, int64_t n, int n_in, double* partials,
-                             hipStream_t s) {
-  hipLaunchKernelGGL(fit_normal_kernel, dim3(kFitBlocks), dim3(256), 0, s, x, t, n, n_in, partials);
-  return hipGetLastError();
-}
-
-hipError_t launch_fit_residual(const float* x, const float* t, int64_t n, int n_in,
-                               const FitCoef& coef, double* partials, hipStream_t s) {
-  hipLaunchKernelGGL(fit_residual_kernel, dim3(kFitBlocks), dim3(256), 0, s, x, t, n, n_in, coef,
-                     partials);
+hipError_t launch_fit(const float* x, const float* t, int64_t n, int n_in, FitWork* work,
+                      FitResult* host, hipStream_t s) {
+  // enough samples per wave that the blocks' own sums stay small beside them
+  const int nb = (int)std::min<int64_t>(kFitBlocks, (n + 32 * kFitWaves - 1) / (32 * kFitWaves));
+  const int rb = (int)std::min<int64_t>(kFitResidualBlocks, (n + 255) / 256);
+  hipLaunchKernelGGL(fit_moments_kernel, dim3(nb), dim3(64 * kFitWaves), 0, s, x, t, n, n_in,
+                     work->moments);
+  hipLaunchKernelGGL(fit_solve_kernel, dim3(1), dim3(1024), 0, s, work->moments, nb, n_in,
+                     &work->result);
+  switch (n_in) {
+#define ST_FIT_RESIDUAL(N)                                                                        \
+  case N:                                                                                         \
+    hipLaunchKernelGGL(fit_residual_kernel<N>, dim3(rb), dim3(256), 0, s, x, t, n, &work->result, \
+                       work->residuals);                                                          \
+    break;
+    ST_FIT_RESIDUAL(1) ST_FIT_RESIDUAL(2) ST_FIT_RESIDUAL(3) ST_FIT_RESIDUAL(4)
+    ST_FIT_RESIDUAL(5) ST_FIT_RESIDUAL(6) ST_FIT_RESIDUAL(7) ST_FIT_RESIDUAL(8)
+#undef ST_FIT_RESIDUAL
+  }
+  hipLaunchKernelGGL(fit_finish_kernel, dim3(1), dim3(256), 0, s, work->residuals, rb,
+                     &work->result, host);
   return hipGetLastError();
 }
 

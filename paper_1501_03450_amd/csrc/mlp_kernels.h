@@ -128,19 +128,22 @@ struct AdamPending {
   float* loss_out;
 };
 // Least-squares fit of targets t [n][4] on the inputs augmented with a
-// constant, [1, x] (D = n_in + 1 columns), in double precision.  Pass 1:
-// per-block partial sums of the normal equations, D*D entries of [1,x][1,x]ᵀ
-// then D*4 of [1,x] tᵀ (row-major), kFitBlocks blocks.  Pass 2: per-block
-// sums of squared residuals of each component and their largest magnitude,
-// for coefficients coef[4][D].
-constexpr int kFitBlocks = 512;
-struct FitCoef {
-  double c[4][kMlpMaxIn + 1];
+// constant, [1, x] (D = n_in + 1 columns), in double precision: coefficients
+// coef[c][D], sums of squared residuals and their largest magnitudes, queued as
+// four launches; `host` (pinned memory) holds the result once they are done.
+constexpr int kFitBlocks = 256, kFitResidualBlocks = 1024;
+struct FitResult {
+  double coef[4][kMlpMaxIn + 1];
+  double ss[4], mx[4];
+  int32_t bad;            // the normal equations are not positive definite
 };
-hipError_t launch_fit_normal(const float* x, const float* t, int64_t n, int n_in, double* partials,
-                             hipStream_t s);
-hipError_t launch_fit_residual(const float* x, const float* t, int64_t n, int n_in,
-                               const FitCoef& coef, double* partials, hipStream_t s);
+struct FitWork {          // device scratch
+  double moments[kFitBlocks * 256];
+  double residuals[kFitResidualBlocks * 8];
+  FitResult result;
+};
+hipError_t launch_fit(const float* x, const float* t, int64_t n, int n_in, FitWork* work,
+                      FitResult* host, hipStream_t s);
 hipError_t launch_adam(const MlpArgs& a, float lr, float c1, float c2, hipStream_t s,
                        const AdamPending* pending = nullptr);
 hipError_t launch_refresh_bf16(const MlpArgs& a, hipStream_t s);
