@@ -417,11 +417,10 @@ mlp_forward_kernel(const MlpArgs a) {
         if (lane < 16)
           a.gpart_W4[((size_t)blk * 4 + i) * W + wv * 64 + t * 16 + r] = (g[t][i] + mid) + lo;
       }
-    if (tid < 4) {
-      float sb = 0.0f;
-      for (int m = 0; m < rows; ++m) sb += ys[m][tid];
-      a.gpart_b4[(size_t)blk * 4 + tid] = sb;
-    }
+    // wave wv sums column wv over its 64 samples (zero past the batch)
+    float sb = ys[lane][wv];
+    for (int off = 32; off > 0; off >>= 1) sb += __shfl_xor(sb, off, 64);
+    if (lane == 0) a.gpart_b4[(size_t)blk * 4 + wv] = sb;
   }
   __syncthreads();   // h3 in bufA read by every wave before dz3 replaces it
 

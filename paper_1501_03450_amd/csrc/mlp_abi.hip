@@ -41,7 +41,13 @@ struct st_mlp {
 
 namespace {
 
+// Split-K chunks of the weight gradients: at least 128 samples each, at most 64
+// (a chunk writes two 256 KB partials that the reduction reads back: a batch of
+// 1000 with 64 chunks moved 67 MB, 8 chunks move 8 MB).
 constexpr int kSplits = 64;
+int splits_of(int64_t ld) {
+  return (int)std::min<int64_t>(kSplits, std::max<int64_t>(4, (ld / 128 + 3) / 4 * 4));
+}
 
 struct DeviceGuard {
   int old = -1;
@@ -172,8 +178,9 @@ st_status compute_gradient(st_mlp* m, const float* x, const float* t, int64_t ba
   a.dzT2 = m->dzT[0]; a.dzT3 = m->dzT[1];
   a.gpart_W1 = m->gW1; a.gpart_b1 = m->gb1; a.gpart_b2 = m->gb2; a.gpart_b3 = m->gb3;
   a.gpart_W4 = m->gW4; a.gpart_b4 = m->gb4; a.gpart_W2 = m->gW2; a.gpart_W3 = m->gW3;
-  a.n_splits = kSplits;
-  a.split_chunk = ((ld + kSplits - 1) / kSplits + 31) / 32 * 32;
+  const int splits = splits_of(ld);
+  a.n_splits = splits;
+  a.split_chunk = ((ld + splits - 1) / splits + 31) / 32 * 32;
   const int nb = (int)(ld / tile);
   const int64_t W = st::kMlpWidth;
   hipError_t e;
@@ -183,8 +190,8 @@ st_status compute_gradient(st_mlp* m, const float* x, const float* t, int64_t ba
   // every tensor's partials (and the loss) reduced together, one launch per pass
   st::SumSegment red[] = {
       {m->gW1, W * m->n_in, nb, m->grad + o.W1}, {m->gb1, W, nb, m->grad + o.b1},
-      {m->gW2, W * W, kSplits, m->grad + o.W2},  {m->gb2, W, nb, m->grad + o.b2},
-      {m->gW3, W * W, kSplits, m->grad + o.W3},  {m->gb3, W, nb, m->grad + o.b3},
+      {m->gW2, W * W, splits, m->grad + o.W2},  {m->gb2, W, nb, m->grad + o.b2},
+      {m->gW3, W * W, splits, m->grad + o.W3},  {m->gb3, W, nb, m->grad + o.b3},
       {m->gW4, 4 * W, nb, m->grad + o.W4},       {m->gb4, 4, nb, m->grad + o.b4},
       {m->loss_part, 1, nb, d_loss}};
   const int nseg = d_loss ? 9 : 8;
