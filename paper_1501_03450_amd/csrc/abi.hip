@@ -462,7 +462,7 @@ st::TrackArgs track_args(const st_ctx* c) {
   a.tab = c->d_tab;
   a.seq = c->d_seq;
   a.n_records = c->n_records;
-  a.n_blocks = (int32_t)((c->n + st::track_block_size() - 1) / st::track_block_size());
+  a.n_lanes = c->n;
   a.beta0 = c->beta0;
   a.inv_beta0 = 1.0 / c->beta0;
   a.gamma0 = c->beam.gamma0;
@@ -493,22 +493,41 @@ st_status ensure_polarization(st_ctx* c, int64_t n_rep, int64_t nb) {
   return ST_OK;
 }
 
+// Whether `lanes` lanes run in teams of four waves per 64 (bit for bit the same
+// orbits and spins).
+st::TrackPlan track_plan(const st_ctx* c, int64_t lanes, bool mixed) {
+  return {c->nt, mixed, c->ext, !mixed && !c->ext && lanes <= st::kTeamLanes};
+}
+
+// The plan of a whole-bunch call with n_rep reports and its polarization rows
+// per report.  A call whose rows per 64 particles would not fit the fixed
+// scratch array runs in blocks, whoever holds the rows, so that st_track and
+// st_track_noalloc sum in the same order.
+st::TrackPlan bunch_plan(const st_ctx* c, int64_t n_rep, int64_t* rows) {
+  st::TrackPlan p = track_plan(c, c->n, c->beam.precision != ST_FP64);
+  auto rows_of = [&](int64_t per) { return (c->n + per - 1) / per; };
+  if (p.team && (uint64_t)n_rep * (uint64_t)rows_of(st::team_size()) * 4 > kScratchDoubles) p.team = false;
+  *rows = rows_of(p.team ? st::team_size() : st::track_block_size());
+  return p;
+}
+
 // Queue one tracking launch and, with reports, the second pass of the
 // polarization reduction: partials holds reports x blocks x 4 doubles (every
 // slot is written by the tracking kernel before the reduction reads it), pol
 // receives 4 doubles per report.
 st_status launch_tracking(st_ctx* c, int64_t turns, double* partials, double* pol,
                           hipStream_t s) {
-  const int64_t nb = (c->n + st::track_block_size() - 1) / st::track_block_size();
   const int rep_every = c->beam.report_every;
   const int64_t n_rep = rep_every > 0 ? turns / rep_every : 0;
+  int64_t nb;
+  const st::TrackPlan plan = bunch_plan(c, n_rep, &nb);
   st::TrackArgs a = track_args(c);
   a.qout = c->qout;
   a.turns = (int32_t)turns;
   a.report_every = rep_every;
   a.partials = partials;
   hipError_t e;
-  if ((e = st::launch_track(a, c->nt, c->beam.precision != ST_FP64, c->ext, s)) != hipSuccess)
+  if ((e = st::launch_track(a, plan, s)) != hipSuccess)
     return hip_fail(c, e, "launch track");
   if (n_rep > 0 &&
       (e = st::launch_reduce_polarization(partials, (int)nb, (int)n_rep, pol, s)) != hipSuccess)
@@ -706,9 +725,10 @@ st_status st_track(st_ctx* c, int64_t turns, void* stream) {
   c->n_reports = 0;
   if (turns == 0 || c->n == 0) return ST_OK;
   DeviceGuard g(c->device);
-  const int64_t nb = (c->n + st::track_block_size() - 1) / st::track_block_size();
   const int rep_every = c->beam.report_every;
   const int64_t n_rep = rep_every > 0 ? turns / rep_every : 0;
+  int64_t nb;
+  (void)bunch_plan(c, n_rep, &nb);
   st_status pst = ensure_polarization(c, n_rep, nb);
   if (pst != ST_OK) return pst;
   pst = launch_tracking(c, turns, c->d_partials, c->d_pol, (hipStream_t)stream);
@@ -726,9 +746,10 @@ st_status st_track_noalloc(st_ctx* c, int64_t turns, double* d_pol, int64_t capa
   if (!c->have_particles) return fail(c, ST_ESTATE, "no particles bound");
   if (turns < 0 || turns > std::numeric_limits<int32_t>::max())
     return fail(c, ST_EINVAL, "turns must be in 0..2^31-1");
-  const int64_t nb = (c->n + st::track_block_size() - 1) / st::track_block_size();
   const int rep_every = c->beam.report_every;
   const int64_t n_rep = (rep_every > 0 && c->n > 0) ? turns / rep_every : 0;
+  int64_t nb;
+  (void)bunch_plan(c, n_rep, &nb);
   if (n_rep > 0 && (uint64_t)n_rep * (uint64_t)nb * 4 > kScratchDoubles)
     return fail(c, ST_EINVAL,
                 "polarization scratch of " + std::to_string(n_rep) + " reports x " +
@@ -906,12 +927,13 @@ extern "C" st_status st_track_surrogate(st_ctx* c, st_mlp* m, int64_t turns, int
       a.feat_n_in = st_mlp_inputs_of(m);
       for (int i = 0; i < 6; ++i) { a.feat_center[i] = center[i]; a.feat_inv_scale[i] = inv_scale[i]; }
       a.feat_extra = extra;
+      a.n_lanes = n_net;
       if (n_net > 0 && (e = st::launch_orbit(a, c->nt, c->ext, s)) != hipSuccess)
         return hip_fail(c, e, "surrogate orbits");
       if (n_net < n) {      // the particles that fall back, and the lost ones
         a.lane0 = n_net;
-        a.n_blocks = (int32_t)((n - n_net + bs - 1) / bs);
-        if ((e = st::launch_track(a, c->nt, false, c->ext, s)) != hipSuccess)
+        a.n_lanes = n - n_net;
+        if ((e = st::launch_track(a, track_plan(c, a.n_lanes, false), s)) != hipSuccess)
           return hip_fail(c, e, "surrogate turns");
       }
       if (n_net > 0) {
@@ -930,7 +952,8 @@ extern "C" st_status st_track_surrogate(st_ctx* c, st_mlp* m, int64_t turns, int
     st::TrackArgs a = track_args(c);
     a.turns = 1;
     a.qout = c->d_q64;
-    if ((e = st::launch_track(a, c->nt, false, c->ext, s)) != hipSuccess) return hip_fail(c, e, "audit turn");
+    if ((e = st::launch_track(a, track_plan(c, n, false), s)) != hipSuccess)
+      return hip_fail(c, e, "audit turn");
     if ((e = st::launch_audit(c->alive, d_fallback, c->d_failed, c->d_qnn, c->d_q64, n, threshold,
                               (int32_t)t, s)) != hipSuccess)
       return hip_fail(c, e, "audit");
@@ -943,18 +966,18 @@ extern "C" st_status st_track_surrogate(st_ctx* c, st_mlp* m, int64_t turns, int
     if ((e = st::launch_partition(1, c->d_failed, c->alive, d_fallback, n, c->d_pcount,
                                   c->d_poff, c->d_rperm, s)) != hipSuccess)
       return hip_fail(c, e, "replay order");
-    // the replay launch covers only the blocks of the failed particles'
-    // lanes (the lanes past them in the last block are not live in the replay)
+    // the replay launch covers only the failed particles' lanes
     if ((e = count_first()) != hipSuccess) return hip_fail(c, e, "replay count");
     if (n_first > 0) {
       st::TrackArgs r = track_args(c);
       r.alive = c->d_ralive;
       r.perm = c->d_rperm;
-      r.n_blocks = (int32_t)((n_first + st::track_block_size() - 1) / st::track_block_size());
+      r.n_lanes = n_first;
       r.turns = (int)(t - last_audit);
       r.report_every = 0;
       r.partials = nullptr;
-      if ((e = st::launch_track(r, c->nt, false, c->ext, s)) != hipSuccess) return hip_fail(c, e, "replay");
+      if ((e = st::launch_track(r, track_plan(c, n_first, false), s)) != hipSuccess)
+        return hip_fail(c, e, "replay");
     }
     if ((e = st::launch_replay_finish(c->d_failed, c->d_ralive, c->alive, n, s)) != hipSuccess)
       return hip_fail(c, e, "replay status");

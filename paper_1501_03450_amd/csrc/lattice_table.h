@@ -179,11 +179,11 @@ struct TrackArgs {
   int32_t n_records;
   int32_t turns;
   int32_t report_every;
-  int32_t n_blocks;
+  int32_t n_blocks;   // set by the launch
   double* partials;   // [n_reports][n_blocks][4]
   double beta0, inv_beta0, gamma0, inv_gamma0_sq, G, aperture;
   double ymax;        // largest (θ/2)² the quaternion polynomial covers
-  int64_t lane0;      // first lane of the launch in the lane order
+  int64_t lane0, n_lanes;  // lanes of the launch in the lane order
   // optional lane order: lane g works on particle perm[g] (a permutation of
   // 0..n-1), so that particles taking the same path share waves
   const int32_t* perm;

@@ -8,13 +8,29 @@
 namespace st {
 
 int track_block_size();
+int team_size();
 
-// nt: number of series terms of the double-precision quaternion half-angle
-// series (5, 6, 8, 9, 12, 16); mixed: the kernel with single-precision spin
-// arithmetic in the elements flagged for it.
-// ext: the lattice uses drift-kick (TEAPOT) bends or piece-wise constant
-// spin placements (run in double precision).
-hipError_t launch_track(const TrackArgs& a, int nt, bool mixed, bool ext, hipStream_t stream);
+// How a launch runs.  nt: number of series terms of the double-precision
+// quaternion half-angle series (5, 6, 8, 9, 12, 16); mixed: the kernel with
+// single-precision spin arithmetic in the elements flagged for it; ext: the
+// lattice uses drift-kick (TEAPOT) bends, piece-wise constant spin placements,
+// solenoids or rectangular bends (run in double precision); team: four waves
+// per 64 particles (neither mixed nor ext), the same results bit for bit.
+struct TrackPlan {
+  int nt;
+  bool mixed, ext, team;
+};
+// Lanes up to which a team per 64 particles is the faster one: its extra work
+// (the slices are computed twice) fills SIMDs that would idle.  Two teams fit a
+// compute unit, so this is one round of them; past it a second round starts, and
+// the blocks take the same time up to 65536 lanes.  Teams against blocks, us a
+// turn: RHIC-scale ring 848 / 1305 at 16384 lanes and 1065 / 1305 at 32768; the
+// small ring 90 / 121 at 32768.
+constexpr int64_t kTeamLanes = 32768;
+
+// Tracks a.n_lanes lanes from a.lane0 on, in blocks of 256 lanes or teams of 64
+// (the polarization partials have that many rows per report).
+hipError_t launch_track(TrackArgs a, const TrackPlan& plan, hipStream_t stream);
 
 // Surrogate tracking: the orbit only, for the a.feat_n particles on the
 // network (the first lanes of the lane order).
