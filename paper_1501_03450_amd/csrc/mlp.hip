@@ -13,9 +13,10 @@
 // into three bf16 parts whose sum is exact, so those products keep fp32
 // precision too.
 //
-// Kernels (one batch, 64 samples per workgroup of four waves):
-//   forward        inference: all four layers fused, activations kept in LDS
-//   forward<TRAIN> the training step's forward and backward passes of one
+// Kernels (one batch; training: 64 samples per workgroup of four waves):
+//   infer          all four layers fused, W2 and W3 in registers, activations
+//                  kept in LDS
+//   train          the training step's forward and backward passes of one
 //                  tile in one kernel: it stores the two hidden activations
 //                  the weight gradients need and silu'(z2) (bf16,
 //                  feature-major, straight from the accumulators), keeps
@@ -128,10 +129,9 @@ __device__ __forceinline__ __bf16 split3(float v, int part) {
   return (__bf16)(r - (float)mid);
 }
 
-// Hidden-layer epilogue: z = acc + b, h = silu(z) into LDS (bf16, row-major),
-// and when hT is set also to HBM feature-major [256][ld] from the registers
-// (a lane holds four consecutive samples of one feature: one 8-byte store per
-// 16x16 tile).
+// Hidden-layer epilogue: z = acc + b, h = silu(z) into LDS (bf16, row-major)
+// and to HBM feature-major [256][ld] from the registers (a lane holds four
+// consecutive samples of one feature: one 8-byte store per 16x16 tile).
 __device__ __forceinline__ void hidden_epilogue(const f32x4 acc[4][4], const float* bias,
                                                 __bf16* out_lds, int rows, int n_base, int lane,
                                                 __bf16* hT, int64_t ld, int64_t b0) {
@@ -151,7 +151,7 @@ __device__ __forceinline__ void hidden_epilogue(const f32x4 acc[4][4], const flo
         h[i] = (__bf16)(m0 + i < rows ? silu(z) : 0.0f);
         out_lds[(m0 + i) * LDA + n] = h[i];
       }
-      if (hT) *reinterpret_cast<bf16x4*>(hT + (size_t)n * ld + b0 + m0) = h;
+      *reinterpret_cast<bf16x4*>(hT + (size_t)n * ld + b0 + m0) = h;
     }
   }
 }
@@ -241,14 +241,9 @@ __device__ __forceinline__ void store_grad_tile(const f32x4 acc[4][4], __bf16* o
   }
 }
 
-// One activation buffer per workgroup (34 KB of LDS, so four workgroups fit
-// on a CU): each layer's GEMM reads it, a barrier, then the epilogue
-// overwrites it with the layer's output.  Inference is compiled for four
-// waves per SIMD (128 registers), so that four workgroups are resident per
-// CU and the whole batch of 1024 tiles of a 65536-sample batch is on the
-// chip at once.
-//
-// TRAIN: the same tile then runs the backward pass through the layers, with
+// One activation buffer per workgroup: each layer's GEMM reads it, a barrier,
+// then the epilogue overwrites it with the layer's output.  The same tile then
+// runs the backward pass through the layers, with
 // silu'(z3) kept in LDS from the forward epilogue (bf16, in the accumulator
 // layout the backward products use), silu'(z2) read back from HBM and dL/dy
 // in LDS: dz3 = (dL/dy W4) ⊙ silu'(z3), dz2 = (dz3 W3) ⊙ silu'(z2) and
@@ -262,18 +257,17 @@ __device__ __forceinline__ void store_grad_tile(const f32x4 acc[4][4], __bf16* o
 #ifndef ST_MLP_TRAIN_WAVES
 #define ST_MLP_TRAIN_WAVES 2
 #endif
-template <bool TRAIN>
 __global__ void __launch_bounds__(NT)
-__attribute__((amdgpu_waves_per_eu(TRAIN ? ST_MLP_TRAIN_WAVES : 4, TRAIN ? ST_MLP_TRAIN_WAVES : 4)))
-mlp_forward_kernel(const MlpArgs a) {
+__attribute__((amdgpu_waves_per_eu(ST_MLP_TRAIN_WAVES, ST_MLP_TRAIN_WAVES)))
+mlp_train_kernel(const MlpArgs a) {
   __shared__ __align__(16) __bf16 bufA[TM * LDA];
   __shared__ float xs[TM][kMlpMaxIn];
   __shared__ float ys[TM][4];
   __shared__ float red[NT / 64];
-  // training: silu'(z3) of the four waves' tiles (32 KB; inference: unused)
-  __shared__ uint2 ds3s[TRAIN ? (NT / 64) * 16 * 64 : 1];
+  // silu'(z3) of the four waves' tiles (32 KB)
+  __shared__ uint2 ds3s[(NT / 64) * 16 * 64];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  uint2* const ds3 = ds3s + (TRAIN ? wv * 16 * 64 : 0);
+  uint2* const ds3 = ds3s + wv * 16 * 64;
   const int64_t B = a.batch, b0 = (int64_t)blockIdx.x * TM;
   const int rows = (int)min((int64_t)TM, B - b0);
   const int nin = a.n_in;
@@ -294,28 +288,20 @@ mlp_forward_kernel(const MlpArgs a) {
 #pragma unroll
     for (int mt = 0; mt < 4; ++mt) acc[mt][nt] = col[mt];
   }
-  hidden_epilogue(acc, P + a.off.b1, bufA, rows, wv * 64, lane, TRAIN ? a.hT1 : nullptr, a.ld, b0);
+  hidden_epilogue(acc, P + a.off.b1, bufA, rows, wv * 64, lane, a.hT1, a.ld, b0);
   __syncthreads();
 
   // layer 2 (MFMA)
   zero_acc(acc);
   gemm_64x64<2>(bufA, a.W2b, wv * 64, acc, lane);
   __syncthreads();
-  if (TRAIN)
-    hidden_epilogue_dsilu(acc, P + a.off.b2, bufA, rows, wv * 64, lane, a.dsT2, ds3, a.hT2, a.ld,
-                          b0);
-  else
-    hidden_epilogue(acc, P + a.off.b2, bufA, rows, wv * 64, lane, nullptr, 0, 0);
+  hidden_epilogue_dsilu(acc, P + a.off.b2, bufA, rows, wv * 64, lane, a.dsT2, ds3, a.hT2, a.ld, b0);
   __syncthreads();
   // layer 3 (MFMA)
   zero_acc(acc);
   gemm_64x64<2>(bufA, a.W3b, wv * 64, acc, lane);
   __syncthreads();
-  if (TRAIN)
-    hidden_epilogue_dsilu(acc, P + a.off.b3, bufA, rows, wv * 64, lane, nullptr, ds3, nullptr, a.ld,
-                          b0);
-  else
-    hidden_epilogue(acc, P + a.off.b3, bufA, rows, wv * 64, lane, nullptr, 0, 0);
+  hidden_epilogue_dsilu(acc, P + a.off.b3, bufA, rows, wv * 64, lane, nullptr, ds3, nullptr, a.ld, b0);
   __syncthreads();
 
   // layer 4 (bf16 matrix cores, W4 in three parts: operand rows j, 4 + j and
@@ -339,8 +325,7 @@ mlp_forward_kernel(const MlpArgs a) {
   }
   __syncthreads();
 
-  // normalised output; when training, the loss and dL/dy (into ys, zero for
-  // padded samples)
+  // normalised output, the loss and dL/dy (into ys, zero for padded samples)
   float l = 0.0f;
   if (tid < TM) {
     const int m = tid;
@@ -360,10 +345,7 @@ mlp_forward_kernel(const MlpArgs a) {
     const float ny = sqrtf(y0 * y0 + y1 * y1 + y2 * y2 + y3 * y3);
     const float inv = 1.0f / ny;
     const float q[4] = {y0 * inv, y1 * inv, y2 * inv, y3 * inv};
-    if (!TRAIN) {
-      if (m < rows)
-        for (int j = 0; j < 4; ++j) a.q_out[(b0 + m) * 4 + j] = q[j];
-    } else if (m < rows) {
+    if (m < rows) {
       const float* t = a.target + (b0 + m) * 4;
       float dq[4], qd = 0.0f;
       for (int j = 0; j < 4; ++j) {
@@ -377,7 +359,6 @@ mlp_forward_kernel(const MlpArgs a) {
       for (int j = 0; j < 4; ++j) ys[m][j] = 0.0f;
     }
   }
-  if (!TRAIN) return;
   for (int off = 32; off > 0; off >>= 1) l += __shfl_xor(l, off, 64);
   if (lane == 0) red[wv] = l;
   __syncthreads();
@@ -525,6 +506,151 @@ mlp_forward_kernel(const MlpArgs a) {
         if (c < nin) a.gpart_W1[((size_t)blk * W + n) * nin + c] = g[t][i];
         else if (c == nin) a.gpart_b1[(size_t)blk * W + n] = g[t][i];
       }
+  }
+}
+
+// Inference.  One persistent workgroup per compute unit, eight waves; wave wv
+// holds rows 32 wv .. 32 wv + 31 of W2 and W3 in registers (128 of them) for
+// all its tiles, so that the weights cross L2 once per launch instead of once per
+// tile.  Weights are the A operand and activations the B operand: a lane then
+// has four consecutive features of one sample, one 8-byte LDS store.  Layer 3 of
+// a tile runs beside layer 1 of the next, layer 2 of that beside layer 4: two
+// barriers per tile, and work for both the matrix cores and the vector units
+// between them.  What bounds it is the activation's exponential and reciprocal
+// (a quarter of the vector rate): about 150 cycles a sample and CU, of the 205
+// it takes.  The sums run in the order that one wave per 64 columns gives.  2^21
+// samples: 1236 -> 735 us against a workgroup per tile with the weights read
+// from L2 by every tile; 65536: 47 -> 33; 1000: 22.7 -> 13.1.
+constexpr int kInferWaves = 8;
+constexpr int64_t kMlpCus = 256;
+
+template <int TILES>       // samples per tile / 16
+__device__ __forceinline__ void infer_hidden(const bf16x8 (&w)[2][8], const f32x4 (&bias)[2],
+                                             const __bf16* in, __bf16* out, int n_base, int lane) {
+  const int r = lane & 15, g = lane >> 4;
+#pragma unroll
+  for (int st = 0; st < TILES; ++st) {
+    const __bf16* row = in + (st * 16 + r) * LDA + 8 * g;
+    f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      const bf16x8 x = *reinterpret_cast<const bf16x8*>(row + 32 * k);
+#pragma unroll
+      for (int ft = 0; ft < 2; ++ft)
+        acc[ft] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[ft][k], x, acc[ft], 0, 0, 0);
+    }
+#pragma unroll
+    for (int ft = 0; ft < 2; ++ft) {
+      bf16x4 h;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) h[i] = (__bf16)silu(acc[ft][i] + bias[ft][i]);
+      *reinterpret_cast<bf16x4*>(out + (st * 16 + r) * LDA + n_base + 16 * ft + 4 * g) = h;
+    }
+  }
+}
+
+template <int TILES>
+__global__ void __launch_bounds__(64 * kInferWaves) __attribute__((amdgpu_waves_per_eu(2, 2)))
+mlp_infer_kernel(const MlpArgs a) {
+  constexpr int M = 16 * TILES, XS = kMlpMaxIn + 1, NTH = 64 * kInferWaves;
+  __shared__ __align__(16) __bf16 h1[M * LDA], h2[M * LDA], h3[M * LDA], w4[16 * LDA];
+  __shared__ float xs[4][M][XS];
+  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int r = lane & 15, g = lane >> 4, n_base = 32 * wv, nin = a.n_in;
+  const int64_t B = a.batch, tiles = (B + M - 1) / M;
+  const int count = (int)((tiles - blockIdx.x + gridDim.x - 1) / gridDim.x);
+  const float* P = a.params;
+  const int xm = tid / kMlpMaxIn, xk = tid % kMlpMaxIn;
+  auto load_x = [&](int i) {        // this thread's input of the block's i-th tile
+    const int64_t m = ((int64_t)blockIdx.x + (int64_t)i * gridDim.x) * M + xm;
+    return i < count && xm < M && m < B && xk < nin ? a.x[m * nin + xk] : 0.0f;
+  };
+  float x_next = load_x(0);
+  bf16x8 w2[2][8], w3[2][8];
+  f32x4 b1[2], b2[2], b3[2];
+  float w1[2][2];
+#pragma unroll
+  for (int ft = 0; ft < 2; ++ft) {
+    const int n = n_base + 16 * ft;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      b1[ft][i] = P[a.off.b1 + n + 4 * g + i];
+      b2[ft][i] = P[a.off.b2 + n + 4 * g + i];
+      b3[ft][i] = P[a.off.b3 + n + 4 * g + i];
+    }
+#pragma unroll
+    for (int q = 0; q < 2; ++q) w1[ft][q] = 4 * q + g < nin ? P[a.off.W1 + (n + r) * nin + 4 * q + g] : 0.0f;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      w2[ft][k] = *reinterpret_cast<const bf16x8*>(a.W2b + (size_t)(n + r) * W + 32 * k + 8 * g);
+      w3[ft][k] = *reinterpret_cast<const bf16x8*>(a.W3b + (size_t)(n + r) * W + 32 * k + 8 * g);
+    }
+  }
+  {
+    const int row = tid / 32, k = tid % 32 * 8;
+    *reinterpret_cast<bf16x8*>(w4 + row * LDA + k) =
+        *reinterpret_cast<const bf16x8*>(a.W4s + row * W + k);
+  }
+  auto layer1 = [&](int slot) {
+#pragma unroll
+    for (int st = 0; st < TILES; ++st) {
+      const float x0 = xs[slot][st * 16 + r][g], x1 = xs[slot][st * 16 + r][4 + g];
+#pragma unroll
+      for (int ft = 0; ft < 2; ++ft) {
+        f32x4 d = {0.f, 0.f, 0.f, 0.f};
+        d = __builtin_amdgcn_mfma_f32_16x16x4f32(w1[ft][0], x0, d, 0, 0, 0);
+        d = __builtin_amdgcn_mfma_f32_16x16x4f32(w1[ft][1], x1, d, 0, 0, 0);
+        bf16x4 h;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) h[i] = (__bf16)silu(d[i] + b1[ft][i]);
+        *reinterpret_cast<bf16x4*>(h1 + (st * 16 + r) * LDA + n_base + 16 * ft + 4 * g) = h;
+      }
+    }
+  };
+  // wave wv < TILES: 16 samples; lane groups 0, 1 and 2 hold the three parts of
+  // the four outputs, and group 0 finishes
+  auto layer4 = [&](int i) {
+    const __bf16* row = h3 + (wv * 16 + r) * LDA + 8 * g;
+    f32x4 y = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int k = 0; k < 8; ++k)
+      y = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+          *reinterpret_cast<const bf16x8*>(w4 + r * LDA + 32 * k + 8 * g),
+          *reinterpret_cast<const bf16x8*>(row + 32 * k), y, 0, 0, 0);
+    const float* x = xs[i & 3][wv * 16 + r];
+    float u[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const float mid = __shfl(y[j], lane + 16, 64), lo = __shfl(y[j], lane + 32, 64);
+      const float yj = P[a.off.b4 + j] + ((y[j] + mid) + lo);
+      float base = a.out_ref[j];
+#pragma unroll
+      for (int k = 0; k < kMlpMaxIn; ++k) base = fmaf(a.out_lin[j][k], x[k], base);
+      u[j] = fmaf(a.out_scale[j], yj, base);
+    }
+    const float inv = 1.0f / sqrtf(u[0] * u[0] + u[1] * u[1] + u[2] * u[2] + u[3] * u[3]);
+    const int64_t m = ((int64_t)blockIdx.x + (int64_t)i * gridDim.x) * M + wv * 16 + r;
+    if (lane < 16 && m < B)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) a.q_out[m * 4 + j] = u[j] * inv;
+  };
+  if (xm < M) xs[0][xm][xk] = x_next;
+  x_next = load_x(1);
+  __syncthreads();
+  layer1(0);
+  if (xm < M) xs[1][xm][xk] = x_next;
+  __syncthreads();
+  infer_hidden<TILES>(w2, b2, h1, h2, n_base, lane);
+  __syncthreads();
+  for (int i = 0; i < count; ++i) {
+    x_next = load_x(i + 2);
+    infer_hidden<TILES>(w3, b3, h2, h3, n_base, lane);
+    if (i + 1 < count) layer1((i + 1) & 3);
+    __syncthreads();
+    if (i + 1 < count) infer_hidden<TILES>(w2, b2, h1, h2, n_base, lane);
+    if (wv < TILES) layer4(i);
+    if (xm < M) xs[(i + 2) & 3][xm][xk] = x_next;
+    __syncthreads();
   }
 }
 
@@ -716,10 +842,22 @@ __global__ void __launch_bounds__(256) refresh_bf16_kernel(const MlpArgs a) {
 
 int mlp_tile() { return TM; }
 
-hipError_t launch_mlp_forward(const MlpArgs& a, bool train, hipStream_t s) {
-  const dim3 grid((unsigned)((a.batch + TM - 1) / TM)), block(NT);
-  if (train) hipLaunchKernelGGL(mlp_forward_kernel<true>, grid, block, 0, s, a);
-  else       hipLaunchKernelGGL(mlp_forward_kernel<false>, grid, block, 0, s, a);
+hipError_t launch_mlp_infer(const MlpArgs& a, hipStream_t s) {
+  // A workgroup per CU.  Tiles of 32 samples spread a small batch over more of
+  // them; from four such rounds on, the two barriers per tile weigh more: 32
+  // against 64 samples a tile, 13.1 / 15.8 us for 1000, 19.5 / 21.4 for 24576,
+  // 22.6 / 21.4 for 32768, 833 / 735 for 2^21.
+  const int64_t small = (a.batch + 31) / 32, large = (a.batch + 63) / 64;
+  const dim3 block(64 * kInferWaves);
+  if (small <= 3 * kMlpCus)
+    hipLaunchKernelGGL(mlp_infer_kernel<2>, dim3((unsigned)std::min(kMlpCus, small)), block, 0, s, a);
+  else
+    hipLaunchKernelGGL(mlp_infer_kernel<4>, dim3((unsigned)std::min(kMlpCus, large)), block, 0, s, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_mlp_train(const MlpArgs& a, hipStream_t s) {
+  hipLaunchKernelGGL(mlp_train_kernel, dim3((unsigned)((a.batch + TM - 1) / TM)), dim3(NT), 0, s, a);
   return hipGetLastError();
 }
 

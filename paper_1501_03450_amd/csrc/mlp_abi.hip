@@ -184,7 +184,7 @@ st_status compute_gradient(st_mlp* m, const float* x, const float* t, int64_t ba
   const int nb = (int)(ld / tile);
   const int64_t W = st::kMlpWidth;
   hipError_t e;
-  if ((e = st::launch_mlp_forward(a, true, s)) != hipSuccess) return hip_fail(m, e, "forward and backward");
+  if ((e = st::launch_mlp_train(a, s)) != hipSuccess) return hip_fail(m, e, "forward and backward");
   if ((e = st::launch_mlp_weight_grad(a, s)) != hipSuccess) return hip_fail(m, e, "weight gradients");
   const st::MlpOffsets& o = m->off;
   // every tensor's partials (and the loss) reduced together, one launch per pass
@@ -414,7 +414,7 @@ st_status st_mlp_infer(st_mlp* m, const float* d_x, float* d_q, int64_t n, void*
   a.batch = n;
   a.x = d_x;
   a.q_out = d_q;
-  hipError_t e = st::launch_mlp_forward(a, false, (hipStream_t)stream);
+  hipError_t e = st::launch_mlp_infer(a, (hipStream_t)stream);
   if (e != hipSuccess) return hip_fail(m, e, "inference");
   return ST_OK;
 }

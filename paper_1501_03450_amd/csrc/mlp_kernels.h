@@ -86,9 +86,11 @@ int mlp_tile();
 hipError_t launch_features(const double* z, int64_t n, const FeatureMap& f, int n_in, float* x,
                            hipStream_t s);
 hipError_t launch_targets(const double* q, int64_t n, const double* ref, float* t, hipStream_t s);
-// train: the fused forward and backward pass of one batch (activations, dz2,
-// dz3 and the per-tile partials); otherwise inference into q_out.
-hipError_t launch_mlp_forward(const MlpArgs& a, bool train, hipStream_t s);
+// Inference of a.batch samples into q_out.
+hipError_t launch_mlp_infer(const MlpArgs& a, hipStream_t s);
+// The fused forward and backward pass of one batch (activations, dz2, dz3 and
+// the per-tile partials).
+hipError_t launch_mlp_train(const MlpArgs& a, hipStream_t s);
 // dW2, dW3 split-K partials from the feature-major activations and gradients.
 hipError_t launch_mlp_weight_grad(const MlpArgs& a, hipStream_t s);
 // Several independent column sums of row-major partials part[parts][len] into
