@@ -5,34 +5,32 @@
 // The two 256×256 layers run on the matrix cores: bf16 operands, fp32
 // accumulation, v_mfma_f32_16x16x32_bf16 (A[i][k] in lane i + 16(k/8),
 // element k%8; B[k][j] in lane j + 16(k/8); D[i][j] in lane j + 16(i/4),
-// element i%4).  The n_in -> 256 layer (and its recomputation and weight
-// gradient in the backward pass) runs on the fp32 matrix cores,
-// v_mfma_f32_16x16x4_f32 (A[i][k] in lane i + 16k, B[k][j] in lane j + 16k,
-// D as above), so its operands stay fp32.  The 256 -> 4 layer and its weight
-// gradient use the bf16 matrix cores with the fp32 operand (W4, dL/dy) split
-// into three bf16 parts whose sum is exact, so those products keep fp32
-// precision too.
+// element i%4), with the weights as A and the samples as columns of B.  The
+// n_in -> 256 layer (and its recomputation and weight gradient in the backward
+// pass) runs on the fp32 matrix cores, v_mfma_f32_16x16x4_f32 (A[i][k] in lane
+// i + 16k, B[k][j] in lane j + 16k, D as above), so its operands stay fp32.
+// The 256 -> 4 layer and its weight gradient use the bf16 matrix cores with the
+// fp32 operand (W4, dL/dy) split into three bf16 parts whose sum is exact, so
+// those products keep fp32 precision too.
 //
-// Kernels (one batch; training: 64 samples per workgroup of four waves):
+// Kernels:
 //   infer          all four layers fused, W2 and W3 in registers, activations
 //                  kept in LDS
-//   train          the training step's forward and backward passes of one
-//                  tile in one kernel: it stores the two hidden activations
-//                  the weight gradients need and silu'(z2) (bf16,
-//                  feature-major, straight from the accumulators), keeps
-//                  silu'(z3) and dL/dy in LDS, fuses the loss,
-//                  then runs dL/dy -> dz3 -> dz2 -> dz1 through the transposed
-//                  bf16 weights with z1 recomputed by the same matrix-core
-//                  products, stores dz3 and dz2 feature-major, and forms the
-//                  per-workgroup partial sums of the b1..b4, W1 and W4
-//                  gradients
-//   weight_grad    dW2, dW3 = dzᵀ hᵀ as split-K MFMA GEMMs over the batch
+//   train_forward  the same with the loss and dL/dy; stores h1, h2 and dz3
+//                  (sample-major) for the weight gradients, silu'(z2) and dz3
+//                  for the backward half, and forms the per-workgroup partial
+//                  sums of the b3, W4 and b4 gradients
+//   train_backward dz3 -> dz2 -> dz1 through W3ᵀ and W2ᵀ in registers, z1
+//                  recomputed by the forward half's products; stores dz2 and
+//                  forms the partial sums of the b2, b1 and W1 gradients
+//   weight_grad    dW2, dW3 = dzᵀ h as split-K MFMA GEMMs over the batch
 //   reduce         fixed-order sum of the partials (deterministic)
 //   adam           fp32 master weights, then the bf16 copies W and Wᵀ
 #include <hip/hip_runtime.h>
 #include <hip/hip_bf16.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "mlp_kernels.h"
 
@@ -41,12 +39,12 @@ namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef int i32x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 
 constexpr int W = kMlpWidth;       // 256
-constexpr int TM = 64;             // samples per workgroup
 constexpr int LDA = W + 8;         // padded LDS row (bf16 elements)
-constexpr int NT = 256;            // threads per workgroup
+constexpr int NT = 256;            // threads of a weight-gradient workgroup
 
 // σ(z) = 1/(1 + e^-z) with the hardware exponential and reciprocal
 // (about 1 ulp each): the activations are rounded to bf16 right after.
@@ -59,62 +57,11 @@ __device__ __forceinline__ float dsilu(float z) {
   return s * (1.0f + z * (1.0f - s));
 }
 
-// acc[mt][nt] += A[16 MT x 256] (LDS, row stride LDA) · B'[n_base + 16 nt + j][k]
-// (global, row-major [256][256]) for the wave's 64 output columns.  Each
-// 16x16 output tile accumulates over k in the same order whatever MT and
-// UNROLL are, so a tile computed in a smaller call has the same bits.  With
-// the loop unrolled (UNROLL = 8) the compiler issues the B loads of later k
-// steps ahead of the MFMAs; the L2 latency that remains is covered by the
-// other waves on the SIMD.  Callers short of registers unroll by 2.
-template <int MT, int UNROLL = 8>
-__device__ __forceinline__ void gemm_tiles(const __bf16* A, const __bf16* Bg, int n_base,
-                                           f32x4 acc[MT][4], int lane) {
-  const int r = lane & 15, kb = 8 * (lane >> 4);
-  const __bf16* brow = Bg + (size_t)(n_base + r) * W + kb;
-#pragma unroll UNROLL
-  for (int k0 = 0; k0 < W; k0 += 32) {
-    bf16x8 a[MT], b[4];
-#pragma unroll
-    for (int nt = 0; nt < 4; ++nt) b[nt] = *reinterpret_cast<const bf16x8*>(brow + nt * 16 * W + k0);
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-      a[mt] = *reinterpret_cast<const bf16x8*>(A + (mt * 16 + r) * LDA + k0 + kb);
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-      for (int nt = 0; nt < 4; ++nt)
-        acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[mt], b[nt], acc[mt][nt], 0, 0, 0);
-  }
-}
-
-template <int UNROLL = 8>
-__device__ __forceinline__ void gemm_64x64(const __bf16* A, const __bf16* Bg, int n_base,
-                                           f32x4 acc[4][4], int lane) {
-  gemm_tiles<4, UNROLL>(A, Bg, n_base, acc, lane);
-}
-
 __device__ __forceinline__ void zero_acc(f32x4 acc[4][4]) {
 #pragma unroll
   for (int mt = 0; mt < 4; ++mt)
 #pragma unroll
     for (int nt = 0; nt < 4; ++nt) acc[mt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
-}
-
-// Layer 1 for the 16 features n0 .. n0 + 15 on the fp32 matrix cores:
-// acc[mt] = x[16 mt + i][k] W1[n0 + j][k] summed over the eight zero-padded
-// inputs, two steps of four.  The backward pass recomputes z1 with the same
-// call, so both passes see the same bits.
-__device__ __forceinline__ void layer1_cols(const float (*xs)[kMlpMaxIn], const float* W1, int nin,
-                                            int n0, f32x4 acc[4], int lane) {
-  const int r = lane & 15, kq = lane >> 4;
-  const float w0 = kq < nin ? W1[(n0 + r) * nin + kq] : 0.0f;
-  const float w1 = 4 + kq < nin ? W1[(n0 + r) * nin + 4 + kq] : 0.0f;
-#pragma unroll
-  for (int mt = 0; mt < 4; ++mt) {
-    f32x4 d = {0.f, 0.f, 0.f, 0.f};
-    d = __builtin_amdgcn_mfma_f32_16x16x4f32(xs[mt * 16 + r][kq], w0, d, 0, 0, 0);
-    acc[mt] = __builtin_amdgcn_mfma_f32_16x16x4f32(xs[mt * 16 + r][4 + kq], w1, d, 0, 0, 0);
-  }
 }
 
 // Part `part` (0, 1 or 2) of v split into three bf16 values that sum to v
@@ -129,423 +76,68 @@ __device__ __forceinline__ __bf16 split3(float v, int part) {
   return (__bf16)(r - (float)mid);
 }
 
-// Hidden-layer epilogue: z = acc + b, h = silu(z) into LDS (bf16, row-major)
-// and to HBM feature-major [256][ld] from the registers (a lane holds four
-// consecutive samples of one feature: one 8-byte store per 16x16 tile).
-__device__ __forceinline__ void hidden_epilogue(const f32x4 acc[4][4], const float* bias,
-                                                __bf16* out_lds, int rows, int n_base, int lane,
-                                                __bf16* hT, int64_t ld, int64_t b0) {
-  const int c = lane & 15, rq = 4 * (lane >> 4);
+// Layout of the bf16 copies of a 256×256 matrix: the order in which the waves of
+// a workgroup hold it in registers.  Wave n / 32 takes 32 rows as two 16-row
+// operand tiles whose rows are interleaved by four, so that a lane's accumulators
+// are eight consecutive rows' (features) of one column (sample), one 16-byte
+// store; the operands of a (wave, tile, 32-step of k) are 1 KB in lane order.
+// Read from row-major copies, 64 bytes of 16 rows per load, the 256 KB took 18000
+// cycles per CU.
+__device__ __forceinline__ int weight_at(int n, int k) {
+  const int r = 4 * (n >> 3 & 3) + (n & 3), ft = n >> 2 & 1;
+  return (((n >> 5) * 16 + ft * 8 + (k >> 5)) * 64 + r + 16 * (k >> 3 & 3)) * 8 + (k & 7);
+}
+// the row of lane r's operand in tile ft of a wave's rows
+__device__ __forceinline__ int wave_row(int n_base, int ft, int r) {
+  return n_base + 8 * (r >> 2) + 4 * ft + (r & 3);
+}
+__device__ __forceinline__ void load_weights(bf16x8 (&w)[2][8], const __bf16* src, int wv, int lane) {
+  const __bf16* p = src + wv * 32 * W;
 #pragma unroll
-  for (int nt = 0; nt < 4; ++nt) {
-    const int n = n_base + nt * 16 + c;
-    const float bn = bias[n];
+  for (int ft = 0; ft < 2; ++ft)
 #pragma unroll
-    for (int mt = 0; mt < 4; ++mt) {
-      const int m0 = mt * 16 + rq;
-      bf16x4 h;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const float z = acc[mt][nt][i] + bn;
-        // padded samples (beyond the batch) carry zero activations
-        h[i] = (__bf16)(m0 + i < rows ? silu(z) : 0.0f);
-        out_lds[(m0 + i) * LDA + n] = h[i];
-      }
-      *reinterpret_cast<bf16x4*>(hT + (size_t)n * ld + b0 + m0) = h;
-    }
-  }
+    for (int k = 0; k < 8; ++k)
+      w[ft][k] = *reinterpret_cast<const bf16x8*>(p + (unsigned)(((ft * 8 + k) * 64 + lane) * 8));
 }
 
-// silu'(z3) of a wave's 64x64 tile kept in LDS between the forward and
-// backward halves of the training kernel, in the accumulator layout: lane
-// `lane` of the wave stores the four bf16 values of (nt, mt) (samples
-// 16 mt + rq .. + 3 of feature 16 nt + c) as one 8-byte word at
-// [(4 nt + mt) * 64 + lane] of the wave's 8 KB, and reads back only its own.
-
-__device__ __forceinline__ uint32_t pack_bf16x2(__bf16 lo, __bf16 hi) {
-  return (uint32_t)__builtin_bit_cast(unsigned short, lo) |
-         ((uint32_t)__builtin_bit_cast(unsigned short, hi) << 16);
-}
-// element i (0..3) of a packed quadruple, as float
-__device__ __forceinline__ float ds_at(uint2 q, int i) {
-  const uint32_t w = (i >> 1) ? q.y : q.x;
-  return __builtin_bit_cast(float, (i & 1) ? (w & 0xffff0000u) : (w << 16));
-}
-
-// Training epilogue of layers 2 and 3: as hidden_epilogue, and silu'(z)
-// rounded to bf16 (zero for padded samples) either to HBM feature-major
-// [256][ld] from the registers (dsT set) or to the wave's LDS words (ds).
-__device__ __forceinline__ void hidden_epilogue_dsilu(const f32x4 acc[4][4], const float* bias,
-                                                      __bf16* out_lds, int rows, int n_base,
-                                                      int lane, __bf16* dsT, uint2* ds,
-                                                      __bf16* hT, int64_t ld, int64_t b0) {
-  const int c = lane & 15, rq = 4 * (lane >> 4);
+// acc = rows of w times the 256 inputs of a sample (row: the lane's sample, from
+// its first k on)
+__device__ __forceinline__ void wave_gemm(const bf16x8 (&w)[2][8], const __bf16* row, f32x4 (&acc)[2]) {
 #pragma unroll
-  for (int nt = 0; nt < 4; ++nt) {
-    const int n = n_base + nt * 16 + c;
-    const float bn = bias[n];
+  for (int ft = 0; ft < 2; ++ft) acc[ft] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int mt = 0; mt < 4; ++mt) {
-      const int m0 = mt * 16 + rq;
-      bf16x4 d, h;
+  for (int k = 0; k < 8; ++k) {
+    const bf16x8 x = *reinterpret_cast<const bf16x8*>(row + 32 * k);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const float z = acc[mt][nt][i] + bn;
-        const float sg = sigmoid(z);
-        const bool in = m0 + i < rows;
-        h[i] = (__bf16)(in ? z * sg : 0.0f);
-        out_lds[(m0 + i) * LDA + n] = h[i];
-        d[i] = (__bf16)(in ? sg * (1.0f + z * (1.0f - sg)) : 0.0f);
-      }
-      if (dsT) {
-        *reinterpret_cast<bf16x4*>(dsT + (size_t)n * ld + b0 + m0) = d;
-      } else {
-        ds[(nt * 4 + mt) * 64 + lane] = make_uint2(pack_bf16x2(d[0], d[1]), pack_bf16x2(d[2], d[3]));
-      }
-      if (hT) *reinterpret_cast<bf16x4*>(hT + (size_t)n * ld + b0 + m0) = h;
-    }
-  }
-}
-
-// A wave's 64 x 64 block of gradients into LDS (bf16, row-major); samples
-// beyond the batch get zeros.  With dzT set, the same bf16 values also go to
-// HBM feature-major from the registers, and gb[n] receives their sum over
-// the tile's samples (the bias gradient partial).
-__device__ __forceinline__ void store_grad_tile(const f32x4 acc[4][4], __bf16* out_lds, int rows,
-                                                int n_base, int lane, __bf16* dzT = nullptr,
-                                                int64_t ld = 0, int64_t b0 = 0,
-                                                float* gb = nullptr) {
-  const int c = lane & 15, rq = 4 * (lane >> 4);
-#pragma unroll
-  for (int nt = 0; nt < 4; ++nt) {
-    const int n = n_base + nt * 16 + c;
-    float sum = 0.0f;
-#pragma unroll
-    for (int mt = 0; mt < 4; ++mt) {
-      const int m0 = mt * 16 + rq;
-      bf16x4 v;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        v[i] = (__bf16)(m0 + i < rows ? acc[mt][nt][i] : 0.0f);
-        out_lds[(m0 + i) * LDA + n] = v[i];
-        sum += (float)v[i];
-      }
-      if (dzT) *reinterpret_cast<bf16x4*>(dzT + (size_t)n * ld + b0 + m0) = v;
-    }
-    if (gb) {
-      // the four lane groups hold samples rq = 0, 4, 8, 12 of every 16
-      sum += __shfl_xor(sum, 16, 64);
-      sum += __shfl_xor(sum, 32, 64);
-      if (lane < 16) gb[n] = sum;
-    }
-  }
-}
-
-// One activation buffer per workgroup: each layer's GEMM reads it, a barrier,
-// then the epilogue overwrites it with the layer's output.  The same tile then
-// runs the backward pass through the layers, with
-// silu'(z3) kept in LDS from the forward epilogue (bf16, in the accumulator
-// layout the backward products use), silu'(z2) read back from HBM and dL/dy
-// in LDS: dz3 = (dL/dy W4) ⊙ silu'(z3), dz2 = (dz3 W3) ⊙ silu'(z2) and
-// dz1 = (dz2 W2) ⊙ silu'(z1) with z1 recomputed by the same matrix-core
-// products as in the forward half.  h1, h2, dz2 and dz3 go to HBM
-// feature-major for the weight-gradient kernel; the bias, W1 and W4 gradient
-// partials of the tile are formed here.  Two waves per SIMD, 180 registers
-// without spills and 68 KB of LDS (two workgroups per CU); with silu'(z3)
-// in registers instead the kernel spilled 32 bytes per lane, and with
-// silu'(z2) there as well 368.
-#ifndef ST_MLP_TRAIN_WAVES
-#define ST_MLP_TRAIN_WAVES 2
-#endif
-__global__ void __launch_bounds__(NT)
-__attribute__((amdgpu_waves_per_eu(ST_MLP_TRAIN_WAVES, ST_MLP_TRAIN_WAVES)))
-mlp_train_kernel(const MlpArgs a) {
-  __shared__ __align__(16) __bf16 bufA[TM * LDA];
-  __shared__ float xs[TM][kMlpMaxIn];
-  __shared__ float ys[TM][4];
-  __shared__ float red[NT / 64];
-  // silu'(z3) of the four waves' tiles (32 KB)
-  __shared__ uint2 ds3s[(NT / 64) * 16 * 64];
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  uint2* const ds3 = ds3s + wv * 16 * 64;
-  const int64_t B = a.batch, b0 = (int64_t)blockIdx.x * TM;
-  const int rows = (int)min((int64_t)TM, B - b0);
-  const int nin = a.n_in;
-  const float* P = a.params;
-
-  for (int i = tid; i < TM * kMlpMaxIn; i += NT) {
-    const int m = i / kMlpMaxIn, k = i % kMlpMaxIn;
-    xs[m][k] = (m < rows && k < nin) ? a.x[(b0 + m) * nin + k] : 0.0f;
-  }
-  __syncthreads();
-
-  // layer 1 (fp32 matrix cores): the wave's 64 features
-  f32x4 acc[4][4];
-#pragma unroll
-  for (int nt = 0; nt < 4; ++nt) {
-    f32x4 col[4];
-    layer1_cols(xs, P + a.off.W1, nin, wv * 64 + nt * 16, col, lane);
-#pragma unroll
-    for (int mt = 0; mt < 4; ++mt) acc[mt][nt] = col[mt];
-  }
-  hidden_epilogue(acc, P + a.off.b1, bufA, rows, wv * 64, lane, a.hT1, a.ld, b0);
-  __syncthreads();
-
-  // layer 2 (MFMA)
-  zero_acc(acc);
-  gemm_64x64<2>(bufA, a.W2b, wv * 64, acc, lane);
-  __syncthreads();
-  hidden_epilogue_dsilu(acc, P + a.off.b2, bufA, rows, wv * 64, lane, a.dsT2, ds3, a.hT2, a.ld, b0);
-  __syncthreads();
-  // layer 3 (MFMA)
-  zero_acc(acc);
-  gemm_64x64<2>(bufA, a.W3b, wv * 64, acc, lane);
-  __syncthreads();
-  hidden_epilogue_dsilu(acc, P + a.off.b3, bufA, rows, wv * 64, lane, nullptr, ds3, nullptr, a.ld, b0);
-  __syncthreads();
-
-  // layer 4 (bf16 matrix cores, W4 in three parts: operand rows j, 4 + j and
-  // 8 + j): wave wv takes samples 16 wv .. 16 wv + 15, and the three partial
-  // outputs of (sample, j) sit in lanes c = j, j + 4, j + 8 of a lane group
-  {
-    const int r = lane & 15, kb = 8 * (lane >> 4), rq = 4 * (lane >> 4);
-    f32x4 y4 = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int k0 = 0; k0 < W; k0 += 32) {
-      const bf16x8 av = *reinterpret_cast<const bf16x8*>(bufA + (wv * 16 + r) * LDA + k0 + kb);
-      const bf16x8 bv = *reinterpret_cast<const bf16x8*>(a.W4s + r * W + k0 + kb);
-      y4 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bv, y4, 0, 0, 0);
-    }
-    const float bj = P[a.off.b4 + (r & 3)];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const float mid = __shfl(y4[i], lane + 4, 64), lo = __shfl(y4[i], lane + 8, 64);
-      if (r < 4) ys[wv * 16 + rq + i][r] = bj + ((y4[i] + mid) + lo);
-    }
-  }
-  __syncthreads();
-
-  // normalised output, the loss and dL/dy (into ys, zero for padded samples)
-  float l = 0.0f;
-  if (tid < TM) {
-    const int m = tid;
-    // frame base ref + lin x (zero columns past n_in: xs is zero-padded)
-    float base[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      float b = a.out_ref[j];
-#pragma unroll
-      for (int k = 0; k < kMlpMaxIn; ++k) b = fmaf(a.out_lin[j][k], xs[m][k], b);
-      base[j] = b;
-    }
-    const float y0 = fmaf(a.out_scale[0], ys[m][0], base[0]);
-    const float y1 = fmaf(a.out_scale[1], ys[m][1], base[1]);
-    const float y2 = fmaf(a.out_scale[2], ys[m][2], base[2]);
-    const float y3 = fmaf(a.out_scale[3], ys[m][3], base[3]);
-    const float ny = sqrtf(y0 * y0 + y1 * y1 + y2 * y2 + y3 * y3);
-    const float inv = 1.0f / ny;
-    const float q[4] = {y0 * inv, y1 * inv, y2 * inv, y3 * inv};
-    if (m < rows) {
-      const float* t = a.target + (b0 + m) * 4;
-      float dq[4], qd = 0.0f;
-      for (int j = 0; j < 4; ++j) {
-        const float d = q[j] - t[j];
-        l += d * d;
-        dq[j] = 2.0f * d * a.inv_loss_norm;
-        qd += q[j] * dq[j];
-      }
-      for (int j = 0; j < 4; ++j) ys[m][j] = a.out_scale[j] * ((dq[j] - q[j] * qd) * inv);
-    } else {
-      for (int j = 0; j < 4; ++j) ys[m][j] = 0.0f;
-    }
-  }
-  for (int off = 32; off > 0; off >>= 1) l += __shfl_xor(l, off, 64);
-  if (lane == 0) red[wv] = l;
-  __syncthreads();
-  if (tid == 0) a.loss_part[blockIdx.x] = (red[0] + red[1] + red[2] + red[3]) * a.inv_loss_norm;
-  const int blk = blockIdx.x;
-
-  // dW4 and db4 partials of this tile.
-  // gW4[j][k] = sum over m of dL/dy[m][j] h3[m][k] on the bf16 matrix cores
-  // with dL/dy in three parts (operand rows j, 4 + j, 8 + j; rows 12-15
-  // zero; padded samples have dL/dy = 0): wave wv takes features 64 wv ..
-  // 64 wv + 63, and the parts of row j come out in lane groups 0, 1 and 2
-  {
-    const int r = lane & 15, kb = 8 * (lane >> 4);
-    f32x4 g[4];
-#pragma unroll
-    for (int t = 0; t < 4; ++t) g[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int s0 = 0; s0 < TM; s0 += 32) {
-      bf16x8 av;
-#pragma unroll
-      for (int e = 0; e < 8; ++e)
-        av[e] = r < 12 ? split3(ys[s0 + kb + e][r & 3], r >> 2) : (__bf16)0.0f;
-#pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        const int n = wv * 64 + t * 16 + r;
-        bf16x8 bv;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) bv[e] = bufA[(s0 + kb + e) * LDA + n];
-        g[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bv, g[t], 0, 0, 0);
-      }
-    }
-#pragma unroll
-    for (int t = 0; t < 4; ++t)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const float mid = __shfl(g[t][i], lane + 16, 64), lo = __shfl(g[t][i], lane + 32, 64);
-        if (lane < 16)
-          a.gpart_W4[((size_t)blk * 4 + i) * W + wv * 64 + t * 16 + r] = (g[t][i] + mid) + lo;
-      }
-    // wave wv sums column wv over its 64 samples (zero past the batch)
-    float sb = ys[lane][wv];
-    for (int off = 32; off > 0; off >>= 1) sb += __shfl_xor(sb, off, 64);
-    if (lane == 0) a.gpart_b4[(size_t)blk * 4 + wv] = sb;
-  }
-  __syncthreads();   // h3 in bufA read by every wave before dz3 replaces it
-
-  // backward half
-  const int n_base = wv * 64, c = lane & 15, rq = 4 * (lane >> 4);
-  // dz3 = (dL/dy W4) ⊙ silu'(z3) in the accumulator layout (a lane: four
-  // consecutive samples of one feature, silu'(z3) one 8-byte load), its bias
-  // gradient partial before rounding, and dz3 in bf16 into LDS (zero past the
-  // batch, where dL/dy is zero)
-  {
-    float gb[4];
-#pragma unroll
-    for (int nt = 0; nt < 4; ++nt) {
-      const int n = n_base + nt * 16 + c;
-      const float w0 = P[a.off.W4 + 0 * W + n], w1 = P[a.off.W4 + 1 * W + n];
-      const float w2 = P[a.off.W4 + 2 * W + n], w3 = P[a.off.W4 + 3 * W + n];
-      float sum = 0.0f;
-#pragma unroll
-      for (int mt = 0; mt < 4; ++mt) {
-        bf16x4 v;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int m = mt * 16 + rq + i;
-          const float dh = w0 * ys[m][0] + w1 * ys[m][1] + w2 * ys[m][2] + w3 * ys[m][3];
-          const float dz = dh * ds_at(ds3[(nt * 4 + mt) * 64 + lane], i);
-          sum += dz;
-          v[i] = (__bf16)dz;
-          bufA[m * LDA + n] = v[i];
-        }
-        *reinterpret_cast<bf16x4*>(a.dzT3 + (size_t)n * a.ld + b0 + mt * 16 + rq) = v;
-      }
-      gb[nt] = sum;
-    }
-    // sum the four lane groups (samples rq = 0, 4, 8, 12 of every 16)
-#pragma unroll
-    for (int nt = 0; nt < 4; ++nt) {
-      gb[nt] += __shfl_xor(gb[nt], 16, 64);
-      gb[nt] += __shfl_xor(gb[nt], 32, 64);
-    }
-    if (lane < 16)
-#pragma unroll
-      for (int nt = 0; nt < 4; ++nt) a.gpart_b3[(size_t)blk * W + n_base + nt * 16 + c] = gb[nt];
-  }
-  __syncthreads();
-
-  // dz2 = (dz3 W3) ⊙ silu'(z2): a lane's four consecutive samples of one
-  // feature are one 8-byte load of the feature-major silu'(z2)
-  zero_acc(acc);
-  gemm_64x64<2>(bufA, a.W3Tb, n_base, acc, lane);
-#pragma unroll
-  for (int nt = 0; nt < 4; ++nt) {
-    const __bf16* dsrow = a.dsT2 + (size_t)(n_base + nt * 16 + c) * a.ld + b0;
-#pragma unroll
-    for (int mt = 0; mt < 4; ++mt) {
-      const bf16x4 d = *reinterpret_cast<const bf16x4*>(dsrow + mt * 16 + rq);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) acc[mt][nt][i] = acc[mt][nt][i] * (float)d[i];
-    }
-  }
-  __syncthreads();   // bufA: dz3 -> dz2
-  store_grad_tile(acc, bufA, rows, n_base, lane, a.dzT2, a.ld, b0, a.gpart_b2 + (size_t)blk * W);
-  __syncthreads();
-  // dz1 = (dz2 W2) ⊙ silu'(z1), z1 = W1 x + b1 by the forward pass's products
-  zero_acc(acc);
-  gemm_64x64<2>(bufA, a.W2Tb, n_base, acc, lane);
-#pragma unroll
-  for (int nt = 0; nt < 4; ++nt) {
-    f32x4 z1[4];
-    layer1_cols(xs, P + a.off.W1, nin, n_base + nt * 16, z1, lane);
-    const float bn = P[a.off.b1 + n_base + nt * 16 + c];
-#pragma unroll
-    for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) acc[mt][nt][i] = acc[mt][nt][i] * dsilu(z1[mt][i] + bn);
-  }
-  __syncthreads();   // bufA: dz2 -> dz1
-  store_grad_tile(acc, bufA, rows, n_base, lane);
-  __syncthreads();
-  // W1 and b1 gradient partials on the fp32 matrix cores: D[n][k] = sum over
-  // m of dz1[m][n] [x | 1][m][k], A = dz1ᵀ (the wave's 64 features, from
-  // LDS), B = the inputs with a column of ones after them, steps of four
-  // samples (padded samples have dz1 = 0)
-  {
-    const int r = lane & 15, kq = lane >> 4;
-    f32x4 g[4];
-#pragma unroll
-    for (int t = 0; t < 4; ++t) g[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll 4
-    for (int s0 = 0; s0 < TM; s0 += 4) {
-      const int m = s0 + kq;
-      const float bx = r < nin ? xs[m][r] : (r == nin ? 1.0f : 0.0f);
-#pragma unroll
-      for (int t = 0; t < 4; ++t)
-        g[t] = __builtin_amdgcn_mfma_f32_16x16x4f32((float)bufA[m * LDA + n_base + t * 16 + r], bx,
-                                                    g[t], 0, 0, 0);
-    }
-#pragma unroll
-    for (int t = 0; t < 4; ++t)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int n = n_base + t * 16 + rq + i;
-        if (c < nin) a.gpart_W1[((size_t)blk * W + n) * nin + c] = g[t][i];
-        else if (c == nin) a.gpart_b1[(size_t)blk * W + n] = g[t][i];
-      }
+    for (int ft = 0; ft < 2; ++ft)
+      acc[ft] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[ft][k], x, acc[ft], 0, 0, 0);
   }
 }
 
 // Inference.  One persistent workgroup per compute unit, eight waves; wave wv
 // holds rows 32 wv .. 32 wv + 31 of W2 and W3 in registers (128 of them) for
 // all its tiles, so that the weights cross L2 once per launch instead of once per
-// tile.  Weights are the A operand and activations the B operand: a lane then
-// has four consecutive features of one sample, one 8-byte LDS store.  Layer 3 of
-// a tile runs beside layer 1 of the next, layer 2 of that beside layer 4: two
+// tile.  Layer 3 of a tile runs beside layer 1 of the next, layer 2 of that beside layer 4: two
 // barriers per tile, and work for both the matrix cores and the vector units
 // between them.  What bounds it is the activation's exponential and reciprocal
-// (a quarter of the vector rate): about 150 cycles a sample and CU, of the 205
-// it takes.  The sums run in the order that one wave per 64 columns gives.  2^21
-// samples: 1236 -> 735 us against a workgroup per tile with the weights read
-// from L2 by every tile; 65536: 47 -> 33; 1000: 22.7 -> 13.1.
+// (a quarter of the vector rate): about 150 cycles a sample and CU, of the 200
+// it takes.  2^21 samples: 1256 -> 716 us against a workgroup per tile with the
+// weights read from L2 by every tile.
 constexpr int kInferWaves = 8;
 constexpr int64_t kMlpCus = 256;
 
 template <int TILES>       // samples per tile / 16
-__device__ __forceinline__ void infer_hidden(const bf16x8 (&w)[2][8], const f32x4 (&bias)[2],
-                                             const __bf16* in, __bf16* out, int n_base, int lane) {
+__device__ __forceinline__ void infer_hidden(const bf16x8 (&w)[2][8], const float (&bias)[8],
+                                             const __bf16* in, __bf16* out, int f0, int lane) {
   const int r = lane & 15, g = lane >> 4;
 #pragma unroll
   for (int st = 0; st < TILES; ++st) {
-    const __bf16* row = in + (st * 16 + r) * LDA + 8 * g;
-    f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+    f32x4 acc[2];
+    wave_gemm(w, in + (st * 16 + r) * LDA + 8 * g, acc);
+    bf16x8 h;
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      const bf16x8 x = *reinterpret_cast<const bf16x8*>(row + 32 * k);
-#pragma unroll
-      for (int ft = 0; ft < 2; ++ft)
-        acc[ft] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[ft][k], x, acc[ft], 0, 0, 0);
-    }
-#pragma unroll
-    for (int ft = 0; ft < 2; ++ft) {
-      bf16x4 h;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) h[i] = (__bf16)silu(acc[ft][i] + bias[ft][i]);
-      *reinterpret_cast<bf16x4*>(out + (st * 16 + r) * LDA + n_base + 16 * ft + 4 * g) = h;
-    }
+    for (int e = 0; e < 8; ++e) h[e] = (__bf16)silu(acc[e >> 2][e & 3] + bias[e]);
+    *reinterpret_cast<bf16x8*>(out + (st * 16 + r) * LDA + f0) = h;
   }
 }
 
@@ -556,7 +148,7 @@ mlp_infer_kernel(const MlpArgs a) {
   __shared__ __align__(16) __bf16 h1[M * LDA], h2[M * LDA], h3[M * LDA], w4[16 * LDA];
   __shared__ float xs[4][M][XS];
   const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int r = lane & 15, g = lane >> 4, n_base = 32 * wv, nin = a.n_in;
+  const int r = lane & 15, g = lane >> 4, n_base = 32 * wv, f0 = n_base + 8 * g, nin = a.n_in;
   const int64_t B = a.batch, tiles = (B + M - 1) / M;
   const int count = (int)((tiles - blockIdx.x + gridDim.x - 1) / gridDim.x);
   const float* P = a.params;
@@ -566,45 +158,42 @@ mlp_infer_kernel(const MlpArgs a) {
     return i < count && xm < M && m < B && xk < nin ? a.x[m * nin + xk] : 0.0f;
   };
   float x_next = load_x(0);
+  float b1[8], b2[8], b3[8], w1[2][2];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    b1[e] = P[a.off.b1 + f0 + e];
+    b2[e] = P[a.off.b2 + f0 + e];
+    b3[e] = P[a.off.b3 + f0 + e];
+  }
+#pragma unroll
+  for (int ft = 0; ft < 2; ++ft)
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const float v = P[a.off.W1 + wave_row(n_base, ft, r) * nin + min(4 * q + g, nin - 1)];
+      w1[ft][q] = 4 * q + g < nin ? v : 0.0f;
+    }
+  const bf16x8 w4_piece = *reinterpret_cast<const bf16x8*>(a.W4s + tid * 8);
+  // (loads arrive in order: what the first layer needs ahead of the weights)
+  __builtin_amdgcn_sched_barrier(0);
   bf16x8 w2[2][8], w3[2][8];
-  f32x4 b1[2], b2[2], b3[2];
-  float w1[2][2];
-#pragma unroll
-  for (int ft = 0; ft < 2; ++ft) {
-    const int n = n_base + 16 * ft;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      b1[ft][i] = P[a.off.b1 + n + 4 * g + i];
-      b2[ft][i] = P[a.off.b2 + n + 4 * g + i];
-      b3[ft][i] = P[a.off.b3 + n + 4 * g + i];
-    }
-#pragma unroll
-    for (int q = 0; q < 2; ++q) w1[ft][q] = 4 * q + g < nin ? P[a.off.W1 + (n + r) * nin + 4 * q + g] : 0.0f;
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      w2[ft][k] = *reinterpret_cast<const bf16x8*>(a.W2b + (size_t)(n + r) * W + 32 * k + 8 * g);
-      w3[ft][k] = *reinterpret_cast<const bf16x8*>(a.W3b + (size_t)(n + r) * W + 32 * k + 8 * g);
-    }
-  }
-  {
-    const int row = tid / 32, k = tid % 32 * 8;
-    *reinterpret_cast<bf16x8*>(w4 + row * LDA + k) =
-        *reinterpret_cast<const bf16x8*>(a.W4s + row * W + k);
-  }
+  load_weights(w2, a.W2b, wv, lane);
+  load_weights(w3, a.W3b, wv, lane);
+  __builtin_amdgcn_sched_barrier(0);
+  *reinterpret_cast<bf16x8*>(w4 + tid / 32 * LDA + tid % 32 * 8) = w4_piece;
   auto layer1 = [&](int slot) {
 #pragma unroll
     for (int st = 0; st < TILES; ++st) {
       const float x0 = xs[slot][st * 16 + r][g], x1 = xs[slot][st * 16 + r][4 + g];
+      bf16x8 h;
 #pragma unroll
       for (int ft = 0; ft < 2; ++ft) {
         f32x4 d = {0.f, 0.f, 0.f, 0.f};
         d = __builtin_amdgcn_mfma_f32_16x16x4f32(w1[ft][0], x0, d, 0, 0, 0);
         d = __builtin_amdgcn_mfma_f32_16x16x4f32(w1[ft][1], x1, d, 0, 0, 0);
-        bf16x4 h;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) h[i] = (__bf16)silu(d[i] + b1[ft][i]);
-        *reinterpret_cast<bf16x4*>(h1 + (st * 16 + r) * LDA + n_base + 16 * ft + 4 * g) = h;
+        for (int e = 0; e < 4; ++e) h[4 * ft + e] = (__bf16)silu(d[e] + b1[4 * ft + e]);
       }
+      *reinterpret_cast<bf16x8*>(h1 + (st * 16 + r) * LDA + f0) = h;
     }
   };
   // wave wv < TILES: 16 samples; lane groups 0, 1 and 2 hold the three parts of
@@ -640,61 +229,490 @@ mlp_infer_kernel(const MlpArgs a) {
   layer1(0);
   if (xm < M) xs[1][xm][xk] = x_next;
   __syncthreads();
-  infer_hidden<TILES>(w2, b2, h1, h2, n_base, lane);
+  infer_hidden<TILES>(w2, b2, h1, h2, f0, lane);
   __syncthreads();
   for (int i = 0; i < count; ++i) {
     x_next = load_x(i + 2);
-    infer_hidden<TILES>(w3, b3, h2, h3, n_base, lane);
+    infer_hidden<TILES>(w3, b3, h2, h3, f0, lane);
     if (i + 1 < count) layer1((i + 1) & 3);
     __syncthreads();
-    if (i + 1 < count) infer_hidden<TILES>(w2, b2, h1, h2, n_base, lane);
+    if (i + 1 < count) infer_hidden<TILES>(w2, b2, h1, h2, f0, lane);
     if (wv < TILES) layer4(i);
     if (xm < M) xs[(i + 2) & 3][xm][xk] = x_next;
     __syncthreads();
   }
 }
 
-// Weight gradients of the two 256×256 layers: gW[n][k] = Σ_b dzT[n][b] hT[k][b]
+// Training, forward half.  The workgroups, waves and weights in registers are
+// those of inference; the rows of a wave's two weight tiles are interleaved so
+// that a lane ends up with eight consecutive features of one sample (f0 ..
+// f0 + 7): one 16-byte store to LDS and to HBM (sample-major, as the weight
+// gradients read them) per 16 samples.  silu'(z2) goes to HBM in the order the
+// backward half's lanes read it, silu'(z3) stays in registers until the tile's
+// dL/dy is there, one barrier later; h3 is kept that long for the W4 gradient.
+// The b3, W4 and b4 gradients and the loss are summed over the workgroup's tiles
+// (at most kTrainTiles, which bounds the length of the sums).  What bounds it is
+// the vector units: 9200 of the 11600 cycles that a tile takes on each SIMD.
+// Tiles of 64 samples need more than the 256 registers a lane has (536 B of
+// scratch, 97 us against 57).  Both halves, 65536 samples: 146 us in one kernel
+// that read four weight matrices from L2 for every tile -> 98; 1000 samples: 54 ->
+// 22.
+constexpr int kTrainTile = 32, kTrainTiles = 16;
+
+// Four rows (p, p + ld, ..) of 16 columns, transposed on the way out of LDS: the
+// lanes of a 16-lane group address the rows' four-element pieces in order, and
+// each gets its column's four elements.
+typedef short i16x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) i16x4 lds_i16x4;
+__device__ __forceinline__ bf16x4 read_columns(const __bf16* m, int ld, int row, int col, int lane) {
+  const int t = lane & 15;
+  const __bf16* p = m + (row + (t >> 2)) * ld + col + 4 * (t & 3);
+  return __builtin_bit_cast(bf16x4, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)p));
+}
+// A matrix operand whose k runs down the rows: rows row + 8 g .. + 7 of column
+// col + r for lane r + 16 g.
+__device__ __forceinline__ bf16x8 read_operand(const __bf16* m, int ld, int row, int col, int lane) {
+  const int g = lane >> 4;
+  const bf16x4 lo = read_columns(m, ld, row + 8 * g, col, lane);
+  const bf16x4 hi = read_columns(m, ld, row + 8 * g + 4, col, lane);
+  return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+}
+
+__global__ void __launch_bounds__(64 * kInferWaves) __attribute__((amdgpu_waves_per_eu(2, 2)))
+mlp_train_forward_kernel(const MlpArgs a) {
+  constexpr int M = kTrainTile, TILES = M / 16, XS = kMlpMaxIn + 1, LDY = M + 8;
+  __shared__ __align__(16) __bf16 h1[M * LDA], h2[M * LDA], h3[2][M * LDA], w4[16 * LDA];
+  __shared__ __align__(16) __bf16 yp[16 * LDY];        // dL/dy in three parts, [4 part + j][sample]
+  __shared__ __align__(16) float ys[M][4], ts[M][4], w4f[4 * W], bias[3][W];
+  __shared__ f32x4 gb3[2][64 * kInferWaves];           // dL/db3 of a lane's samples and features
+  __shared__ float xs[3][M][XS], sums[M][XS];          // sums: dL/dy and the loss of a lane's samples
+  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int r = lane & 15, g = lane >> 4, n_base = 32 * wv, f0 = n_base + 8 * g, nin = a.n_in;
+  const int64_t B = a.batch, tiles = (B + M - 1) / M;
+  const int count = (int)((tiles - blockIdx.x + gridDim.x - 1) / gridDim.x);
+  const float* P = a.params;
+  const int xm = tid / kMlpMaxIn, xk = tid % kMlpMaxIn;
+  auto first = [&](int i) { return ((int64_t)blockIdx.x + (int64_t)i * gridDim.x) * M; };
+  // the inputs (waves 0 to 3) and targets (0 and 1) of a tile, one value a thread;
+  // past the batch or the block's tiles some value of theirs, dropped by keep_x
+  auto rows_of = [&](int64_t m0) { return (int)min((int64_t)M, B - m0); };
+  auto load_x = [&](int i) {
+    const int64_t m0 = min(first(i), B - 1);
+    return a.x[m0 * nin + (unsigned)(min(xm, rows_of(m0) - 1) * nin + min(xk, nin - 1))];
+  };
+  auto keep_x = [&](int i, float v) {
+    if (wv < M * kMlpMaxIn / 64) xs[i % 3][xm][xk] = xk < nin && xm < B - first(i) ? v : 0.0f;
+  };
+  auto load_t = [&](int i) {
+    const int64_t m0 = min(first(i), B - 1);
+    return a.target[m0 * 4 + (unsigned)min(tid, 4 * rows_of(m0) - 1)];
+  };
+  // what the first layer needs ahead of the weights: loads arrive in order
+  const float x0 = load_x(0), x1 = load_x(1);
+  float w1[2][2];
+#pragma unroll
+  for (int ft = 0; ft < 2; ++ft)
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const float v = P[a.off.W1 + wave_row(n_base, ft, r) * nin + min(4 * q + g, nin - 1)];
+      w1[ft][q] = 4 * q + g < nin ? v : 0.0f;
+    }
+  const int b = min(tid, W - 1);
+  const float bias1 = P[a.off.b1 + b], bias2 = P[a.off.b2 + b], bias3 = P[a.off.b3 + b];
+  const bf16x8 w4_piece = *reinterpret_cast<const bf16x8*>(a.W4s + tid * 8);
+  const float w4_0 = P[a.off.W4 + tid], w4_1 = P[a.off.W4 + tid + 2 * W];
+  float b4[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+    b4[j] = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(
+                                          __builtin_bit_cast(int, P[a.off.b4 + j])));
+  __builtin_amdgcn_sched_barrier(0);
+  bf16x8 w2[2][8], w3[2][8];
+  load_weights(w2, a.W2b, wv, lane);
+  load_weights(w3, a.W3b, wv, lane);
+  __builtin_amdgcn_sched_barrier(0);
+  *reinterpret_cast<bf16x8*>(w4 + tid / 32 * LDA + tid % 32 * 8) = w4_piece;
+  w4f[tid] = w4_0;
+  w4f[tid + 2 * W] = w4_1;
+  for (int i = tid; i < 4 * LDY; i += 64 * kInferWaves) yp[12 * LDY + i] = (__bf16)0.0f;
+  gb3[0][tid] = gb3[1][tid] = f32x4{0.f, 0.f, 0.f, 0.f};
+  if (tid < M * 5) sums[tid / 5][tid % 5] = 0.0f;
+  if (tid < W) {
+    bias[0][tid] = bias1;
+    bias[1][tid] = bias2;
+    bias[2][tid] = bias3;
+  }
+  f32x4 gw4[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+  bf16x8 ds3[TILES];
+
+  // h of a lane's eight features of sample 16 st + r of a tile, zero past the batch
+  auto store_h = [&](bf16x8 h, __bf16* lds, int st, __bf16* out, int rows) {
+    i32x4 bits = __builtin_bit_cast(i32x4, h);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) bits[e] = st * 16 + r < rows ? bits[e] : 0;
+    h = __builtin_bit_cast(bf16x8, bits);
+    *reinterpret_cast<bf16x8*>(lds + (st * 16 + r) * LDA + f0) = h;
+    if (out) *reinterpret_cast<bf16x8*>(out + (unsigned)((st * 16 + r) * W + f0)) = h;
+  };
+  auto load_bias = [&](float (&b)[8], int l) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) b[e] = bias[l][f0 + e];
+  };
+  auto layer1 = [&](int i) {
+    const int slot = i % 3;
+    const int64_t m0 = first(i);
+    float b[8];
+    load_bias(b, 0);
+#pragma unroll
+    for (int st = 0; st < TILES; ++st) {
+      const float x0 = xs[slot][st * 16 + r][g], x1 = xs[slot][st * 16 + r][4 + g];
+      bf16x8 h;
+#pragma unroll
+      for (int ft = 0; ft < 2; ++ft) {
+        f32x4 d = {0.f, 0.f, 0.f, 0.f};
+        d = __builtin_amdgcn_mfma_f32_16x16x4f32(w1[ft][0], x0, d, 0, 0, 0);
+        d = __builtin_amdgcn_mfma_f32_16x16x4f32(w1[ft][1], x1, d, 0, 0, 0);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) h[4 * ft + e] = (__bf16)silu(d[e] + b[4 * ft + e]);
+      }
+      store_h(h, h1, st, a.h1 + m0 * W, rows_of(m0));
+    }
+  };
+  auto layer = [&](const bf16x8 (&w)[2][8], int l, const __bf16* in, __bf16* out,
+                   __bf16* out_global, int64_t m0, auto keep_ds) {
+    float b[8];
+    load_bias(b, l);
+#pragma unroll
+    for (int st = 0; st < TILES; ++st) {
+      f32x4 acc[2];
+      wave_gemm(w, in + (st * 16 + r) * LDA + 8 * g, acc);
+      bf16x8 h, ds;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const float z = acc[e >> 2][e & 3] + b[e], sg = sigmoid(z);
+        h[e] = (__bf16)(z * sg);
+        ds[e] = (__bf16)(sg * (1.0f + z * (1.0f - sg)));
+      }
+      store_h(h, out, st, out_global ? out_global + m0 * W : nullptr, rows_of(m0));
+      keep_ds(st, ds);
+    }
+  };
+  auto layer2 = [&](int i) {
+    __bf16* out = a.ds2 + first(i) * W;
+    layer(w2, 1, h1, h2, a.h2, first(i), [&](int st, bf16x8 ds) {
+      *reinterpret_cast<bf16x8*>(out + (unsigned)(((wv * TILES + st) * 64 + lane) * 8)) = ds;
+    });
+  };
+  // outputs, loss and dL/dy of a tile: wave wv < TILES takes 16 samples; lane
+  // groups 0, 1 and 2 hold the three parts of the four outputs, group 0 finishes
+  auto layer4 = [&](int i) {
+    const __bf16* row = h3[i & 1] + (wv * 16 + r) * LDA + 8 * g;
+    f32x4 y = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 2
+    for (int k = 0; k < 8; ++k)
+      y = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+          *reinterpret_cast<const bf16x8*>(w4 + r * LDA + 32 * k + 8 * g),
+          *reinterpret_cast<const bf16x8*>(row + 32 * k), y, 0, 0, 0);
+    const float* x = xs[i % 3][wv * 16 + r];
+    float u[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const float mid = __shfl(y[j], lane + 16, 64), lo = __shfl(y[j], lane + 32, 64);
+      const float yj = b4[j] + ((y[j] + mid) + lo);
+      float base = a.out_ref[j];
+#pragma unroll
+      for (int k = 0; k < kMlpMaxIn; ++k) base = fmaf(a.out_lin[j][k], x[k], base);
+      u[j] = fmaf(a.out_scale[j], yj, base);
+    }
+    const float inv = 1.0f / sqrtf(u[0] * u[0] + u[1] * u[1] + u[2] * u[2] + u[3] * u[3]);
+    const bool in = wv * 16 + r < B - first(i);
+    float q[4], dq[4], qd = 0.0f, l = 0.0f;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      q[j] = u[j] * inv;
+      const float d = q[j] - ts[wv * 16 + r][j];
+      l += d * d;
+      dq[j] = 2.0f * d * a.inv_loss_norm;
+      qd += q[j] * dq[j];
+    }
+    float* sum = sums[wv * 16 + r];
+    if (lane < 16) sum[4] += in ? l : 0.0f;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const float dy = in ? a.out_scale[j] * ((dq[j] - q[j] * qd) * inv) : 0.0f;
+      if (lane < 16) {
+        sum[j] += dy;
+        ys[wv * 16 + r][j] = dy;
+#pragma unroll
+        for (int part = 0; part < 3; ++part) yp[(4 * part + j) * LDY + wv * 16 + r] = split3(dy, part);
+      }
+    }
+  };
+  // dz3 = (dL/dy W4) ⊙ silu'(z3), its bias gradient before rounding, and the W4
+  // gradient dL/dyᵀ h3 of the wave's features
+  auto finish = [&](int i) {
+    const int64_t m0 = first(i);
+#pragma unroll
+    for (int half = 0; half < 2; ++half) {
+      f32x4 w[4], sum = gb3[half][tid];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) w[j] = *reinterpret_cast<const f32x4*>(w4f + j * W + f0 + 4 * half);
+#pragma unroll
+      for (int st = 0; st < TILES; ++st) {
+        const f32x4 y = *reinterpret_cast<const f32x4*>(ys[st * 16 + r]);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float dh = w[0][e] * y[0] + w[1][e] * y[1] + w[2][e] * y[2] + w[3][e] * y[3];
+          const float dz = dh * (float)ds3[st][4 * half + e];
+          sum[e] += dz;
+          ds3[st][4 * half + e] = (__bf16)dz;
+        }
+      }
+      gb3[half][tid] = sum;
+    }
+#pragma unroll
+    for (int st = 0; st < TILES; ++st)
+      *reinterpret_cast<bf16x8*>(a.dz3 + m0 * W + (unsigned)((st * 16 + r) * W + f0)) = ds3[st];
+#pragma unroll
+    for (int s0 = 0; s0 < M; s0 += 32) {
+      const bf16x8 y = *reinterpret_cast<const bf16x8*>(yp + r * LDY + s0 + 8 * g);
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+        gw4[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+            y, read_operand(h3[i & 1], LDA, s0, n_base + 16 * t, lane), gw4[t], 0, 0, 0);
+    }
+  };
+  keep_x(0, x0);
+  keep_x(1, x1);
+  __syncthreads();
+  float x_next = load_x(2), t_next = load_t(0);
+  layer1(0);
+  __syncthreads();
+  layer2(0);
+  __syncthreads();
+  // Loads and stores complete in order, so a value is loaded a whole tile ahead,
+  // and the last tile is apart: the waits then count past the stores between.
+  auto tile = [&](int i, auto more) {
+    layer(w3, 2, h2, h3[i & 1], nullptr, first(i), [&](int st, bf16x8 ds) { ds3[st] = ds; });
+    keep_x(i + 2, x_next);
+    if (wv < 4 * M / 64) ts[tid / 4][tid % 4] = t_next;
+    if (more.value) {
+      x_next = load_x(i + 3);
+      t_next = load_t(i + 1);
+      layer1(i + 1);
+    }
+    __syncthreads();
+    if (wv < TILES) layer4(i);
+    if (more.value) layer2(i + 1);
+    __syncthreads();
+    finish(i);
+  };
+  for (int i = 0; i + 1 < count; ++i) tile(i, std::true_type());
+  tile(count - 1, std::false_type());
+  const int64_t blk = blockIdx.x;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    float v = gb3[e >> 2][tid][e & 3];
+#pragma unroll
+    for (int off = 1; off < 16; off <<= 1) v += __shfl_xor(v, off, 64);
+    if (r == 0) a.gpart_b3[blk * W + f0 + e] = v;
+  }
+#pragma unroll
+  for (int t = 0; t < 2; ++t)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const float mid = __shfl(gw4[t][j], lane + 16, 64), lo = __shfl(gw4[t][j], lane + 32, 64);
+      if (lane < 16) a.gpart_W4[(blk * 4 + j) * W + n_base + 16 * t + r] = (gw4[t][j] + mid) + lo;
+    }
+  if (tid < 5) {
+    float v = 0.0f;
+    for (int m = 0; m < M; ++m) v += sums[m][tid];
+    if (tid < 4) a.gpart_b4[blk * 4 + tid] = v;
+    else         a.loss_part[blk] = v * a.inv_loss_norm;
+  }
+}
+
+// Training, backward half, with the rows of W3ᵀ and W2ᵀ in registers: dz2 =
+// (dz3 W3) ⊙ silu'(z2) and dz1 = (dz2 W2) ⊙ silu'(z1), z1 recomputed by the
+// forward half's products.  dz1 is only needed by the wave that forms it, for the
+// W1 and b1 gradients (fp32 matrix cores, samples taken four by four in the
+// order that the transposed read gives them).
+__global__ void __launch_bounds__(64 * kInferWaves) __attribute__((amdgpu_waves_per_eu(2, 2)))
+mlp_train_backward_kernel(const MlpArgs a) {
+  constexpr int M = kTrainTile, TILES = M / 16, XS = kMlpMaxIn + 1, NTH = 64 * kInferWaves, LD1 = 48;
+  constexpr int Q = M * W / 8 / NTH;       // 16-byte pieces of a tile per thread
+  __shared__ __align__(16) __bf16 d3[M * LDA], d2[M * LDA], d1[kInferWaves][M * LD1];
+  __shared__ float xs[2][M][XS];
+  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int r = lane & 15, g = lane >> 4, n_base = 32 * wv, f0 = n_base + 8 * g, nin = a.n_in;
+  const int64_t B = a.batch, tiles = (B + M - 1) / M;
+  const int count = (int)((tiles - blockIdx.x + gridDim.x - 1) / gridDim.x);
+  const float* P = a.params;
+  const int xm = tid / kMlpMaxIn, xk = tid % kMlpMaxIn;
+  auto first = [&](int i) { return ((int64_t)blockIdx.x + (int64_t)i * gridDim.x) * M; };
+  float x_next;
+  bf16x8 next[Q], ds2[TILES];
+  // (past the last tile: that one again, so that every wait counts the same loads)
+  auto load_tile = [&](int i) {
+    const int64_t m0 = first(min(i, count - 1));
+    const int rows = (int)min((int64_t)M, B - m0);
+    x_next = a.x[m0 * nin + (unsigned)(min(xm, rows - 1) * nin + min(xk, nin - 1))];
+#pragma unroll
+    for (int q = 0; q < Q; ++q)
+      next[q] = *reinterpret_cast<const bf16x8*>(a.dz3 + m0 * W + (unsigned)((tid + q * NTH) * 8));
+  };
+  auto store_tile = [&](int i) {
+    if (wv < M * kMlpMaxIn / 64)
+      xs[i & 1][xm][xk] = xk < nin && xm < B - first(i) ? x_next : 0.0f;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      const int c = tid + q * NTH;
+      *reinterpret_cast<bf16x8*>(d3 + c / (W / 8) * LDA + c % (W / 8) * 8) = next[q];
+    }
+  };
+  auto load_ds = [&](int i) {
+    const __bf16* src = a.ds2 + first(min(i, count - 1)) * W;
+#pragma unroll
+    for (int st = 0; st < TILES; ++st)
+      ds2[st] = *reinterpret_cast<const bf16x8*>(src + (unsigned)(((wv * TILES + st) * 64 + lane) * 8));
+  };
+  load_tile(0);
+  __builtin_amdgcn_sched_barrier(0);
+  bf16x8 w3[2][8], w2[2][8];
+  load_weights(w3, a.W3Tb, wv, lane);
+  load_ds(0);
+  load_weights(w2, a.W2Tb, wv, lane);
+  float b1[8], w1[2][2];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) b1[e] = P[a.off.b1 + f0 + e];
+#pragma unroll
+  for (int ft = 0; ft < 2; ++ft)
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const float v = P[a.off.W1 + wave_row(n_base, ft, r) * nin + min(4 * q + g, nin - 1)];
+      w1[ft][q] = 4 * q + g < nin ? v : 0.0f;
+    }
+  __builtin_amdgcn_sched_barrier(0);
+  float gb2[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  f32x4 gw1[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+  __bf16* const own = d1[wv];
+  // the W1 and b1 gradients of a tile whose dz1 the wave has left in LDS
+  auto grad1 = [&](int i) {
+    const float (*x)[XS] = xs[i & 1];
+#pragma unroll
+    for (int st = 0; st < TILES; ++st) {
+      bf16x4 v[2];
+#pragma unroll
+      for (int ft = 0; ft < 2; ++ft) v[ft] = read_columns(own, LD1, 16 * st + 4 * g, 16 * ft, lane);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float xv = x[16 * st + 4 * g + e][min(r, nin - 1)];
+        const float in = r < nin ? xv : r == nin ? 1.0f : 0.0f;
+#pragma unroll
+        for (int ft = 0; ft < 2; ++ft)
+          gw1[ft] = __builtin_amdgcn_mfma_f32_16x16x4f32((float)v[ft][e], in, gw1[ft], 0, 0, 0);
+      }
+    }
+  };
+  store_tile(0);
+  __syncthreads();
+  for (int i = 0; i < count; ++i) {
+    const int64_t m0 = first(i);
+    load_tile(i + 1);
+    if (i > 0) grad1(i - 1);
+#pragma unroll
+    for (int st = 0; st < TILES; ++st) {
+      f32x4 acc[2];
+      wave_gemm(w3, d3 + (st * 16 + r) * LDA + 8 * g, acc);
+      bf16x8 v;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        v[e] = (__bf16)(acc[e >> 2][e & 3] * (float)ds2[st][e]);
+        gb2[e] += (float)v[e];
+      }
+      *reinterpret_cast<bf16x8*>(d2 + (st * 16 + r) * LDA + f0) = v;
+      *reinterpret_cast<bf16x8*>(a.dz2 + m0 * W + (unsigned)((st * 16 + r) * W + f0)) = v;
+    }
+    __syncthreads();
+    load_ds(i + 1);
+    const float (*x)[XS] = xs[i & 1];
+#pragma unroll
+    for (int st = 0; st < TILES; ++st) {
+      f32x4 acc[2];
+      wave_gemm(w2, d2 + (st * 16 + r) * LDA + 8 * g, acc);
+      const float x0 = x[st * 16 + r][g], x1 = x[st * 16 + r][4 + g];
+      bf16x8 v;
+#pragma unroll
+      for (int ft = 0; ft < 2; ++ft) {
+        f32x4 z = {0.f, 0.f, 0.f, 0.f};
+        z = __builtin_amdgcn_mfma_f32_16x16x4f32(w1[ft][0], x0, z, 0, 0, 0);
+        z = __builtin_amdgcn_mfma_f32_16x16x4f32(w1[ft][1], x1, z, 0, 0, 0);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          v[4 * ft + e] = (__bf16)(acc[ft][e] * dsilu(z[e] + b1[4 * ft + e]));
+      }
+      *reinterpret_cast<bf16x8*>(own + (st * 16 + r) * LD1 + 8 * g) = v;
+    }
+    store_tile(i + 1);
+    __syncthreads();
+  }
+  grad1(count - 1);
+  const int64_t blk = blockIdx.x;
+#pragma unroll
+  for (int e = 0; e < 8; ++e)
+#pragma unroll
+    for (int off = 1; off < 16; off <<= 1) gb2[e] += __shfl_xor(gb2[e], off, 64);
+  if (r == 0)
+#pragma unroll
+    for (int e = 0; e < 8; ++e) a.gpart_b2[blk * W + f0 + e] = gb2[e];
+#pragma unroll
+  for (int ft = 0; ft < 2; ++ft)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int64_t n = n_base + 16 * ft + 4 * g + e;
+      if (r < nin) a.gpart_W1[(blk * W + n) * nin + r] = gw1[ft][e];
+      else if (r == nin) a.gpart_b1[blk * W + n] = gw1[ft][e];
+    }
+}
+
+// Weight gradients of the two 256×256 layers: gW[n][k] = Σ_b dz[b][n] h[b][k]
 // over one split (a contiguous range of samples).  A workgroup computes a
 // 128×128 tile of one split, each wave a 64×64 quarter of it; every 32-sample
-// step stages the tile's 128 rows of both operands in LDS (double-buffered,
-// rows padded to 40 elements so that the fragment reads hit distinct banks),
-// and the next step's global loads are in flight during the current step's
-// sixteen MFMAs.  The four tiles of a (layer, split) group read the same
-// operands, so the launch keeps a group on one XCD (workgroups are dealt to
-// the 8 XCDs in turn), where they share the XCD's L2.
-constexpr int kWgTile = 128, kWgRow = 40;
+// step stages the tile's 128 columns of both operands in LDS (double-buffered),
+// from where they are read transposed (rows padded to 288 B: the four row pieces
+// of a transposed read lie in different banks), and the next step's global loads
+// are in flight during the current step's sixteen MFMAs.  The four tiles of a
+// (layer, split) group read the same operands, so the launch keeps a group on
+// one XCD (workgroups are dealt to the 8 XCDs in turn), where they share the
+// XCD's L2.
+constexpr int kWgTile = 128, kWgRow = kWgTile + 16;
 __global__ void __launch_bounds__(NT) mlp_weight_grad_kernel(const MlpArgs a) {
-  __shared__ __align__(16) __bf16 As[2][kWgTile * kWgRow];
-  __shared__ __align__(16) __bf16 Bs[2][kWgTile * kWgRow];
+  __shared__ __align__(16) __bf16 As[2][32 * kWgRow];
+  __shared__ __align__(16) __bf16 Bs[2][32 * kWgRow];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int id = blockIdx.x, xcd = id % 8, slot = id / 8;
   const int group = xcd + 8 * (slot / 4), tile = slot % 4;
   const int which = group & 1, split = group >> 1;
-  const __bf16* dzT = which == 0 ? a.dzT2 : a.dzT3;
-  const __bf16* hT = which == 0 ? a.hT1 : a.hT2;
+  const __bf16* dz = which == 0 ? a.dz2 : a.dz3;
+  const __bf16* h = which == 0 ? a.h1 : a.h2;
   float* out = (which == 0 ? a.gpart_W2 : a.gpart_W3) + (size_t)split * W * W;
   const int n0 = (tile >> 1) * kWgTile, k0 = (tile & 1) * kWgTile;
   const int wn = (wv >> 1) * 64, wk = (wv & 1) * 64;
-  const int64_t ld = a.ld;
-  const int64_t bs = (int64_t)split * a.split_chunk, be = min(ld, bs + a.split_chunk);
+  const int64_t bs = (int64_t)split * a.split_chunk, be = min(a.ld, bs + a.split_chunk);
   const int nsteps = be > bs ? (int)((be - bs) / 32) : 0;
-  // staging: thread t moves 16 bytes of rows t/4 and 64 + t/4, chunk t%4
-  const int sr = tid >> 2, sc = (tid & 3) * 8;
-  const __bf16* ga0 = dzT + (size_t)(n0 + sr) * ld + bs + sc;
-  const __bf16* ga1 = dzT + (size_t)(n0 + 64 + sr) * ld + bs + sc;
-  const __bf16* gb0 = hT + (size_t)(k0 + sr) * ld + bs + sc;
-  const __bf16* gb1 = hT + (size_t)(k0 + 64 + sr) * ld + bs + sc;
-  const int so0 = sr * kWgRow + sc, so1 = (64 + sr) * kWgRow + sc;
-  const int r = lane & 15, kq = 8 * (lane >> 4);
+  // staging: thread t moves 16 bytes of samples t/16 and 16 + t/16, piece t%16
+  const int sr = tid >> 4, sc = (tid & 15) * 8;
+  const __bf16* ga = dz + (bs + sr) * W + n0 + sc;
+  const __bf16* gb = h + (bs + sr) * W + k0 + sc;
+  const int so0 = sr * kWgRow + sc, so1 = so0 + 16 * kWgRow;
   f32x4 acc[4][4];
   zero_acc(acc);
   bf16x8 xa0, xa1, xb0, xb1;
   if (nsteps > 0) {
-    xa0 = *reinterpret_cast<const bf16x8*>(ga0);
-    xa1 = *reinterpret_cast<const bf16x8*>(ga1);
-    xb0 = *reinterpret_cast<const bf16x8*>(gb0);
-    xb1 = *reinterpret_cast<const bf16x8*>(gb1);
+    xa0 = *reinterpret_cast<const bf16x8*>(ga);
+    xa1 = *reinterpret_cast<const bf16x8*>(ga + 16 * W);
+    xb0 = *reinterpret_cast<const bf16x8*>(gb);
+    xb1 = *reinterpret_cast<const bf16x8*>(gb + 16 * W);
     *reinterpret_cast<bf16x8*>(&As[0][so0]) = xa0;
     *reinterpret_cast<bf16x8*>(&As[0][so1]) = xa1;
     *reinterpret_cast<bf16x8*>(&Bs[0][so0]) = xb0;
@@ -705,17 +723,17 @@ __global__ void __launch_bounds__(NT) mlp_weight_grad_kernel(const MlpArgs a) {
     const int cur = st & 1;
     const bool more = st + 1 < nsteps;
     if (more) {
-      const int64_t off = (int64_t)(st + 1) * 32;
-      xa0 = *reinterpret_cast<const bf16x8*>(ga0 + off);
-      xa1 = *reinterpret_cast<const bf16x8*>(ga1 + off);
-      xb0 = *reinterpret_cast<const bf16x8*>(gb0 + off);
-      xb1 = *reinterpret_cast<const bf16x8*>(gb1 + off);
+      const int64_t off = (int64_t)(st + 1) * 32 * W;
+      xa0 = *reinterpret_cast<const bf16x8*>(ga + off);
+      xa1 = *reinterpret_cast<const bf16x8*>(ga + off + 16 * W);
+      xb0 = *reinterpret_cast<const bf16x8*>(gb + off);
+      xb1 = *reinterpret_cast<const bf16x8*>(gb + off + 16 * W);
     }
     bf16x8 av[4], bv[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      av[i] = *reinterpret_cast<const bf16x8*>(&As[cur][(wn + i * 16 + r) * kWgRow + kq]);
-      bv[i] = *reinterpret_cast<const bf16x8*>(&Bs[cur][(wk + i * 16 + r) * kWgRow + kq]);
+      av[i] = read_operand(As[cur], kWgRow, 0, wn + i * 16, lane);
+      bv[i] = read_operand(Bs[cur], kWgRow, 0, wk + i * 16, lane);
     }
 #pragma unroll
     for (int i = 0; i < 4; ++i)
@@ -807,12 +825,12 @@ __global__ void __launch_bounds__(256) adam_kernel(const MlpArgs a, float lr, fl
   a.params_rw[i] = p;
   if (i >= a.off.W2 && i < a.off.W2 + W * W) {
     const int64_t e = i - a.off.W2, n = e / W, k = e % W;
-    a.W2b_rw[n * W + k] = (__bf16)p;
-    a.W2Tb_rw[k * W + n] = (__bf16)p;
+    a.W2b_rw[weight_at((int)n, (int)k)] = (__bf16)p;
+    a.W2Tb_rw[weight_at((int)k, (int)n)] = (__bf16)p;
   } else if (i >= a.off.W3 && i < a.off.W3 + W * W) {
     const int64_t e = i - a.off.W3, n = e / W, k = e % W;
-    a.W3b_rw[n * W + k] = (__bf16)p;
-    a.W3Tb_rw[k * W + n] = (__bf16)p;
+    a.W3b_rw[weight_at((int)n, (int)k)] = (__bf16)p;
+    a.W3Tb_rw[weight_at((int)k, (int)n)] = (__bf16)p;
   } else if (i >= a.off.W4 && i < a.off.W4 + 4 * W) {
     const int64_t e = i - a.off.W4, j = e / W, k = e % W;
 #pragma unroll
@@ -827,10 +845,11 @@ __global__ void __launch_bounds__(256) refresh_bf16_kernel(const MlpArgs a) {
   if (e >= W * W) return;
   const int64_t n = e / W, k = e % W;
   const float p2 = a.params[a.off.W2 + e], p3 = a.params[a.off.W3 + e];
-  a.W2b_rw[n * W + k] = (__bf16)p2;
-  a.W2Tb_rw[k * W + n] = (__bf16)p2;
-  a.W3b_rw[n * W + k] = (__bf16)p3;
-  a.W3Tb_rw[k * W + n] = (__bf16)p3;
+  const int at = weight_at((int)n, (int)k), at_t = weight_at((int)k, (int)n);
+  a.W2b_rw[at] = (__bf16)p2;
+  a.W2Tb_rw[at_t] = (__bf16)p2;
+  a.W3b_rw[at] = (__bf16)p3;
+  a.W3Tb_rw[at_t] = (__bf16)p3;
   if (e < 16 * W) {        // W4 in three parts, rows 12-15 zero
     const int64_t row = e / W;
     a.W4s_rw[e] = row < 12 ? split3(a.params[a.off.W4 + (row & 3) * W + k], (int)(row >> 2))
@@ -840,7 +859,14 @@ __global__ void __launch_bounds__(256) refresh_bf16_kernel(const MlpArgs a) {
 
 }  // namespace
 
-int mlp_tile() { return TM; }
+TrainShape mlp_train_shape(int64_t batch) {
+  const int64_t tiles = (batch + kTrainTile - 1) / kTrainTile;
+  return {kTrainTile, (int)std::min(tiles, mlp_train_rows(batch))};
+}
+int64_t mlp_train_rows(int64_t ld) {
+  const int64_t tiles = (ld + kTrainTile - 1) / kTrainTile, per = kMlpCus * kTrainTiles;
+  return kMlpCus * ((tiles + per - 1) / per);
+}
 
 hipError_t launch_mlp_infer(const MlpArgs& a, hipStream_t s) {
   // A workgroup per CU.  Tiles of 32 samples spread a small batch over more of
@@ -857,7 +883,11 @@ hipError_t launch_mlp_infer(const MlpArgs& a, hipStream_t s) {
 }
 
 hipError_t launch_mlp_train(const MlpArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL(mlp_train_kernel, dim3((unsigned)((a.batch + TM - 1) / TM)), dim3(NT), 0, s, a);
+  const TrainShape t = mlp_train_shape(a.batch);
+  if (a.ld % t.tile != 0 || a.ld < a.batch) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)t.blocks), block(64 * kInferWaves);
+  hipLaunchKernelGGL(mlp_train_forward_kernel, grid, block, 0, s, a);
+  hipLaunchKernelGGL(mlp_train_backward_kernel, grid, block, 0, s, a);
   return hipGetLastError();
 }
 

@@ -26,11 +26,11 @@ struct st_mlp {
   float* grad = nullptr;
   __bf16* wb = nullptr;             // W2, W3, W2ᵀ, W3ᵀ in bf16 (4 × 256²), then W4 split (16 × 256)
   // training scratch, sized for the largest batch seen
-  int64_t cap_ld = 0;
+  int64_t cap_ld = 0, cap_rows = 0;    // samples, rows of the partial gradients
   std::vector<void*> scratch;
-  __bf16 *hT[2] = {nullptr, nullptr};
-  __bf16 *dzT[2] = {nullptr, nullptr};
-  __bf16* dsT2 = nullptr;
+  __bf16 *h[2] = {nullptr, nullptr};
+  __bf16 *dz[2] = {nullptr, nullptr};
+  __bf16* ds2 = nullptr;
   float *loss_part = nullptr, *red_tmp = nullptr;
   float *gW1 = nullptr, *gb1 = nullptr, *gb2 = nullptr, *gb3 = nullptr, *gW4 = nullptr, *gb4 = nullptr;
   float *gW2 = nullptr, *gW3 = nullptr;
@@ -81,7 +81,7 @@ uint64_t splitmix64(uint64_t x) {
 void free_scratch(st_mlp* m) {
   for (void* p : m->scratch) (void)hipFree(p);
   m->scratch.clear();
-  m->cap_ld = 0;
+  m->cap_ld = m->cap_rows = 0;
 }
 
 template <class T>
@@ -95,11 +95,11 @@ st_status ensure_scratch(st_mlp* m, int64_t ld) {
   if (ld <= m->cap_ld) return ST_OK;
   free_scratch(m);
   const int64_t W = st::kMlpWidth;
-  const int64_t nb = ld / st::mlp_tile();
+  const int64_t nb = st::mlp_train_rows(ld);
   hipError_t e = hipSuccess;
-  for (int l = 0; l < 2 && e == hipSuccess; ++l) e = alloc(m, &m->hT[l], (size_t)(W * ld));
-  for (int l = 0; l < 2 && e == hipSuccess; ++l) e = alloc(m, &m->dzT[l], (size_t)(W * ld));
-  if (e == hipSuccess) e = alloc(m, &m->dsT2, (size_t)(W * ld));
+  for (int l = 0; l < 2 && e == hipSuccess; ++l) e = alloc(m, &m->h[l], (size_t)(W * ld));
+  for (int l = 0; l < 2 && e == hipSuccess; ++l) e = alloc(m, &m->dz[l], (size_t)(W * ld));
+  if (e == hipSuccess) e = alloc(m, &m->ds2, (size_t)(W * ld));
   if (e == hipSuccess) e = alloc(m, &m->loss_part, (size_t)nb);
   // multi-pass reduction buffers of the per-workgroup partials, one double
   // buffer per tensor (all reduced together)
@@ -123,6 +123,7 @@ st_status ensure_scratch(st_mlp* m, int64_t ld) {
     return fail(m, ST_ENOMEM, std::string("training scratch: ") + hipGetErrorString(e));
   }
   m->cap_ld = ld;
+  m->cap_rows = nb;
   return ST_OK;
 }
 
@@ -158,14 +159,15 @@ st::MlpArgs base_args(st_mlp* m) {
 
 // Forward, backward and the gradient reduction for one batch into m->grad.
 // With pend set, the reduction stops after its first pass and pend receives
-// what is left for the Adam kernel to add (the per-tile partials of a large
-// batch; the split-K weight partials are complete after one pass).
+// what is left for the Adam kernel to add (the per-workgroup partials of a
+// large batch; the split-K weight partials are complete after one pass).
 st_status compute_gradient(st_mlp* m, const float* x, const float* t, int64_t batch, float* d_loss,
                            hipStream_t s, st::AdamPending* pend = nullptr) {
-  const int64_t tile = st::mlp_tile();
-  const int64_t ld = (batch + tile - 1) / tile * tile;
+  const st::TrainShape shape = st::mlp_train_shape(batch);
+  const int64_t ld = (batch + shape.tile - 1) / shape.tile * shape.tile;
   st_status st = ensure_scratch(m, ld);
   if (st != ST_OK) return st;
+  if (shape.blocks > m->cap_rows) return fail(m, ST_EDEVICE, "training scratch has too few rows");
   st::MlpArgs a = base_args(m);
   a.batch = batch;
   a.ld = ld;
@@ -173,15 +175,15 @@ st_status compute_gradient(st_mlp* m, const float* x, const float* t, int64_t ba
   a.target = t;
   a.inv_loss_norm = 1.0f / (float)batch;
   a.loss_part = m->loss_part;
-  a.dsT2 = m->dsT2;
-  a.hT1 = m->hT[0]; a.hT2 = m->hT[1];
-  a.dzT2 = m->dzT[0]; a.dzT3 = m->dzT[1];
+  a.ds2 = m->ds2;
+  a.h1 = m->h[0]; a.h2 = m->h[1];
+  a.dz2 = m->dz[0]; a.dz3 = m->dz[1];
   a.gpart_W1 = m->gW1; a.gpart_b1 = m->gb1; a.gpart_b2 = m->gb2; a.gpart_b3 = m->gb3;
   a.gpart_W4 = m->gW4; a.gpart_b4 = m->gb4; a.gpart_W2 = m->gW2; a.gpart_W3 = m->gW3;
   const int splits = splits_of(ld);
   a.n_splits = splits;
   a.split_chunk = ((ld + splits - 1) / splits + 31) / 32 * 32;
-  const int nb = (int)(ld / tile);
+  const int nb = shape.blocks;
   const int64_t W = st::kMlpWidth;
   hipError_t e;
   if ((e = st::launch_mlp_train(a, s)) != hipSuccess) return hip_fail(m, e, "forward and backward");
@@ -392,7 +394,7 @@ st_status st_mlp_train_step(st_mlp* m, const float* d_x, const float* d_t, int64
   if (!(lr > 0.0f) || !std::isfinite(lr)) return fail(m, ST_EINVAL, "learning rate must be > 0");
   DeviceGuard g(m->device);
   hipStream_t s = (hipStream_t)stream;
-  // the reduction's last pass (the per-tile partials of a large batch) runs
+  // the reduction's last pass (the per-workgroup partials of a large batch) runs
   // inside the Adam kernel
   st::AdamPending pend;
   if ((st = compute_gradient(m, d_x, d_t, batch, d_loss, s, &pend)) != ST_OK) return st;

@@ -39,7 +39,7 @@ struct MlpArgs {
   int64_t n_params;
   const float* params;    // fp32 master weights (flat)
   float* params_rw;
-  const __bf16* W2b;      // bf16 [256][256] copies of W2, W3 and their transposes
+  const __bf16* W2b;      // bf16 copies of W2, W3 and their transposes, in operand order
   const __bf16* W3b;
   const __bf16* W2Tb;
   const __bf16* W3Tb;
@@ -57,12 +57,12 @@ struct MlpArgs {
   float out_lin[4][kMlpMaxIn];
   float inv_loss_norm;    // 1/batch
   float* loss_part;       // [blocks]
-  __bf16* hT1;            // [256][ld] activations, feature-major
-  __bf16* hT2;
-  __bf16* dsT2;           // [256][ld] silu'(z2) (bf16), from the forward half to the backward
-  __bf16* dzT2;           // [256][ld] gradients at the pre-activations
-  __bf16* dzT3;
-  float* gpart_W1;        // per-block partial gradients
+  __bf16* h1;             // [ld][256] activations (padded samples: zero)
+  __bf16* h2;
+  __bf16* ds2;            // silu'(z2) (bf16, ld x 256), in the order the backward half reads it
+  __bf16* dz2;            // [ld][256] gradients at the pre-activations
+  __bf16* dz3;
+  float* gpart_W1;        // per-workgroup partial gradients
   float* gpart_b1;
   float* gpart_b2;
   float* gpart_b3;
@@ -82,14 +82,21 @@ struct FeatureMap {
   double center[6], inv_scale[6], extra;
 };
 
-int mlp_tile();
+// How a training batch is split: samples per tile (the padding of the batch)
+// and workgroups (rows of the partial gradients); mlp_train_rows bounds the
+// workgroups of every batch of up to ld samples.
+struct TrainShape {
+  int tile, blocks;
+};
+TrainShape mlp_train_shape(int64_t batch);
+int64_t mlp_train_rows(int64_t ld);
 hipError_t launch_features(const double* z, int64_t n, const FeatureMap& f, int n_in, float* x,
                            hipStream_t s);
 hipError_t launch_targets(const double* q, int64_t n, const double* ref, float* t, hipStream_t s);
 // Inference of a.batch samples into q_out.
 hipError_t launch_mlp_infer(const MlpArgs& a, hipStream_t s);
-// The fused forward and backward pass of one batch (activations, dz2, dz3 and
-// the per-tile partials).
+// The forward and backward passes of one batch (activations, dz2, dz3 and the
+// per-workgroup partials).
 hipError_t launch_mlp_train(const MlpArgs& a, hipStream_t s);
 // dW2, dW3 split-K partials from the feature-major activations and gradients.
 hipError_t launch_mlp_weight_grad(const MlpArgs& a, hipStream_t s);
