@@ -157,12 +157,13 @@ st::MlpArgs base_args(st_mlp* m) {
   return a;
 }
 
-// Forward, backward and the gradient reduction for one batch into m->grad.
+// Forward, backward and the gradient reduction for one batch into grad
+// (n_params floats).
 // With pend set, the reduction stops after its first pass and pend receives
 // what is left for the Adam kernel to add (the per-workgroup partials of a
 // large batch; the split-K weight partials are complete after one pass).
-st_status compute_gradient(st_mlp* m, const float* x, const float* t, int64_t batch, float* d_loss,
-                           hipStream_t s, st::AdamPending* pend = nullptr) {
+st_status compute_gradient(st_mlp* m, const float* x, const float* t, int64_t batch, float* grad,
+                           float* d_loss, hipStream_t s, st::AdamPending* pend = nullptr) {
   const st::TrainShape shape = st::mlp_train_shape(batch);
   const int64_t ld = (batch + shape.tile - 1) / shape.tile * shape.tile;
   st_status st = ensure_scratch(m, ld);
@@ -191,10 +192,10 @@ st_status compute_gradient(st_mlp* m, const float* x, const float* t, int64_t ba
   const st::MlpOffsets& o = m->off;
   // every tensor's partials (and the loss) reduced together, one launch per pass
   st::SumSegment red[] = {
-      {m->gW1, W * m->n_in, nb, m->grad + o.W1}, {m->gb1, W, nb, m->grad + o.b1},
-      {m->gW2, W * W, splits, m->grad + o.W2},  {m->gb2, W, nb, m->grad + o.b2},
-      {m->gW3, W * W, splits, m->grad + o.W3},  {m->gb3, W, nb, m->grad + o.b3},
-      {m->gW4, 4 * W, nb, m->grad + o.W4},       {m->gb4, 4, nb, m->grad + o.b4},
+      {m->gW1, W * m->n_in, nb, grad + o.W1}, {m->gb1, W, nb, grad + o.b1},
+      {m->gW2, W * W, splits, grad + o.W2},  {m->gb2, W, nb, grad + o.b2},
+      {m->gW3, W * W, splits, grad + o.W3},  {m->gb3, W, nb, grad + o.b3},
+      {m->gW4, 4 * W, nb, grad + o.W4},       {m->gb4, 4, nb, grad + o.b4},
       {m->loss_part, 1, nb, d_loss}};
   const int nseg = d_loss ? 9 : 8;
   st::SumLeft left[9];
@@ -205,7 +206,7 @@ st_status compute_gradient(st_mlp* m, const float* x, const float* t, int64_t ba
     *pend = st::AdamPending{};
     for (int k = 0; k < 8; ++k)
       if (left[k].rows > 0)
-        pend->seg[pend->n++] = {left[k].src, red[k].out - m->grad, left[k].len, left[k].rows};
+        pend->seg[pend->n++] = {left[k].src, red[k].out - grad, left[k].len, left[k].rows};
     if (d_loss && left[8].rows > 0) {
       pend->loss_src = left[8].src;
       pend->loss_rows = left[8].rows;
@@ -380,11 +381,7 @@ st_status st_mlp_gradient(st_mlp* m, const float* d_x, const float* d_t, int64_t
   if (!d_grad) return fail(m, ST_EINVAL, "gradient output is NULL");
   DeviceGuard g(m->device);
   hipStream_t s = (hipStream_t)stream;
-  if ((st = compute_gradient(m, d_x, d_t, batch, d_loss, s)) != ST_OK) return st;
-  hipError_t e = hipMemcpyAsync(d_grad, m->grad, (size_t)m->n_params * sizeof(float),
-                                hipMemcpyDeviceToDevice, s);
-  if (e != hipSuccess) return hip_fail(m, e, "copy gradient");
-  return ST_OK;
+  return compute_gradient(m, d_x, d_t, batch, d_grad, d_loss, s);
 }
 
 st_status st_mlp_train_step(st_mlp* m, const float* d_x, const float* d_t, int64_t batch, float lr,
@@ -397,7 +394,7 @@ st_status st_mlp_train_step(st_mlp* m, const float* d_x, const float* d_t, int64
   // the reduction's last pass (the per-workgroup partials of a large batch) runs
   // inside the Adam kernel
   st::AdamPending pend;
-  if ((st = compute_gradient(m, d_x, d_t, batch, d_loss, s, &pend)) != ST_OK) return st;
+  if ((st = compute_gradient(m, d_x, d_t, batch, m->grad, d_loss, s, &pend)) != ST_OK) return st;
   m->step += 1;
   const float c1 = (float)(1.0 / (1.0 - std::pow((double)st::kAdamBeta1, (double)m->step)));
   const float c2 = (float)(1.0 / (1.0 - std::pow((double)st::kAdamBeta2, (double)m->step)));
