@@ -928,14 +928,11 @@ extern "C" st_status st_track_surrogate(st_ctx* c, st_mlp* m, int64_t turns, int
       for (int i = 0; i < 6; ++i) { a.feat_center[i] = center[i]; a.feat_inv_scale[i] = inv_scale[i]; }
       a.feat_extra = extra;
       a.n_lanes = n_net;
-      if (n_net > 0 && (e = st::launch_orbit(a, c->nt, c->ext, s)) != hipSuccess)
-        return hip_fail(c, e, "surrogate orbits");
-      if (n_net < n) {      // the particles that fall back, and the lost ones
-        a.lane0 = n_net;
-        a.n_lanes = n - n_net;
-        if ((e = st::launch_track(a, track_plan(c, a.n_lanes, false), s)) != hipSuccess)
-          return hip_fail(c, e, "surrogate turns");
-      }
+      st::TrackArgs f = a;  // the particles that fall back, and the lost ones
+      f.lane0 = n_net;
+      f.n_lanes = n - n_net;
+      if ((e = st::launch_surrogate_turns(a, f, track_plan(c, f.n_lanes, false), s)) != hipSuccess)
+        return hip_fail(c, e, "surrogate turns");
       if (n_net > 0) {
         const st_status ms = st_mlp_infer(m, c->d_feat, c->d_qnn, k * n_net, stream);
         if (ms != ST_OK) return fail(c, ms, std::string("network: ") + st_mlp_last_error(m));

@@ -1087,6 +1087,14 @@ __device__ __forceinline__ Quat element_pass(const Record& r, const ConstElem* t
   return q;
 }
 
+// A block's LDS: cold per-lane data, the spin (touched once per turn) and the
+// orbit at the current element's entrance (read back only on a loss).
+struct BlockShared {
+  double red[kBlock / 64][4];
+  double cold[8][kBlock];
+  double mk_slot[kMKWords][kBlock];
+};
+
 // EXT: the kernel also knows the drift-kick sector bend, the piece-wise
 // constant spin placements, solenoids and rectangular bends (kept out of the
 // other instantiations so that their register allocation is not shaped by code
@@ -1095,14 +1103,12 @@ __device__ __forceinline__ Quat element_pass(const Record& r, const ConstElem* t
 // a.feat_n lanes of the lane order: the orbit only, with the network's inputs
 // written at the start of each turn.
 template <int NT, bool MIXED, bool EXT, bool ORBIT>
-__device__ __forceinline__ void track_body(const TrackArgs a) {
-  __shared__ double red[kBlock / 64][4];
-  // Cold per-lane data in LDS: the spin (touched once per turn) and the
-  // orbit at the current element's entrance (read back only on a loss).
-  __shared__ double cold[8][kBlock];
-  __shared__ double mk_slot[kMKWords][kBlock];
+__device__ __forceinline__ void track_body(const TrackArgs& a, int block, BlockShared& sh) {
+  auto& red = sh.red;
+  auto& cold = sh.cold;
+  auto& mk_slot = sh.mk_slot;
   const int tid = threadIdx.x;
-  const int64_t g = a.lane0 + (int64_t)blockIdx.x * kBlock + tid;
+  const int64_t g = a.lane0 + (int64_t)block * kBlock + tid;
   const bool valid = g < a.lane0 + a.n_lanes;
   const int64_t j = (valid && a.perm) ? (int64_t)a.perm[g] : g;
   int32_t status = valid ? a.alive[j] : 0;
@@ -1217,7 +1223,7 @@ __device__ __forceinline__ void track_body(const TrackArgs a) {
         double s = 0.0;
         for (int k = 0; k < kBlock / 64; ++k) s += red[k][tid];
         const int rep = t / a.report_every - 1;
-        a.partials[((int64_t)rep * a.n_blocks + blockIdx.x) * 4 + tid] = s;
+        a.partials[((int64_t)rep * a.n_blocks + block) * 4 + tid] = s;
       }
       __syncthreads();
     }
@@ -1262,19 +1268,30 @@ struct TeamMeta {
   int32_t who;             // the wave that forms its quaternion
 };
 
+struct TeamShared {
+  double entry[2][kTeamBatch][4][kTeam];      // X, Px, Y, Py
+  double quat[2][kTeamBatch][4][kTeam];
+  double mk_slot[kTeamWaves][kMKWords][kTeam];
+  double cold_t[kTeam];
+  TeamMeta meta[2][kTeamBatch], qmeta[2][kTeamBatch];
+  int32_t filled[2], last[2];
+  uint64_t end_live[2];
+};
+
 template <int NT>
-__global__ void __launch_bounds__(kTeam * kTeamWaves) __attribute__((amdgpu_waves_per_eu(2)))
-team_kernel(const TrackArgs a) {
-  __shared__ double entry[2][kTeamBatch][4][kTeam];      // X, Px, Y, Py
-  __shared__ double quat[2][kTeamBatch][4][kTeam];
-  __shared__ double mk_slot[kTeamWaves][kMKWords][kTeam];
-  __shared__ double cold_t[kTeam];
-  __shared__ TeamMeta meta[2][kTeamBatch], qmeta[2][kTeamBatch];
-  __shared__ int32_t filled[2], last[2];
-  __shared__ uint64_t end_live[2];
+__device__ __forceinline__ void team_body(const TrackArgs& a, int block, TeamShared& sh) {
+  auto& entry = sh.entry;
+  auto& quat = sh.quat;
+  auto& mk_slot = sh.mk_slot;
+  auto& cold_t = sh.cold_t;
+  auto& meta = sh.meta;
+  auto& qmeta = sh.qmeta;
+  auto& filled = sh.filled;
+  auto& last = sh.last;
+  auto& end_live = sh.end_live;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int64_t g = a.lane0 + (int64_t)blockIdx.x * kTeam + lane, n = a.n;
+  const int64_t g = a.lane0 + (int64_t)block * kTeam + lane, n = a.n;
   const bool valid = g < a.lane0 + a.n_lanes;
   const int64_t j = (valid && a.perm) ? (int64_t)a.perm[g] : g;
   const int32_t status0 = valid ? a.alive[j] : 0;
@@ -1441,7 +1458,7 @@ team_kernel(const TrackArgs a) {
           if (lane == c) mine = v[c];
         }
         const int rep = t / a.report_every - 1;
-        if (lane < 4) a.partials[((int64_t)rep * a.n_blocks + blockIdx.x) * 4 + lane] = mine;
+        if (lane < 4) a.partials[((int64_t)rep * a.n_blocks + block) * 4 + lane] = mine;
       }
       was_live = live;
     }
@@ -1459,7 +1476,8 @@ template <int NT, bool MIXED, bool EXT>
 __global__ void __launch_bounds__(kBlock)
 __attribute__((amdgpu_waves_per_eu((MIXED || EXT) ? ST_WAVES_PER_EU_WIDE : ST_WAVES_PER_EU)))
 track_kernel(const TrackArgs a) {
-  track_body<NT, MIXED, EXT, false>(a);
+  __shared__ BlockShared sh;
+  track_body<NT, MIXED, EXT, false>(a, blockIdx.x, sh);
 }
 
 // Without the spin arithmetic the orbit push fits 128 registers, so four waves
@@ -1469,7 +1487,35 @@ template <int NT, bool EXT>
 __global__ void __launch_bounds__(kBlock)
 __attribute__((amdgpu_waves_per_eu(EXT ? 2 : ST_WAVES_PER_EU_ORBIT)))
 orbit_kernel(const TrackArgs a) {
-  track_body<NT, false, EXT, true>(a);
+  __shared__ BlockShared sh;
+  track_body<NT, false, EXT, true>(a, blockIdx.x, sh);
+}
+
+template <int NT>
+__global__ void __launch_bounds__(kTeam * kTeamWaves) __attribute__((amdgpu_waves_per_eu(2)))
+team_kernel(const TrackArgs a) {
+  __shared__ TeamShared sh;
+  team_body<NT>(a, blockIdx.x, sh);
+}
+
+// Surrogate tracking, the turns between two audits: the fallback particles in
+// teams and the orbits of those on the network side by side, on disjoint lanes.
+// Each alone is bound by its chain, not by the chip: nine turns of 52000 orbits and
+// 13600 fallback particles took 6.0 and 7.6 ms one after the other.  65536
+// particles over 20 turns: 48.0 -> 38.5 ms.
+template <int NT>
+__global__ void __launch_bounds__(kTeam * kTeamWaves) __attribute__((amdgpu_waves_per_eu(2)))
+surrogate_kernel(const TrackArgs fallback, const TrackArgs orbit) {
+  static_assert(kTeam * kTeamWaves == kBlock);
+  __shared__ union {
+    TeamShared team;
+    BlockShared block;
+  } sh;
+  const int block = blockIdx.x;
+  if (block < fallback.n_blocks)
+    team_body<NT>(fallback, block, sh.team);
+  else
+    track_body<5, false, false, true>(orbit, block - fallback.n_blocks, sh.block);
 }
 
 // Deterministic second pass of the polarization reduction: one block per
@@ -1543,6 +1589,28 @@ hipError_t launch_orbit(const TrackArgs& a, int nt, bool ext, hipStream_t stream
     case 9:  hipLaunchKernelGGL((orbit_kernel<9, true>), grid, block, 0, stream, a); break;
     case 12: hipLaunchKernelGGL((orbit_kernel<12, true>), grid, block, 0, stream, a); break;
     default: hipLaunchKernelGGL((orbit_kernel<16, true>), grid, block, 0, stream, a); break;
+  }
+  return hipGetLastError();
+}
+
+hipError_t launch_surrogate_turns(TrackArgs orbit, TrackArgs fallback, const TrackPlan& plan,
+                                  hipStream_t stream) {
+  if (!plan.team || orbit.n_lanes > kBesideLanes || orbit.n_lanes <= 0 || fallback.n_lanes <= 0) {
+    hipError_t e = hipSuccess;
+    if (orbit.n_lanes > 0) e = launch_orbit(orbit, plan.nt, plan.ext, stream);
+    if (e == hipSuccess && fallback.n_lanes > 0) e = launch_track(fallback, plan, stream);
+    return e;
+  }
+  fallback.n_blocks = (int32_t)((fallback.n_lanes + kTeam - 1) / kTeam);
+  orbit.n_blocks = (int32_t)((orbit.n_lanes + kBlock - 1) / kBlock);
+  const dim3 grid((unsigned)(fallback.n_blocks + orbit.n_blocks)), block(kBlock);
+  switch (plan.nt) {
+    case 5:  hipLaunchKernelGGL(surrogate_kernel<5>, grid, block, 0, stream, fallback, orbit); break;
+    case 6:  hipLaunchKernelGGL(surrogate_kernel<6>, grid, block, 0, stream, fallback, orbit); break;
+    case 8:  hipLaunchKernelGGL(surrogate_kernel<8>, grid, block, 0, stream, fallback, orbit); break;
+    case 9:  hipLaunchKernelGGL(surrogate_kernel<9>, grid, block, 0, stream, fallback, orbit); break;
+    case 12: hipLaunchKernelGGL(surrogate_kernel<12>, grid, block, 0, stream, fallback, orbit); break;
+    default: hipLaunchKernelGGL(surrogate_kernel<16>, grid, block, 0, stream, fallback, orbit); break;
   }
   return hipGetLastError();
 }

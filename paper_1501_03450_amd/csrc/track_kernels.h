@@ -32,9 +32,15 @@ constexpr int64_t kTeamLanes = 32768;
 // (the polarization partials have that many rows per report).
 hipError_t launch_track(TrackArgs a, const TrackPlan& plan, hipStream_t stream);
 
-// Surrogate tracking: the orbit only, for the a.feat_n particles on the
-// network (the first lanes of the lane order).
-hipError_t launch_orbit(const TrackArgs& a, int nt, bool ext, hipStream_t stream);
+// Surrogate tracking: the orbit only of the orbit.feat_n particles on the network
+// (the first lanes of the lane order), and the turns of the fallback ones.  Where
+// those are few enough for teams and the orbits for kBesideLanes, one launch runs
+// both beside each other: each is a chain that leaves SIMDs idle.
+hipError_t launch_surrogate_turns(TrackArgs orbit, TrackArgs fallback, const TrackPlan& plan,
+                                  hipStream_t stream);
+// Orbit lanes of one round in that launch, whose registers (the teams') leave two
+// waves per SIMD; the orbit kernel of its own has four.
+constexpr int64_t kBesideLanes = 131072;
 
 hipError_t launch_surrogate_spin(double* spin, const int32_t* alive, const int32_t* fallback,
                                  const float* qnn, int64_t n, hipStream_t s);
