@@ -496,7 +496,7 @@ st_status ensure_polarization(st_ctx* c, int64_t n_rep, int64_t nb) {
 // Whether `lanes` lanes run in teams of four waves per 64 (bit for bit the same
 // orbits and spins).
 st::TrackPlan track_plan(const st_ctx* c, int64_t lanes, bool mixed) {
-  return {c->nt, mixed, c->ext, !mixed && !c->ext && lanes <= st::kTeamLanes};
+  return {c->nt, mixed, c->ext, (c->ext || !mixed) && lanes <= st::kTeamLanes};
 }
 
 // The plan of a whole-bunch call with n_rep reports and its polarization rows

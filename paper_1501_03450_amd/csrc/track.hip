@@ -1090,9 +1090,9 @@ __device__ __forceinline__ Quat element_pass(const Record& r, const ConstElem* t
 // A block's LDS: cold per-lane data, the spin (touched once per turn) and the
 // orbit at the current element's entrance (read back only on a loss).
 struct BlockShared {
-  double red[kBlock / 64][4];
   double cold[8][kBlock];
   double mk_slot[kMKWords][kBlock];
+  double red[kBlock / 64][4];   // (last: the lanes' addresses start at 0; 4 to 8 % of an extended turn)
 };
 
 // EXT: the kernel also knows the drift-kick sector bend, the piece-wise
@@ -1257,6 +1257,8 @@ __device__ __forceinline__ void track_body(const TrackArgs& a, int block, BlockS
 // us a turn; 1024 on the small ring: 117 -> 69 us.  What bounds it now is wave 0:
 // a dependent double-precision FMA takes 7.6 cycles here where independent ones
 // issue every 4.6; seven waves to form quaternions instead of three gain nothing.
+// Extended elements gain as much: drift-kick bends in 8 slices, 1657 particles, 413
+// -> 296 us a turn; fourth-order quadrupoles 320 -> 213.
 constexpr int kTeam = 64;              // particles of a team
 constexpr int kTeamBatch = 8;          // elements of a batch
 constexpr int kTeamWaves = 4;
@@ -1278,7 +1280,7 @@ struct TeamShared {
   uint64_t end_live[2];
 };
 
-template <int NT>
+template <int NT, bool EXT>
 __device__ __forceinline__ void team_body(const TrackArgs& a, int block, TeamShared& sh) {
   auto& entry = sh.entry;
   auto& quat = sh.quat;
@@ -1329,7 +1331,7 @@ __device__ __forceinline__ void team_body(const TrackArgs& a, int block, TeamSha
           if (op != OP_NONE) {
             en[0][lane] = X; en[1][lane] = Px; en[2][lane] = Y; en[3][lane] = Py;
             cold_t[lane] = T;
-            if (live) (void)element_pass<NT, false, false, false>(r, tab, X, Px, Y, Py, T, p, a, &mkc);
+            if (live) (void)element_pass<NT, false, EXT, false>(r, tab, X, Px, Y, Py, T, p, a, &mkc);
           }
           const int32_t now = cur;
           r = load_record(rec + next);
@@ -1348,7 +1350,7 @@ __device__ __forceinline__ void team_body(const TrackArgs& a, int block, TeamSha
               status = -(1 + ie);
             }
             const uint64_t after = __ballot(live);
-            const int cost = op < OP_THICK ? 1 : op == OP_THICK ? 10 : op < OP_MKX ? 7 : 5;
+            const int cost = EXT && op == OP_EXT ? 10 : op < OP_THICK ? 1 : op == OP_THICK ? 10 : op < OP_MKX ? 7 : 5;
             int who = 1, least = load[1];       // the wave with the least to do
 #pragma unroll
             for (int w = 2; w < kTeamWaves; ++w) {
@@ -1431,7 +1433,7 @@ __device__ __forceinline__ void team_body(const TrackArgs& a, int block, TeamSha
         if ((m.live >> lane) & 1) {
           double X = entry[b][k][0][lane], Px = entry[b][k][1][lane];
           double Y = entry[b][k][2][lane], Py = entry[b][k][3][lane], T = 0.0;
-          q = element_pass<NT, false, false, false>(r, tab, X, Px, Y, Py, T, p, a, &mkc);
+          q = element_pass<NT, false, EXT, false>(r, tab, X, Px, Y, Py, T, p, a, &mkc);
         }
         quat[b][k][0][lane] = q.w; quat[b][k][1][lane] = q.x;
         quat[b][k][2][lane] = q.y; quat[b][k][3][lane] = q.z;
@@ -1491,11 +1493,11 @@ orbit_kernel(const TrackArgs a) {
   track_body<NT, false, EXT, true>(a, blockIdx.x, sh);
 }
 
-template <int NT>
+template <int NT, bool EXT>
 __global__ void __launch_bounds__(kTeam * kTeamWaves) __attribute__((amdgpu_waves_per_eu(2)))
 team_kernel(const TrackArgs a) {
   __shared__ TeamShared sh;
-  team_body<NT>(a, blockIdx.x, sh);
+  team_body<NT, EXT>(a, blockIdx.x, sh);
 }
 
 // Surrogate tracking, the turns between two audits: the fallback particles in
@@ -1513,7 +1515,7 @@ surrogate_kernel(const TrackArgs fallback, const TrackArgs orbit) {
   } sh;
   const int block = blockIdx.x;
   if (block < fallback.n_blocks)
-    team_body<NT>(fallback, block, sh.team);
+    team_body<NT, false>(fallback, block, sh.team);
   else
     track_body<5, false, false, true>(orbit, block - fallback.n_blocks, sh.block);
 }
@@ -1563,15 +1565,16 @@ hipError_t launch_nt(const TrackArgs& a, int nt, hipStream_t stream) {
   return hipGetLastError();
 }
 
+template <bool EXT>
 hipError_t launch_team(const TrackArgs& a, int nt, hipStream_t stream) {
   const dim3 grid((unsigned)a.n_blocks), block(kTeam * kTeamWaves);
   switch (nt) {
-    case 5:  hipLaunchKernelGGL(team_kernel<5>, grid, block, 0, stream, a); break;
-    case 6:  hipLaunchKernelGGL(team_kernel<6>, grid, block, 0, stream, a); break;
-    case 8:  hipLaunchKernelGGL(team_kernel<8>, grid, block, 0, stream, a); break;
-    case 9:  hipLaunchKernelGGL(team_kernel<9>, grid, block, 0, stream, a); break;
-    case 12: hipLaunchKernelGGL(team_kernel<12>, grid, block, 0, stream, a); break;
-    default: hipLaunchKernelGGL(team_kernel<16>, grid, block, 0, stream, a); break;
+    case 5:  hipLaunchKernelGGL((team_kernel<5, EXT>), grid, block, 0, stream, a); break;
+    case 6:  hipLaunchKernelGGL((team_kernel<6, EXT>), grid, block, 0, stream, a); break;
+    case 8:  hipLaunchKernelGGL((team_kernel<8, EXT>), grid, block, 0, stream, a); break;
+    case 9:  hipLaunchKernelGGL((team_kernel<9, EXT>), grid, block, 0, stream, a); break;
+    case 12: hipLaunchKernelGGL((team_kernel<12, EXT>), grid, block, 0, stream, a); break;
+    default: hipLaunchKernelGGL((team_kernel<16, EXT>), grid, block, 0, stream, a); break;
   }
   return hipGetLastError();
 }
@@ -1595,7 +1598,7 @@ hipError_t launch_orbit(const TrackArgs& a, int nt, bool ext, hipStream_t stream
 
 hipError_t launch_surrogate_turns(TrackArgs orbit, TrackArgs fallback, const TrackPlan& plan,
                                   hipStream_t stream) {
-  if (!plan.team || orbit.n_lanes > kBesideLanes || orbit.n_lanes <= 0 || fallback.n_lanes <= 0) {
+  if (!plan.team || plan.ext || orbit.n_lanes > kBesideLanes || orbit.n_lanes <= 0 || fallback.n_lanes <= 0) {
     hipError_t e = hipSuccess;
     if (orbit.n_lanes > 0) e = launch_orbit(orbit, plan.nt, plan.ext, stream);
     if (e == hipSuccess && fallback.n_lanes > 0) e = launch_track(fallback, plan, stream);
@@ -1619,9 +1622,10 @@ hipError_t launch_track(TrackArgs a, const TrackPlan& plan, hipStream_t stream) 
   const int per = plan.team ? kTeam : kBlock;
   a.n_blocks = (int32_t)((a.n_lanes + per - 1) / per);
   // the extended methods run in double precision only
-  if (plan.ext) return launch_nt<false, true>(a, plan.nt, stream);
+  if (plan.ext)
+    return plan.team ? launch_team<true>(a, plan.nt, stream) : launch_nt<false, true>(a, plan.nt, stream);
   if (plan.mixed) return launch_nt<true, false>(a, plan.nt, stream);
-  return plan.team ? launch_team(a, plan.nt, stream) : launch_nt<false, false>(a, plan.nt, stream);
+  return plan.team ? launch_team<false>(a, plan.nt, stream) : launch_nt<false, false>(a, plan.nt, stream);
 }
 
 hipError_t launch_reduce_polarization(const double* partials, int n_blocks, int n_reports,

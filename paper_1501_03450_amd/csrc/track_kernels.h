@@ -15,7 +15,7 @@ int team_size();
 // single-precision spin arithmetic in the elements flagged for it; ext: the
 // lattice uses drift-kick (TEAPOT) bends, piece-wise constant spin placements,
 // solenoids or rectangular bends (run in double precision); team: four waves
-// per 64 particles (neither mixed nor ext), the same results bit for bit.
+// per 64 particles (not in mixed precision), the same results bit for bit.
 struct TrackPlan {
   int nt;
   bool mixed, ext, team;
