@@ -302,16 +302,15 @@ HBM_PEAK_GBPS = 8000.0
 
 
 def train_bytes_per_sample(n_in):
-    """HBM bytes one training sample needs between the two step kernels: the
-    fused forward-backward kernel reads x and the target, writes the bf16
-    activations h1, h2 and the bf16 SiLU derivative of layer 2 (read back by
-    its own backward half; the layer-3 derivative stays in registers) and
-    writes the bf16 gradients at the pre-activations of layers 2 and 3; the
-    weight-gradient kernel reads h1, h2 and those two gradients (the split
-    partials of the weight gradients are per batch, not per sample, and not
-    counted)."""
+    """HBM bytes one training sample needs between the step's kernels: the
+    forward half reads x and the target and writes the bf16 activations h1, h2,
+    the bf16 SiLU derivative of layer 2 and the bf16 gradient at the
+    pre-activation of layer 3; the backward half reads x and the last two and
+    writes the gradient of layer 2; the weight-gradient kernel reads h1, h2 and
+    the two gradients (the split partials of the weight gradients are per batch,
+    not per sample, and not counted)."""
     x, t, row = 4 * n_in, 16, 2 * 256
-    train = x + t + 2 * row + row + row + 2 * row
+    train = (x + t + 4 * row) + (x + 3 * row)
     weight_grad = 4 * row
     return train + weight_grad
 
