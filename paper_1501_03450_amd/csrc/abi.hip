@@ -499,6 +499,16 @@ st::TrackPlan track_plan(const st_ctx* c, int64_t lanes, bool mixed) {
   return {c->nt, mixed, c->ext, (c->ext || !mixed) && lanes <= st::kTeamLanes};
 }
 
+// Surrogate bunches run side by side on many streams, where the teams' doubled
+// slices compete with the other bunches' work: sixteen bunches of 65536 with 25 to
+// 60 % of them falling back ran at 4.4e7 particle-turns/s with teams up to
+// kTeamLanes and at 6.7e7 in blocks; with 0.7 % 1.39e8 in teams and 1.22e8 in blocks.
+constexpr int64_t kSurrogateTeamLanes = 8192;
+st::TrackPlan surrogate_plan(const st_ctx* c, int64_t lanes) {
+  st::TrackPlan p = track_plan(c, lanes, false);
+  p.team = p.team && lanes <= kSurrogateTeamLanes;
+  return p;
+}
 // The plan of a whole-bunch call with n_rep reports and its polarization rows
 // per report.  A call whose rows per 64 particles would not fit the fixed
 // scratch array runs in blocks, whoever holds the rows, so that st_track and
@@ -931,7 +941,7 @@ extern "C" st_status st_track_surrogate(st_ctx* c, st_mlp* m, int64_t turns, int
       st::TrackArgs f = a;  // the particles that fall back, and the lost ones
       f.lane0 = n_net;
       f.n_lanes = n - n_net;
-      if ((e = st::launch_surrogate_turns(a, f, track_plan(c, f.n_lanes, false), s)) != hipSuccess)
+      if ((e = st::launch_surrogate_turns(a, f, surrogate_plan(c, f.n_lanes), s)) != hipSuccess)
         return hip_fail(c, e, "surrogate turns");
       if (n_net > 0) {
         const st_status ms = st_mlp_infer(m, c->d_feat, c->d_qnn, k * n_net, stream);
@@ -949,7 +959,7 @@ extern "C" st_status st_track_surrogate(st_ctx* c, st_mlp* m, int64_t turns, int
     st::TrackArgs a = track_args(c);
     a.turns = 1;
     a.qout = c->d_q64;
-    if ((e = st::launch_track(a, track_plan(c, n, false), s)) != hipSuccess)
+    if ((e = st::launch_track(a, surrogate_plan(c, n), s)) != hipSuccess)
       return hip_fail(c, e, "audit turn");
     if ((e = st::launch_audit(c->alive, d_fallback, c->d_failed, c->d_qnn, c->d_q64, n, threshold,
                               (int32_t)t, s)) != hipSuccess)
@@ -973,7 +983,7 @@ extern "C" st_status st_track_surrogate(st_ctx* c, st_mlp* m, int64_t turns, int
       r.turns = (int)(t - last_audit);
       r.report_every = 0;
       r.partials = nullptr;
-      if ((e = st::launch_track(r, track_plan(c, n_first, false), s)) != hipSuccess)
+      if ((e = st::launch_track(r, surrogate_plan(c, n_first), s)) != hipSuccess)
         return hip_fail(c, e, "replay");
     }
     if ((e = st::launch_replay_finish(c->d_failed, c->d_ralive, c->alive, n, s)) != hipSuccess)
