@@ -1504,7 +1504,7 @@ team_kernel(const TrackArgs a) {
 // teams and the orbits of those on the network side by side, on disjoint lanes.
 // Each alone is bound by its chain, not by the chip: nine turns of 52000 orbits and
 // 13600 fallback particles took 6.0 and 7.6 ms one after the other.  65536
-// particles over 20 turns: 48.0 -> 38.5 ms.
+// particles over 20 turns: 48.0 -> 38.5 ms with the teams taking all of them.
 template <int NT>
 __global__ void __launch_bounds__(kTeam * kTeamWaves) __attribute__((amdgpu_waves_per_eu(2)))
 surrogate_kernel(const TrackArgs fallback, const TrackArgs orbit) {
