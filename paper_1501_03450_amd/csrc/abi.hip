@@ -649,7 +649,10 @@ st_status st_load_lattice(st_ctx* c, const st_element* els, int64_t n, const st_
     const bool lone = uniq[k].kind == ST_DRIFT;
     const bool tail = lone || (i + 1 < n && uniq[elem[(size_t)i + 1]].kind == ST_DRIFT);
     const uint32_t kt = !tail ? UINT32_MAX : lone ? k : elem[(size_t)i + 1];
-    const uint64_t key = ((uint64_t)k << 32) | kt;
+    // The loss check behind a marker finds something only where the marker leads
+    // the lattice: anywhere else the state has just passed the same check.
+    const bool check = i == 0 && uniq[k].kind == ST_MARKER;
+    const uint64_t key = ((uint64_t)check << 63) | ((uint64_t)k << 32) | kt;
     const auto it = record.find(key);
     const int count = tail && !lone ? 2 : 1;
     if (it != record.end()) {
@@ -658,6 +661,10 @@ st_status st_load_lattice(st_ctx* c, const st_element* els, int64_t n, const st_
       st::Record r;
       std::memset(&r, 0, sizeof(r));
       derive_record(r, tab[k], uniq[k], *b, beta0, series_ymax(terms));
+      if (check) {                         // a rotation by nothing, for its check
+        r.op = st::OP_SNAKE;
+        r.s.qw = 1.0;
+      }
       r.elem = (int32_t)k;
       r.count = count;
       if (tail) {
