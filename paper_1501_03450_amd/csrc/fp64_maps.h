@@ -65,6 +65,7 @@ struct Particle {
   double Pt;
   double c3;       // P² - 1 = 2Pt/β0 + Pt², kept exactly (P² itself rounds it)
   double invP;
+  double invP_lo;  // 1/P - invP: what the rounding of invP left
   double dib;      // 1/β - 1/β0
   double invP2_, invbeta_, a1_, a2_;
   // beam constants (kernel arguments, uniform)
@@ -101,6 +102,9 @@ __device__ __forceinline__ Particle make_particle(double Pt, const TrackArgs& a)
   asm("" : "+v"(p.k38), "+v"(p.k18), "+v"(p.k14));
   p.invP = rsqrt_nr(p.P2());
   p.invP2_ = p.invP * p.invP;
+  // 1 - P² invP² from the exact c3 and the exact square of invP
+  const double sq_lo = fma(p.invP, p.invP, -p.invP2_);
+  p.invP_lo = 0.5 * p.invP * (fma(-p.c3, p.invP2_, 1.0 - p.invP2_) - sq_lo * p.P2());
   p.invbeta_ = (a.inv_beta0 + Pt) * p.invP;
   p.dib = -p.c1() * a.inv_beta0 * p.invP * rcp_nr(p.c2() + p.P());
   return p;
@@ -143,7 +147,9 @@ __device__ __forceinline__ void drift(double L, double& X, double Px, double& Y,
 }
 
 // 1/Ps and e = P/Ps - 1 from pp = Px² + Py², by the same series; a lane with
-// larger angles takes e = u/(ρ (1 + ρ)), ρ = Ps/P (from 1 - ρ² = u).
+// larger angles takes e = u/(ρ (1 + ρ)), ρ = Ps/P (from 1 - ρ² = u).  invP_lo
+// keeps the rounding of invP, which is the same in every slice and acts like an
+// error of the momentum, out of 1/Ps.
 struct PsInv {
   double r, e;
 };
@@ -152,7 +158,7 @@ __device__ __forceinline__ PsInv ps_inverse(double pp, const Particle& p) {
   const double u = pp * p.invP2();
   if (u <= kSeriesMaxU) {
     f.e = fma(u, 0.5, series_g(u));
-    f.r = fma(p.invP, f.e, p.invP);
+    f.r = p.invP + fma(p.invP, f.e, p.invP_lo);
   } else {
     const double ps2 = p.P2() - pp;
     f.r = rsqrt_nr(ps2);
@@ -217,7 +223,7 @@ __device__ __forceinline__ void teapot_drift(const TeapotParams& t, double& X, d
                                              double Py, double& T, const Particle& p) {
   const double pp = fma(Px, Px, Py * Py);
   const PsInv f = ps_inverse(pp, p);
-  const double ps = (p.P2() - pp) * f.r;
+  const double ps = fma(p.c3 - pp, f.r, f.r);     // Ps²/Ps, from the exact c3
   const double u = Px * f.r;
   const double inv_den = rcp_one_minus(u * t.tn);
   const double path = fma(X, t.tn, t.tn_h) * inv_den;
