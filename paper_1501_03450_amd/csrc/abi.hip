@@ -274,8 +274,11 @@ void derive_record(st::Record& r, const st::DevElem& d, const st_element& e, con
     r.b.mom = st::kFastMom - turn * (std::fabs(1.0 - e.eta) + 2e-5);
     r.b.turn_c = turn / 1.9;
     r.b.turn_x = turn * e.eta * std::fabs(h);
-    r.b.hw_eta_h = hw * e.eta * h;
-    r.b.hw_h = hw * h;
+    // Ω at the design is hw_h - (1 + G gamma) hw_eta_h: hw_h takes the rounding
+    // of hw_eta_h, which would add up over the bends
+    const long double hl = (long double)e.angle / e.L, hwl = 0.5L * e.L / e.n_slices;
+    r.b.hw_eta_h = (double)(hwl * e.eta * hl);
+    r.b.hw_h = (double)(hwl * hl - (hwl * e.eta * hl - r.b.hw_eta_h) * (1.0L + (long double)b.G * b.gamma0));
     r.op = d.K == 3 ? st::OP_BEND83 : st::OP_BEND82;
   } else {
     // growth through the defocusing plane at the lowest momentum, 1 % over

@@ -443,15 +443,20 @@ __device__ __forceinline__ Quat fast_bend(const HotBend& el, double& X, double& 
   const double cs = SPIN ? el.cs : el.w_cs, sn = SPIN ? el.sn : el.w_sn;
   const double omc = SPIN ? el.omc : el.w_omc;
   const double w = Py * Py * p.invP2();
-  const double invPa = fma(p.invP * w, fma(w, fma(w, 0.3125, p.k38), 0.5), p.invP);
+  const double dPa = p.invP * (w * fma(w, fma(w, 0.3125, p.k38), 0.5)), invPa = p.invP + dPa;
   const double Pa = fma(-Py, Py, p.P2()) * invPa;
   double v, F;
   fast_bend_edge(Px, invPa, p, v, F);
-  const double Px_in = Px, W_in = Pa + F;
-  double wme = (el.one_m_eta2 + ((p.c3 - Py * Py) - Px * Px)) * rcp_nr(W_in + el.eta);
+  const double Px_in = Px, F_in = F;
+  double wme = (el.one_m_eta2 + ((p.c3 - Py * Py) - Px * Px)) * rcp_nr((Pa + F) + el.eta);
   const double b = p.a2() * Py * p.invP2();                     // Ω without its path factor
-  const double kf = el.hw_eta_h * invPa;
-  const double ky = kf * fma(-b, Py, p.a1()), kx = kf * b, kz = el.hw_eta_h * b;
+  const double kf = el.hw_eta_h * invPa, ka = fma(-b, Py, p.a1());
+  const double ky = kf * ka, kx = kf * b, kz = el.hw_eta_h * b;
+  // ky turns the spin by Gγ times the bend, and is the same at every edge: what
+  // its factors' rounding left out joins hw_h (the path factor of ky is near 1)
+  const double invPa_lo = ((p.invP - invPa) + dPa) + p.invP_lo;
+  const double kf_lo = fma(el.hw_eta_h, invPa_lo, fma(el.hw_eta_h, invPa, -kf));
+  const double hw_h = el.hw_h - fma(kf_lo, ka, fma(kf, ka, -ky));
 #pragma unroll
   for (int j = 0; j <= (SPIN ? NS : 1); ++j) {
     if (j > 0) {
@@ -465,10 +470,11 @@ __device__ __forceinline__ Quat fast_bend(const HotBend& el, double& X, double& 
     }
     const double path = fma(el.h, X, 1.0);
     const double g = path * fma(v, fma(v, p.k38, 0.5), 1.0);     // path Pα/Ps
-    lev.fold(j, (g * kx) * Px, fma(-g, ky, el.hw_h), path * kz);
+    lev.fold(j, (g * kx) * Px, fma(-g, ky, hw_h), path * kz);
   }
-  // the slices' angle differences telescope; |sin| < 0.008 here
-  const double sd = fma(Px_in, Pa + F, -Px * W_in) * (invPa * invPa);
+  // the slices' angle differences telescope; |sin| < 0.008 here.  Ps = Pα + F:
+  // 1/Pα enters once, since its rounding is the same in every bend and T follows it
+  const double sd = ((Px_in - Px) + fma(Px_in, F * invPa, -Px * (F_in * invPa))) * invPa;
   const double s2 = sd * sd;
   const double D = fma(sd * s2, fma(s2, fma(s2, AC<3>::v, AC<2>::v), AC<1>::v), sd);
   Y = fma(Py, fma(D, el.inv_eta_h, el.s_eta), Y);

@@ -13,7 +13,7 @@ import pytest
 
 import oracle
 from test_parity_fp64 import gpu_run
-from workloads import Beam, gaussian_bunch
+from workloads import Beam, gaussian_bunch, rhic_like_ring, uniform_bend_ring
 from workloads.bunch import random_spins
 from workloads.lattice import sbend
 
@@ -23,8 +23,10 @@ BEAM = Beam(aperture=2.0)
 QUARTER_ULP = 2.0 ** -54
 
 
-def errors(ring, turns, n=2048):
+def errors(ring, turns, n=2048, only_energy=False):
     z, _, _ = gaussian_bunch(n, 7, BEAM)
+    if only_energy:
+        z[:5] = 0.0
     s = random_spins(n, 8, math.pi)
     g = gpu_run(ring, BEAM, z, s, turns=turns)
     o = oracle.track(ring, BEAM, z, s, turns=turns)
@@ -42,3 +44,23 @@ def test_drift_kick_bends_keep_the_momentum(spin, rows):
     rho = 10.0 / th
     assert rms[0] <= 2.0 * rho * QUARTER_ULP, rms[0]
     assert rms[4] <= math.pi * rho * QUARTER_ULP, rms[4]
+
+
+@pytest.mark.parametrize("ring,turns", [(uniform_bend_ring(), 4), ([sbend(9.45, 0.0238, 8, 4)] * 64, 2),
+                                        ([sbend(3.1, 0.077, 8, 3, eta=1.0003)] * 20, 2)])
+def test_bends_turn_the_spin_by_the_whole_angle(ring, turns):
+    # a factor off by d turns the spin by (1 + G gamma) times the bends' angle times
+    # d too far
+    _, spin = errors(ring, turns)
+    angle = turns * sum(e.angle for e in ring)
+    assert spin <= (1.0 + BEAM.G * BEAM.gamma0) * angle * QUARTER_ULP, spin
+
+
+def test_flight_time_of_the_rhic_scale_ring_off_momentum():
+    # Px changes by the momentum deviation times the angle in every bend, and T by
+    # rho times that: 2.5 m a turn for one sigma, on which a common factor's
+    # roundings act.  1.6 half ulps are two of them and the orbit's own noise
+    # (half of it); the square of a rounded factor is above.
+    rms, _ = errors(rhic_like_ring(), 2, only_energy=True)
+    rho = 9.45 / (2.0 * math.pi / 264.0)
+    assert rms[4] <= 1.6 * 2.0 ** -53 * 2 * 2.0 * math.pi * rho * 1e-3, rms[4]
