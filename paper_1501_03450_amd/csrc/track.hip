@@ -335,7 +335,7 @@ __device__ __forceinline__ Quat thick_element(const DevElem& el, double& X, doub
 // lane's conditions).  The kernel is bound by VALU issue (86 % of the issue
 // slots at two waves per SIMD), so what counts is the instructions per slice
 // edge.  With u = (Px² + Py²)/P² <= 2^-16 known for the whole element,
-//   P/Ps = 1 + u/2 + 3u²/8 (+ 5u³/16)   and, in a bend with Pα² = P² - Py²,
+//   P/Ps = 1 + u/2 + 3u²/8 + 5u³/16   and, in a bend with Pα² = P² - Py²,
 //   Ps - Pα = -(v Pα)(1/2 + v/8 + v²/16), v = Px²/Pα²,
 // take the place of the estimate, Newton steps and reciprocal of every edge;
 // Ω is formed already scaled by half the slice length, so that the quaternion
@@ -427,12 +427,15 @@ struct SpinLevels {
   }
 };
 
-// v = Px²/Pα² and F = Ps - Pα at a bend's edge.
-__device__ __forceinline__ void fast_bend_edge(double Px, double invPa, const Particle& p, double& v,
-                                               double& F) {
-  const double t = Px * Px * invPa;
-  v = t * invPa;
-  F = -t * fma(v, fma(v, 0.0625, p.k18), 0.5);
+// F = Ps - Pα and G = Pα/Ps - 1 at a bend's edge, v = Px²/Pα².  G needs its third
+// term: 5v³/16 is 1e-15 at the bound, a quarter of which a passage of a few rad
+// would carry into the spin.
+struct BendEdge {
+  double F, G;
+};
+__device__ __forceinline__ BendEdge fast_bend_edge(double Px, double invPa, const Particle& p) {
+  const double t = Px * Px * invPa, v = t * invPa;
+  return {-t * fma(v, fma(v, 0.0625, p.k18), 0.5), v * fma(v, fma(v, 0.3125, p.k38), 0.5)};
 }
 
 // Without spin the bend is crossed in one step.
@@ -445,10 +448,9 @@ __device__ __forceinline__ Quat fast_bend(const HotBend& el, double& X, double& 
   const double w = Py * Py * p.invP2();
   const double dPa = p.invP * (w * fma(w, fma(w, 0.3125, p.k38), 0.5)), invPa = p.invP + dPa;
   const double Pa = fma(-Py, Py, p.P2()) * invPa;
-  double v, F;
-  fast_bend_edge(Px, invPa, p, v, F);
-  const double Px_in = Px, F_in = F;
-  double wme = (el.one_m_eta2 + ((p.c3 - Py * Py) - Px * Px)) * rcp_nr((Pa + F) + el.eta);
+  BendEdge at = fast_bend_edge(Px, invPa, p);
+  const double Px_in = Px, F_in = at.F;
+  double wme = (el.one_m_eta2 + ((p.c3 - Py * Py) - Px * Px)) * rcp_nr((Pa + F_in) + el.eta);
   const double b = p.a2() * Py * p.invP2();                     // Ω without its path factor
   const double kf = el.hw_eta_h * invPa, ka = fma(-b, Py, p.a1());
   const double ky = kf * ka, kx = kf * b, kz = el.hw_eta_h * b;
@@ -460,21 +462,21 @@ __device__ __forceinline__ Quat fast_bend(const HotBend& el, double& X, double& 
 #pragma unroll
   for (int j = 0; j <= (SPIN ? NS : 1); ++j) {
     if (j > 0) {
-      const double A = fma(-el.eta_h, X, wme), F0 = F;
+      const double A = fma(-el.eta_h, X, wme), F0 = at.F;
       const double px1 = fma(Px, cs, A * sn);
-      fast_bend_edge(px1, invPa, p, v, F);
-      const double dW = F - F0;
+      at = fast_bend_edge(px1, invPa, p);
+      const double dW = at.F - F0;
       X = fma(X, cs, fma(wme, omc, fma(Px, sn, dW)) * el.inv_eta_h);
       wme += dW;
       Px = px1;
     }
     const double path = fma(el.h, X, 1.0);
-    const double g = path * fma(v, fma(v, p.k38, 0.5), 1.0);     // path Pα/Ps
+    const double g = fma(path, at.G, path);                      // path Pα/Ps
     lev.fold(j, (g * kx) * Px, fma(-g, ky, hw_h), path * kz);
   }
   // the slices' angle differences telescope; |sin| < 0.008 here.  Ps = Pα + F:
   // 1/Pα enters once, since its rounding is the same in every bend and T follows it
-  const double sd = ((Px_in - Px) + fma(Px_in, F * invPa, -Px * (F_in * invPa))) * invPa;
+  const double sd = ((Px_in - Px) + fma(Px_in, at.F * invPa, -Px * (F_in * invPa))) * invPa;
   const double s2 = sd * sd;
   const double D = fma(sd * s2, fma(s2, fma(s2, AC<3>::v, AC<2>::v), AC<1>::v), sd);
   Y = fma(Py, fma(D, el.inv_eta_h, el.s_eta), Y);

@@ -64,3 +64,16 @@ def test_flight_time_of_the_rhic_scale_ring_off_momentum():
     rms, _ = errors(rhic_like_ring(), 2, only_energy=True)
     rho = 9.45 / (2.0 * math.pi / 264.0)
     assert rms[4] <= 1.6 * 2.0 ** -53 * 2 * 2.0 * math.pi * rho * 1e-3, rms[4]
+
+
+def test_bends_at_the_edge_of_the_series_turn_the_spin_by_the_whole_angle():
+    # the same bound where Px is close to the short series' limit of 3.6 mrad: a
+    # series that stops a term early is off by 3e-16 of the angle there
+    ring, beam, n = [sbend(2.0, -0.05, 8, 4)], Beam(gamma0=250.0, aperture=2.0), 2000
+    rng = np.random.default_rng(5)
+    z = np.zeros((6, n))
+    z[1] = rng.choice([-1.0, 1.0], n) * rng.uniform(0.0032, 0.0035, n)
+    s = random_spins(n, 3, math.pi)
+    g, o = gpu_run(ring, beam, z, s), oracle.track(ring, beam, z, s)
+    spin = np.sqrt(np.mean((g["spin"] - o["spin"]) ** 2))
+    assert spin <= (1.0 + beam.G * beam.gamma0) * 0.05 * QUARTER_ULP, spin
