@@ -331,12 +331,13 @@ st::DevElem derive(const st_element& e, const st_beam& beam, double beta0) {
     t.h = e.angle / e.L;
     t.eta_h = e.eta * t.h;
     t.half = 0.5 * t.ds;
-    t.half_ib0 = t.half / beta0;
     const double a = t.h * t.half;
     t.c = std::cos(a);
     t.sn = std::sin(a);
     t.tn = t.sn / t.c;
     t.sec = 1.0 / t.c;
+    // Px swings by tan(a) in a slice, to which a particle's own 10 mrad are added
+    t.closed = (std::fabs(t.tn) + 0.01) * (std::fabs(t.tn) + 0.01) > st::kPsMaxU;
     // the small differences in extended precision: tan(a) - a and 1 - cos(a)
     const long double al = (long double)t.h * (long double)t.half;
     const long double tl = std::tan(al);

@@ -10,6 +10,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 namespace st {
 
 constexpr double inv_fact(int k) {
@@ -69,6 +71,35 @@ struct AsinSeries<0> {
   __device__ __forceinline__ static double eval(double) { return AC<4>::v; }
 };
 
+// What only a lane outside a series' range needs: `c` names those lanes, and the
+// wave jumps to `f` if there is one among them, which replaces the series' result
+// in these lanes alone.  Waves without one pass a compare and a branch that they do
+// not take; as if and else of the lanes, the same choice costs a wave the mask's
+// switching and a taken branch, about 90 cycles where a wave is alone on its SIMD.
+template <class F>
+__device__ __forceinline__ void rare(bool c, F f) {
+  if (__builtin_expect(__any(c), 0)) {
+    if (c) f();
+  }
+}
+
+// One step of a lane's state d...: `f` takes it with the short series (false_type)
+// and reports lanes beyond their range; these take the step again from its start
+// with the closed forms (true_type).  One test for a whole slice keeps the slice one
+// block of instructions, whose chains a wave alone on its SIMD can overlap.
+// `closed`, the same for the wave: the element's own slopes are beyond the range.
+template <class F, class... D>
+__device__ __forceinline__ void series_step(bool closed, F f, D&... d) {
+  const double in[sizeof...(D) + 1] = {d...};
+  bool beyond = closed;
+  if (!closed) f(std::false_type{}, beyond);
+  rare(beyond, [&] {
+    int i = 0;
+    ((d = in[i++]), ...);
+    f(std::true_type{}, beyond);
+  });
+}
+
 // Beyond the series range the argument is reduced by halving, which keeps
 // every lane on the same inline code (no calls, so no registers are spilled
 // around them): with t = x², evaluate the series at t/4^k and apply the
@@ -92,14 +123,18 @@ __device__ __forceinline__ void halving_series(double t, double tmax, double& c,
 
 // asin x = 2 asin(x / (sqrt 2 · sqrt(1 + sqrt(1 - x²)))) halves the argument.
 __device__ __forceinline__ double asin_small(double x) {
-  double scale = 1.0;
-  int k = 0;
-  while (!(fabs(x) <= kAsinPolyMax) && k < 8) {
-    x = x * rsqrt(2.0 * (1.0 + sqrt(1.0 - x * x)));
-    scale *= 2.0;
-    ++k;
-  }
-  return scale * (x * AsinSeries<>::eval(x * x));
+  double y = x * AsinSeries<>::eval(x * x);
+  rare(!(fabs(x) <= kAsinPolyMax), [&] {
+    double scale = 1.0, h = x;
+    int k = 0;
+    while (!(fabs(h) <= kAsinPolyMax) && k < 8) {
+      h = h * rsqrt(2.0 * (1.0 + sqrt(1.0 - h * h)));
+      scale *= 2.0;
+      ++k;
+    }
+    y = scale * (h * AsinSeries<>::eval(h * h));
+  });
+  return y;
 }
 
 // 1/x and 1/sqrt(x): hardware estimate refined by two Newton steps.
@@ -126,8 +161,9 @@ __device__ __forceinline__ double rsqrt_nr(double x) {
 // 35e⁴/128 stays below 3e-17 for |e| <= 1e-4; a larger |e| takes rsqrt_nr.
 __device__ __forceinline__ double rsqrt_near_one(double n2) {
   const double e = n2 - 1.0;
-  if (fabs(e) <= 1e-4) return fma(fma(fma(-0.3125, e, 0.375), e, -0.5), e, 1.0);
-  return rsqrt_nr(n2);
+  double r = fma(fma(fma(-0.3125, e, 0.375), e, -0.5), e, 1.0);
+  rare(!(fabs(e) <= 1e-4), [&] { r = rsqrt_nr(n2); });
+  return r;
 }
 
 // 1/sqrt(x) where it only scales a precession vector: one Newton step from
@@ -142,25 +178,25 @@ __device__ __forceinline__ double rsqrt_omega(double x) {
 
 // Quaternion terms of a rotation by θ = |ω|, ω = f Ω: with y = (θ/2)²,
 // cos(θ/2) and sin(θ/2)/(θ/2).  NT series terms cover y <= ymax.
-// Four terms cover y <= kShortY (y^4/8! < 2^-56): quadrupoles in a ring whose
-// bends need many terms.
+// SHORT: four terms where they cover y (y <= kShortY: y^4/8! < 2^-56), for
+// quadrupoles in a ring whose bends need many terms.
 constexpr double kShortY = 8.6e-4;
-template <int NT>
+template <int NT, bool SHORT = false>
 __device__ __forceinline__ void rot_half_series(double y, double ymax, double& c, double& s) {
-  if (NT > 6 && y <= kShortY) {
+  if constexpr (SHORT && NT > 6) {
     cos_sinc_series<4>(y, c, s);
-  } else if (y <= ymax) {
-    cos_sinc_series<NT>(y, c, s);
+    rare(!(y <= kShortY), [&] { rot_half_series<NT>(y, ymax, c, s); });
   } else {
-    halving_series<NT, false>(y, ymax, c, s);
+    cos_sinc_series<NT>(y, c, s);
+    rare(!(y <= ymax), [&] { halving_series<NT, false>(y, ymax, c, s); });
   }
 }
 
 // The same with the vector factor sin(θ/2)/θ.
-template <int NT>
+template <int NT, bool SHORT = false>
 __device__ __forceinline__ void rot_half_angle(double y, double ymax, double& c, double& sfac) {
   double s;
-  rot_half_series<NT>(y, ymax, c, s);
+  rot_half_series<NT, SHORT>(y, ymax, c, s);
   sfac = 0.5 * s;
 }
 

@@ -115,7 +115,6 @@ __device__ __forceinline__ Particle make_particle(double Pt, const TrackArgs& a)
 // u^4 leave less than 3e-19 (the first omitted one is 63/256 u^5); callers
 // take a closed form beyond.  Transverse momenta of the tracked bunches keep
 // u near 1e-8.
-constexpr double kSeriesMaxU = 1.0 / 4096.0;
 __device__ __forceinline__ double series_g(double u) {
   constexpr double c2 = 3.0 / 8.0, c3 = 5.0 / 16.0, c4 = 35.0 / 128.0;
   return (u * u) * fma(u, fma(u, c4, c3), c2);
@@ -126,56 +125,66 @@ __device__ __forceinline__ double series_g(double u) {
 // flight-time change L/β0 - L(1/β0 + Pt)/Ps is -L (1/β - 1/β0) - L e/β,
 // free of cancellation.  A lane with u > 2^-12 evaluates it as
 // L (c1 - Px² - Py²) / (β0 Ps (Ps + 1 + β0 Pt)).
+struct DriftTerms {
+  double r, t;                                     // 1/Ps and -ΔT/L
+};
+__device__ __forceinline__ DriftTerms drift_series(double u, const Particle& p) {
+  const double e = fma(u, 0.5, series_g(u));
+  return {fma(p.invP, e, p.invP), fma(p.invbeta(), e, p.dib)};
+}
+__device__ __forceinline__ DriftTerms drift_closed(double pp, const Particle& p, double inv_beta0) {
+  const double ps2 = p.P2() - pp, r = rsqrt_nr(ps2);
+  return {r, (pp - p.c1()) * r * inv_beta0 * rcp_nr(fma(ps2, r, p.c2()))};
+}
+__device__ __forceinline__ void drift_move(const DriftTerms& d, double L, double& X, double Px,
+                                           double& Y, double Py, double& T) {
+  X = fma(L * Px, d.r, X);
+  Y = fma(L * Py, d.r, Y);
+  T = fma(-L, d.t, T);
+}
 __device__ __forceinline__ void drift(double L, double& X, double Px, double& Y, double Py,
                                       double& T, const Particle& p, double inv_beta0) {
   const double pp = fma(Px, Px, Py * Py);
   const double u = pp * p.invP2();
-  if (u <= kSeriesMaxU) {
-    const double e = fma(u, 0.5, series_g(u));
-    const double r = fma(p.invP, e, p.invP);       // 1/Ps
-    X = fma(L * Px, r, X);
-    Y = fma(L * Py, r, Y);
-    T = fma(-L, fma(p.invbeta(), e, p.dib), T);
-  } else {
-    const double ps2 = p.P2() - pp;
-    const double r = rsqrt_nr(ps2);
-    const double ps = ps2 * r;
-    X = fma(L * Px, r, X);
-    Y = fma(L * Py, r, Y);
-    T = fma(L * (p.c1() - pp) * r * inv_beta0, rcp_nr(ps + p.c2()), T);
-  }
+  DriftTerms d = drift_series(u, p);
+  rare(!(u <= kSeriesMaxU), [&] { d = drift_closed(pp, p, inv_beta0); });
+  drift_move(d, L, X, Px, Y, Py, T);
+}
+// The same as a part of a series_step.
+template <bool CLOSED>
+__device__ __forceinline__ void drift_part(double L, double& X, double Px, double& Y, double Py,
+                                           double& T, const Particle& p, double inv_beta0,
+                                           bool& beyond) {
+  const double pp = fma(Px, Px, Py * Py);
+  const double u = pp * p.invP2();
+  if (!CLOSED) beyond |= !(u <= kSeriesMaxU);
+  drift_move(CLOSED ? drift_closed(pp, p, inv_beta0) : drift_series(u, p), L, X, Px, Y, Py, T);
 }
 
-// 1/Ps and e = P/Ps - 1 from pp = Px² + Py², by the same series; a lane with
+// 1/Ps and e = P/Ps - 1 from pp = Px² + Py², by the series with one more term, for u
+// <= 2^-9 (the first omitted one, 231/1024 u^6, is 1e-17: inside drift-kick bends Px
+// swings to the sine of half a slice); a lane with
 // larger angles takes e = u/(ρ (1 + ρ)), ρ = Ps/P (from 1 - ρ² = u).  invP_lo
 // keeps the rounding of invP, which is the same in every slice and acts like an
 // error of the momentum, out of 1/Ps.
 struct PsInv {
   double r, e;
 };
-__device__ __forceinline__ PsInv ps_inverse(double pp, const Particle& p) {
+template <bool CLOSED>
+__device__ __forceinline__ PsInv ps_part(double pp, const Particle& p, bool& beyond) {
   PsInv f;
   const double u = pp * p.invP2();
-  if (u <= kSeriesMaxU) {
-    f.e = fma(u, 0.5, series_g(u));
-    f.r = p.invP + fma(p.invP, f.e, p.invP_lo);
-  } else {
+  if constexpr (CLOSED) {
     const double ps2 = p.P2() - pp;
     f.r = rsqrt_nr(ps2);
     f.e = u * (p.P() * f.r) * rcp_nr(fma(ps2 * f.r, p.invP, 1.0));
+  } else {
+    constexpr double c2 = 3.0 / 8.0, c3 = 5.0 / 16.0, c4 = 35.0 / 128.0, c5 = 63.0 / 256.0;
+    f.e = fma(u, 0.5, (u * u) * fma(u, fma(u, fma(u, c5, c4), c3), c2));
+    f.r = p.invP + fma(p.invP, f.e, p.invP_lo);
+    beyond |= !(u <= kPsMaxU);
   }
   return f;
-}
-
-// 1/(1 - x): (1 + x)(1 + x²)(1 + x⁴) for |x| <= 2^-7 (the rest is x^8), the
-// refined hardware estimate beyond.
-__device__ __forceinline__ double rcp_one_minus(double x) {
-  if (fabs(x) <= 0.0078125) {
-    const double x2 = x * x;
-    const double f = fma(x, x2, x2) + x;      // (1 + x)(1 + x²) - 1
-    return 1.0 + fma(1.0 + f, x2 * x2, f);
-  }
-  return rcp_nr(1.0 - x);
 }
 
 // Precession vector of eq. t-bmt.so for a field b = (bx, by, 0) without
@@ -218,17 +227,26 @@ __device__ __forceinline__ void omega_bend(const BendParams& e, double X, double
 //   ΔT    = (ds/2)/β0 - (1/β0 + Pt) path/Ps           (the Pt/β0 term of
 //           eq. generalH adds (ds/2)/β0)
 //         = (1/β0) [(ds/2 - tan(a)/h) - tan(a)(u ds/2 + X)] / D
-//           - path [(1/β - 1/β0) + (P/Ps - 1)/β].
+//           - path [(1/β - 1/β0) + (P/Ps - 1)/β],
+//           the last term in closed form path (Ps² - (1 + β0 Pt)²) /
+//           (β0 Ps (Ps + 1 + β0 Pt)).
+// 1/D is (1 + x)(1 + x²)(1 + x⁴), x = u tan a, which leaves x^8: below 2^-72 where
+// u² <= 2^-9 and |tan a| <= 0.035 (elements beyond it take the closed forms).
+template <bool CLOSED>
 __device__ __forceinline__ void teapot_drift(const TeapotParams& t, double& X, double& Px, double& Y,
-                                             double Py, double& T, const Particle& p) {
+                                             double Py, double& T, const Particle& p, bool& beyond) {
   const double pp = fma(Px, Px, Py * Py);
-  const PsInv f = ps_inverse(pp, p);
+  const PsInv f = ps_part<CLOSED>(pp, p, beyond);
   const double ps = fma(p.c3 - pp, f.r, f.r);     // Ps²/Ps, from the exact c3
   const double u = Px * f.r;
-  const double inv_den = rcp_one_minus(u * t.tn);
+  const double x = u * t.tn, x2 = x * x, x3 = fma(x, x2, x2) + x;       // (1 + x)(1 + x²) - 1
+  const double inv_den = CLOSED ? rcp_nr(1.0 - x) : 1.0 + fma(1.0 + x3, x2 * x2, x3);
   const double path = fma(X, t.tn, t.tn_h) * inv_den;
   const double short_path = fma(-t.tn, fma(t.half, u, X), t.d0) * inv_den;   // ds/2 - path
-  T = fma(short_path, p.ib0, T) - path * fma(p.invbeta(), f.e, p.dib);
+  if (CLOSED)
+    T = fma(fma(path * (p.c1() - pp) * f.r, rcp_nr(ps + p.c2()), short_path), p.ib0, T);
+  else
+    T = fma(short_path, p.ib0, T) - path * fma(p.invbeta(), f.e, p.dib);
   X = fma(X, t.sec, fma(u, t.tn_h, t.omc_h)) * inv_den;
   Px = fma(Px, t.c, ps * t.sn);
   Y = fma(Py * f.r, path, Y);
@@ -261,7 +279,7 @@ __device__ __forceinline__ SolState sol_state(const SolenoidParams& sp, double X
   st.ps = ps2 * st.r;
   const double phi = sp.eta * st.r * sp.ds;
   double sfac;
-  rot_half_angle<NT>(phi * phi, ymax, st.c, sfac);   // cos φ and sin(φ)/(2φ)
+  rot_half_angle<NT, true>(phi * phi, ymax, st.c, sfac);   // cos φ and sin(φ)/(2φ)
   st.sn = 2.0 * phi * sfac;
   st.dT = sp.ds * (p.c1() - kk) * st.r * inv_beta0 * rcp_nr(st.ps + p.c2());
   return st;
@@ -364,11 +382,12 @@ __device__ __forceinline__ void rbend_body(const RbendParams& rb, double s, doub
   Px = Px1;
 }
 
+template <bool CLOSED>
 __device__ __forceinline__ void teapot_slice(const TeapotParams& t, double& X, double& Px, double& Y,
-                                             double Py, double& T, const Particle& p) {
-  teapot_drift(t, X, Px, Y, Py, T, p);
+                                             double Py, double& T, const Particle& p, bool& beyond) {
+  teapot_drift<CLOSED>(t, X, Px, Y, Py, T, p, beyond);
   teapot_kick(t, t.ds, X, Px);
-  teapot_drift(t, X, Px, Y, Py, T, p);
+  teapot_drift<CLOSED>(t, X, Px, Y, Py, T, p, beyond);
 }
 
 // Constants of one particle for the steps of a sector bend: the flight-time
@@ -396,11 +415,12 @@ __device__ __forceinline__ BendLane bend_lane(const BendParams& e, const BendSte
 // and the angle differences of the steps telescope, so a caller that steps
 // through a whole bend applies bend_yt once with the entrance and exit
 // values instead.
-template <bool YT = true>
+template <bool YT = true, bool CLOSED = true>
 __device__ __forceinline__ void bend_step(const BendParams& e, const BendStep& k,
                                           const BendLane& bl, double& X, double& Px, double Py,
                                           double& Y, double& T, double& W0, double& r0,
-                                          double& wme, double Pa2, double invPa2) {
+                                          double& wme, double Pa2, double invPa2,
+                                          bool* beyond = nullptr) {
   double A = fma(-e.eta_h, X, wme);
   double px1 = fma(Px, k.cs, A * k.sn);
   double ps2n = fma(-px1, px1, Pa2);
@@ -409,7 +429,9 @@ __device__ __forceinline__ void bend_step(const BendParams& e, const BendStep& k
   double dW = (Px - px1) * (Px + px1) * rcp_nr(W0 + W1);
   double X1 = fma(X, k.cs, fma(wme, k.omc, fma(Px, k.sn, dW)) * e.inv_eta_h);
   if constexpr (YT) {
-    double D = asin_small(fma(Px, W1, -px1 * W0) * invPa2);
+    const double sd = fma(Px, W1, -px1 * W0) * invPa2;
+    if (!CLOSED) *beyond |= !(fabs(sd) <= kAsinPolyMax);
+    const double D = CLOSED ? asin_small(sd) : sd * AsinSeries<>::eval(sd * sd);
     Y = fma(Py, fma(D, e.inv_eta_h, k.s_eta), Y);
     T += fma(-bl.ibh, D, bl.c0);
   }
@@ -454,13 +476,12 @@ __device__ __forceinline__ void mk_series(const QuadParams& e, const Particle& p
                                           double& sf, double& Ch, double& sd) {
   const double t = e.kabs_hds2 * p.invP;       // (κ s)²
   double Sc, Sh;
-  if (t <= 0.04) {
-    cos_sinc_series<7>(t, C, Sc);
-    cosh_sinhc_series<7>(t, Ch, Sh);
-  } else {
+  cos_sinc_series<7>(t, C, Sc);
+  cosh_sinhc_series<7>(t, Ch, Sh);
+  rare(!(t <= 0.04), [&] {
     halving_series<7, false>(t, 0.04, C, Sc);
     halving_series<7, true>(t, 0.04, Ch, Sh);
-  }
+  });
   sf = e.hds * Sc;
   sd = e.hds * Sh;
 }
@@ -495,22 +516,29 @@ __device__ __forceinline__ double mk_invariant(double kP, double pp, double xf, 
 // (series_g); a lane with larger angles takes the closed form
 // g = u²(2 + ρ)/(2ρ(1 + ρ)²), ρ = Ps/P.  tk collects g - u (u/2 + g)/4: the
 // kick's flight time -ds g/β with its share of the telescoped sum.
-__device__ __forceinline__ void mk_kick(double ds, double& X, double Px, double& Y, double Py,
-                                        double& tk, const Particle& p) {
-  const double pp = fma(Px, Px, Py * Py);
-  const double u = pp * p.invP2();
-  double g, d;
-  if (u <= kSeriesMaxU) {
-    g = series_g(u);
-    d = fma(u, 0.5, g) * p.invP;         // 1/Ps - 1/P
-  } else {
+template <bool CLOSED>
+__device__ __forceinline__ void kick_terms(double pp, double u, const Particle& p, double& g,
+                                           double& d, bool& beyond) {
+  if constexpr (CLOSED) {
     const double ps2 = p.P2() - pp;
     const double r = rsqrt_nr(ps2);
     d = r - p.invP;
     const double rho = ps2 * r * p.invP;
     const double opr = 1.0 + rho;
     g = u * u * (2.0 + rho) * (p.P() * r) * 0.5 * rcp_nr(opr * opr);
+  } else {
+    g = series_g(u);
+    d = fma(u, 0.5, g) * p.invP;         // 1/Ps - 1/P
+    beyond |= !(u <= kSeriesMaxU);
   }
+}
+template <bool CLOSED>
+__device__ __forceinline__ void mk_kick(double ds, double& X, double Px, double& Y, double Py,
+                                        double& tk, const Particle& p, bool& beyond) {
+  const double pp = fma(Px, Px, Py * Py);
+  const double u = pp * p.invP2();
+  double g, d;
+  kick_terms<CLOSED>(pp, u, p, g, d, beyond);
   X = fma(ds * Px, d, X);
   Y = fma(ds * Py, d, Y);
   tk = tk + fma(-0.25 * u, fma(u, 0.5, g), g);
@@ -579,22 +607,13 @@ __device__ __forceinline__ void mk_linear(const MKConst& m, double& xf, double& 
 // -ds/β g - ds (1/β - 1/β0), g = P/Ps - 1 - u/2 (series_g); a lane
 // with larger angles takes the closed form g = u²(2 + ρ)/(2ρ(1 + ρ)²),
 // ρ = Ps/P.
-__device__ __forceinline__ void mk_nonlinear(double ds, double& X, double Px, double& Y,
-                                             double Py, double& T, const Particle& p) {
+template <bool CLOSED>
+__device__ __forceinline__ void mk_nonlinear(double ds, double& X, double Px, double& Y, double Py,
+                                             double& T, const Particle& p, bool& beyond) {
   const double pp = fma(Px, Px, Py * Py);
   const double u = pp * p.invP2();
   double g, d;
-  if (u <= kSeriesMaxU) {
-    g = series_g(u);
-    d = fma(u, 0.5, g) * p.invP;         // 1/Ps - 1/P
-  } else {
-    const double ps2 = p.P2() - pp;
-    const double r = rsqrt_nr(ps2);
-    d = r - p.invP;
-    const double rho = ps2 * r * p.invP;
-    const double opr = 1.0 + rho;
-    g = u * u * (2.0 + rho) * (p.P() * r) * 0.5 * rcp_nr(opr * opr);
-  }
+  kick_terms<CLOSED>(pp, u, p, g, d, beyond);
   X = fma(ds * Px, d, X);
   Y = fma(ds * Py, d, Y);
   T = T - ds * fma(p.invbeta(), g, p.dib);

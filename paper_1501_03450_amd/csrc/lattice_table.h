@@ -28,6 +28,9 @@ enum : int32_t { P_EDGES = 0, P_KICK = 1, P_MIDPOINT = 2 };
 
 constexpr int kMaxRows = 4;   // Romberg tableau rows supported by the kernels
 
+// (Px² + Py²)/P² up to which P/Ps is a series: series_g, and ps_part
+constexpr double kSeriesMaxU = 1.0 / 4096.0, kPsMaxU = 1.0 / 512.0;
+
 // Per-kind parameters, precomputed on the host.
 struct BendStep {          // constants of one exact step of length s
   double cs, sn, omc;      // cos(h s), sin(h s), 1 - cos(h s)
@@ -53,7 +56,8 @@ struct Quad4Params {       // fourth-order quadrupole slice (M_DKD4, M_MK4)
 struct TeapotParams {       // drift-kick sector bend (§3.6)
   double ds;                // orbit slice length (kick length)
   double h, eta_h;          // curvature and dipole field ηh
-  double half, half_ib0;    // drift half ds/2 and (ds/2)/β0
+  double half;              // drift half ds/2
+  double closed;            // 1: Px leaves ps_part's series inside the slices
   double c, sn, tn, sec;    // cos, sin, tan, 1/cos of h ds/2
   double tn_h, omc_h;       // tan(h ds/2)/h and (1/cos(h ds/2) - 1)/h
   double d0;                // ds/2 - tan(h ds/2)/h

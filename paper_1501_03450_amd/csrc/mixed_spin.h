@@ -31,25 +31,24 @@ __device__ __forceinline__ QuatC qc_ident() { return {{1.f, 0.f, 0.f, 0.f}, {0.f
 // and s = sin(θ/2)/θ.  Five series terms hold single precision for y <= 1;
 // beyond, the double-precision series is used for the lane.
 __device__ __forceinline__ void rot_deviation_f32(double y, float& d, float& s) {
-  if (y <= 1.0) {
-    const float t = (float)y;
-    // d = Σ_{n>=1} (-1)^(n+1) t^n/(2n)!,  s = ½ Σ_{n>=0} (-t)^n/(2n+1)!
-    float dd = fmaf(t, -(float)IF<10>::v, (float)IF<8>::v);
-    dd = fmaf(t, dd, -(float)IF<6>::v);
-    dd = fmaf(t, dd, (float)IF<4>::v);
-    dd = fmaf(t, dd, -(float)IF<2>::v);
-    d = -t * dd;
-    float ss = fmaf(t, (float)IF<9>::v, -(float)IF<7>::v);
-    ss = fmaf(t, ss, (float)IF<5>::v);
-    ss = fmaf(t, ss, -(float)IF<3>::v);
-    ss = fmaf(t, ss, 1.0f);
-    s = 0.5f * ss;
-  } else {
+  const float t = (float)y;
+  // d = Σ_{n>=1} (-1)^(n+1) t^n/(2n)!,  s = ½ Σ_{n>=0} (-t)^n/(2n+1)!
+  float dd = fmaf(t, -(float)IF<10>::v, (float)IF<8>::v);
+  dd = fmaf(t, dd, -(float)IF<6>::v);
+  dd = fmaf(t, dd, (float)IF<4>::v);
+  dd = fmaf(t, dd, -(float)IF<2>::v);
+  d = -t * dd;
+  float ss = fmaf(t, (float)IF<9>::v, -(float)IF<7>::v);
+  ss = fmaf(t, ss, (float)IF<5>::v);
+  ss = fmaf(t, ss, -(float)IF<3>::v);
+  ss = fmaf(t, ss, 1.0f);
+  s = 0.5f * ss;
+  rare(!(y <= 1.0), [&] {
     double c, sf;
     halving_series<8, false>(y, 0.36, c, sf);
     d = (float)(1.0 - c);
     s = (float)(0.5 * sf);
-  }
+  });
 }
 
 // (1 - d, v)² = (1 - (2d - d² + |v|²), 2 (1 - d) v): twice the angle.

@@ -85,37 +85,37 @@ __device__ __forceinline__ Record load_record(const ConstRecord* p) {
 // element quaternion.
 // One second-order quadrupole step over the length of q: matrix-kick-matrix
 // (KIND 1 focusing in x, 3 focusing in y) or drift-kick-drift (KIND 2).
-template <int KIND>
+template <int KIND, bool CLOSED>
 __device__ __forceinline__ void quad_step2(const QuadParams& q, const MKConst& mc, double& X,
                                            double& Px, double& Y, double& Py, double& T,
-                                           const Particle& p, const TrackArgs& a) {
+                                           const Particle& p, const TrackArgs& a, bool& beyond) {
   if (KIND == 1) {
     mk_linear(mc, X, Px, Y, Py, T, p);
-    mk_nonlinear(q.ds, X, Px, Y, Py, T, p);
+    mk_nonlinear<CLOSED>(q.ds, X, Px, Y, Py, T, p, beyond);
     mk_linear(mc, X, Px, Y, Py, T, p);
   } else if (KIND == 3) {
     mk_linear(mc, Y, Py, X, Px, T, p);
-    mk_nonlinear(q.ds, X, Px, Y, Py, T, p);
+    mk_nonlinear<CLOSED>(q.ds, X, Px, Y, Py, T, p, beyond);
     mk_linear(mc, Y, Py, X, Px, T, p);
   } else {
-    drift(q.hds, X, Px, Y, Py, T, p, a.inv_beta0);
+    drift_part<CLOSED>(q.hds, X, Px, Y, Py, T, p, a.inv_beta0, beyond);
     Px = fma(-q.k1ds, X, Px);
     Py = fma(q.k1ds, Y, Py);
-    drift(q.hds, X, Px, Y, Py, T, p, a.inv_beta0);
+    drift_part<CLOSED>(q.hds, X, Px, Y, Py, T, p, a.inv_beta0, beyond);
   }
 }
 
 // Fourth-order quadrupole slice (orbit methods DKD4, MK4): the second-order
 // step over x1 ds, x0 ds and x1 ds (2 x1 + x0 = 1, 2 x1^3 + x0^3 = 0).  m1 and
 // m0 are the MK constants of the two step lengths.
-template <int KIND>
+template <int KIND, bool CLOSED>
 __device__ __forceinline__ void quad_slice4(const Quad4Params& q4, const MKConst& m1,
                                             const MKConst& m0, double& X, double& Px, double& Y,
                                             double& Py, double& T, const Particle& p,
-                                            const TrackArgs& a) {
-  quad_step2<KIND>(q4.s1, m1, X, Px, Y, Py, T, p, a);
-  quad_step2<KIND>(q4.s0, m0, X, Px, Y, Py, T, p, a);
-  quad_step2<KIND>(q4.s1, m1, X, Px, Y, Py, T, p, a);
+                                            const TrackArgs& a, bool& beyond) {
+  quad_step2<KIND, CLOSED>(q4.s1, m1, X, Px, Y, Py, T, p, a, beyond);
+  quad_step2<KIND, CLOSED>(q4.s0, m0, X, Px, Y, Py, T, p, a, beyond);
+  quad_step2<KIND, CLOSED>(q4.s1, m1, X, Px, Y, Py, T, p, a, beyond);
 }
 
 // Matrix-kick constants of the last quadrupole a lane crossed, kept in the
@@ -152,12 +152,13 @@ __device__ __forceinline__ MKLin mk_cached(const QuadParams& q, const Particle& 
 
 // One matrix-kick slice, orbit only (KIND 1 focusing in x, 3 in y); tk
 // collects the kick's flight time (mk_flight).
-template <int KIND>
+template <int KIND, bool CLOSED>
 __device__ __forceinline__ void mk_slice(const QuadParams& q, const MKLin& m, double& X, double& Px,
-                                         double& Y, double& Py, double& tk, const Particle& p) {
+                                         double& Y, double& Py, double& tk, const Particle& p,
+                                         bool& beyond) {
   if (KIND == 1) mk_move(m, X, Px, Y, Py);
   else           mk_move(m, Y, Py, X, Px);
-  mk_kick(q.ds, X, Px, Y, Py, tk, p);
+  mk_kick<CLOSED>(q.ds, X, Px, Y, Py, tk, p, beyond);
   if (KIND == 1) mk_move(m, X, Px, Y, Py);
   else           mk_move(m, Y, Py, X, Px);
 }
@@ -175,6 +176,7 @@ __device__ __forceinline__ Quat thick_element(const DevElem& el, double& X, doub
                                               double& Py, double& T, const Particle& p,
                                               const TrackArgs& a, MKCache* mkc = nullptr) {
   static_assert(kMaxRows == 4, "the level products below are written out for four rows");
+  const bool all_closed = KIND == 4 && el.tp.closed != 0.0;
   static_assert(NS == 0 || (KS >= 0 && KS < kMaxRows && NS % (1 << KS) == 0),
                 "NS slices must be divisible by 2^KS");
   const int N = NS > 0 ? NS : el.nsl;
@@ -255,7 +257,8 @@ __device__ __forceinline__ Quat thick_element(const DevElem& el, double& X, doub
     } else {
       // half angle θ/2 = hw |Ω|: q = (cos θ/2, sin(θ/2)/(θ/2) hw Ω)
       double c, sc;
-      rot_half_series<NT>((end_edge ? el.hw2_end : el.hw2_in) * om2, a.ymax, c, sc);
+      rot_half_series<NT, KIND == 1 || KIND == 2 || KIND == 3>((end_edge ? el.hw2_end : el.hw2_in) * om2,
+                                                                  a.ymax, c, sc);
       const double g = sc * (end_edge ? el.hw_end : el.hw_in);
       Quat qb = {c, g * ox, g * oy, g * oz};
       Q0 = FIRST ? qb : qmul(qb, Q0);
@@ -286,16 +289,14 @@ __device__ __forceinline__ Quat thick_element(const DevElem& el, double& X, doub
         bend_step<false>(el.b, el.b.slice, BendLane{0.0, 0.0}, X, Px, Py, Y, T, W, r, wme, Pa2,
                          invPa2);
       } else {
-        if (KIND == 4) {
-          teapot_slice(el.tp, X, Px, Y, Py, T, p);
-        } else if (Y4) {
-          quad_slice4<KIND>(el.q4, mc, mc0, X, Px, Y, Py, T, p, a);
-        } else if constexpr (MK) {
-          mk_slice<KIND>(el.q, ml, X, Px, Y, Py, tk, p);
-          invariant(j == N ? 0.5 : 1.0);
-        } else {
-          quad_step2<KIND>(el.q, mc, X, Px, Y, Py, T, p, a);
-        }
+        series_step(all_closed, [&](auto closed, bool& beyond) {
+          constexpr bool CLOSED = decltype(closed)::value;
+          if constexpr (KIND == 4) teapot_slice<CLOSED>(el.tp, X, Px, Y, Py, T, p, beyond);
+          else if constexpr (Y4)   quad_slice4<KIND, CLOSED>(el.q4, mc, mc0, X, Px, Y, Py, T, p, a, beyond);
+          else if constexpr (MK)   mk_slice<KIND, CLOSED>(el.q, ml, X, Px, Y, Py, tk, p, beyond);
+          else                     quad_step2<KIND, CLOSED>(el.q, mc, X, Px, Y, Py, T, p, a, beyond);
+        }, X, Px, Y, Py, T, tk);
+        if constexpr (MK) invariant(j == N ? 0.5 : 1.0);
         ps2 = p.P2() - fma(Px, Px, Py * Py);
         r = rsqrt_omega(ps2);
       }
@@ -608,7 +609,10 @@ __device__ __forceinline__ void thick_orbit(const DevElem& el, double& X, double
   if constexpr (Y4) {
     MKConst m1, m0;
     if (KIND == 1 || KIND == 3) { m1 = mk_const(el.q4.s1, p); m0 = mk_const(el.q4.s0, p); }
-    for (int j = 0; j < el.nsl; ++j) quad_slice4<KIND>(el.q4, m1, m0, X, Px, Y, Py, T, p, a);
+    for (int j = 0; j < el.nsl; ++j)
+      series_step(false, [&](auto closed, bool& beyond) {
+        quad_slice4<KIND, decltype(closed)::value>(el.q4, m1, m0, X, Px, Y, Py, T, p, a, beyond);
+      }, X, Px, Y, Py, T);
     return;
   }
   if constexpr (KIND == 1 || KIND == 3) {
@@ -616,7 +620,10 @@ __device__ __forceinline__ void thick_orbit(const DevElem& el, double& X, double
     const double kP = fabs(el.q.k1) * p.P(), xp_in = fma(X, Px, Y * Py);
     double esum = 0.0, tk = 0.0;
     for (int j = 0; j <= el.nsl; ++j) {
-      if (j > 0) mk_slice<KIND>(el.q, ml, X, Px, Y, Py, tk, p);
+      if (j > 0)
+        series_step(false, [&](auto closed, bool& beyond) {
+          mk_slice<KIND, decltype(closed)::value>(el.q, ml, X, Px, Y, Py, tk, p, beyond);
+        }, X, Px, Y, Py, tk);
       const double pp = fma(Px, Px, Py * Py);
       esum = fma(j == 0 || j == el.nsl ? 0.5 : 1.0,
                  KIND == 1 ? mk_invariant(kP, pp, X, Y) : mk_invariant(kP, pp, Y, X), esum);
@@ -624,17 +631,19 @@ __device__ __forceinline__ void thick_orbit(const DevElem& el, double& X, double
     T += mk_flight(el.q.ds, el.nsl, esum, fma(X, Px, Y * Py) - xp_in, tk, p);
     return;
   }
-  for (int j = 0; j < el.nsl; ++j) {
-    if (KIND == 4) teapot_slice(el.tp, X, Px, Y, Py, T, p);
-    else           quad_step2<KIND>(el.q, MKConst{}, X, Px, Y, Py, T, p, a);
-  }
+  for (int j = 0; j < el.nsl; ++j)
+    series_step(KIND == 4 && el.tp.closed != 0.0, [&](auto closed, bool& beyond) {
+      constexpr bool CLOSED = decltype(closed)::value;
+      if constexpr (KIND == 4) teapot_slice<CLOSED>(el.tp, X, Px, Y, Py, T, p, beyond);
+      else quad_step2<KIND, CLOSED>(el.q, MKConst{}, X, Px, Y, Py, T, p, a, beyond);
+    }, X, Px, Y, Py, T);
 }
 
 // Piece-wise constant spin through a thick element (§4.1 eq. pwcSpin): one
 // rotation by ds·Ω per slice, later slices on the left, Ω taken between the
 // two half kicks of a drift-kick slice (PLACE == P_KICK; KIND 2 or 4) or at
 // the middle of the slice (P_MIDPOINT: the element carries 2N orbit half
-// slices and the rotation follows every odd one).
+// slices and the rotation lies between the two of a slice).
 template <int NT, int KIND, int PLACE, bool Y4 = false>
 __device__ __forceinline__ Quat pwc_element(const DevElem& el, double& X, double& Px, double& Y,
                                             double& Py, double& T, const Particle& p,
@@ -664,8 +673,15 @@ __device__ __forceinline__ Quat pwc_element(const DevElem& el, double& X, double
   constexpr bool DKD = KIND == 2 && PLACE == P_MIDPOINT && !Y4;
   PsInv ps{0.0, 0.0};
   double esum = 0.0;
-  if constexpr (DKD) ps = ps_inverse(fma(Px, Px, Py * Py), p);
-  for (int j = 1; j <= el.nsl; ++j) {
+  if constexpr (DKD) {
+    const double pp = fma(Px, Px, Py * Py);
+    series_step(false, [&](auto closed, bool& beyond) {
+      ps = ps_part<decltype(closed)::value>(pp, p, beyond);
+    });
+  }
+  // half of a slice (P_MIDPOINT), or of its drift and kick, entered or left (P_KICK)
+  auto half = [&](auto closed, bool& beyond, bool leave) {
+    constexpr bool CLOSED = decltype(closed)::value;
     if constexpr (DKD) {
       double c = el.q.hds * ps.r;
       X = fma(c, Px, X);
@@ -673,51 +689,50 @@ __device__ __forceinline__ Quat pwc_element(const DevElem& el, double& X, double
       esum += ps.e;
       Px = fma(-el.q.k1ds, X, Px);
       Py = fma(el.q.k1ds, Y, Py);
-      ps = ps_inverse(fma(Px, Px, Py * Py), p);
+      ps = ps_part<CLOSED>(fma(Px, Px, Py * Py), p, beyond);
       c = el.q.hds * ps.r;
       X = fma(c, Px, X);
       Y = fma(c, Py, Y);
       esum += ps.e;
-    } else if (PLACE == P_KICK) {
-      if (KIND == 4) {
-        teapot_drift(el.tp, X, Px, Y, Py, T, p);
-        teapot_kick(el.tp, 0.5 * el.tp.ds, X, Px);
-      } else {
-        drift(el.q.hds, X, Px, Y, Py, T, p, a.inv_beta0);
-        Px = fma(-0.5 * el.q.k1ds, X, Px);
-        Py = fma(0.5 * el.q.k1ds, Y, Py);
-      }
-    } else if (KIND == 0) {
-      bend_step(el.b, el.b.slice, bl, X, Px, Py, Y, T, W, r, wme, Pa2, invPa2);
-    } else if (KIND == 4) {
-      teapot_slice(el.tp, X, Px, Y, Py, T, p);
-    } else if (Y4) {
-      quad_slice4<KIND>(el.q4, mc, mc0, X, Px, Y, Py, T, p, a);
+    } else if constexpr (PLACE == P_KICK && KIND == 4) {
+      if (!leave) teapot_drift<CLOSED>(el.tp, X, Px, Y, Py, T, p, beyond);
+      teapot_kick(el.tp, 0.5 * el.tp.ds, X, Px);
+      if (leave) teapot_drift<CLOSED>(el.tp, X, Px, Y, Py, T, p, beyond);
+    } else if constexpr (PLACE == P_KICK) {
+      if (!leave) drift_part<CLOSED>(el.q.hds, X, Px, Y, Py, T, p, a.inv_beta0, beyond);
+      Px = fma(-0.5 * el.q.k1ds, X, Px);
+      Py = fma(0.5 * el.q.k1ds, Y, Py);
+      if (leave) drift_part<CLOSED>(el.q.hds, X, Px, Y, Py, T, p, a.inv_beta0, beyond);
+    } else if constexpr (KIND == 0) {
+      bend_step<true, CLOSED>(el.b, el.b.slice, bl, X, Px, Py, Y, T, W, r, wme, Pa2, invPa2, &beyond);
+    } else if constexpr (KIND == 4) {
+      teapot_slice<CLOSED>(el.tp, X, Px, Y, Py, T, p, beyond);
+    } else if constexpr (Y4) {
+      quad_slice4<KIND, CLOSED>(el.q4, mc, mc0, X, Px, Y, Py, T, p, a, beyond);
     } else {
-      quad_step2<KIND>(el.q, mc, X, Px, Y, Py, T, p, a);
+      quad_step2<KIND, CLOSED>(el.q, mc, X, Px, Y, Py, T, p, a, beyond);
     }
-    if (PLACE == P_KICK || (j & 1)) {
-      if constexpr (DKD) r = ps.r;
-      else if (KIND != 0) r = ps_inverse(fma(Px, Px, Py * Py), p).r;
-      double ox, oy, oz;
-      if (KIND == 0)      omega_bend(el.b, X, Px, Py, r, p, ox, oy, oz);
-      else if (KIND == 4) omega_dipole(el.tp.h, el.tp.eta_h, X, Px, Py, r, p, ox, oy, oz);
-      else                omega_straight(el.q.k1 * Y, el.q.k1 * X, Px, Py, r, p, ox, oy, oz);
-      double c, sfac;
-      rot_half_angle<NT>(0.25 * w * w * fma(ox, ox, fma(oy, oy, oz * oz)), a.ymax, c, sfac);
-      const double g = sfac * w;
-      Q = qmul(Quat{c, g * ox, g * oy, g * oz}, Q);
-    }
-    if (PLACE == P_KICK) {
-      if (KIND == 4) {
-        teapot_kick(el.tp, 0.5 * el.tp.ds, X, Px);
-        teapot_drift(el.tp, X, Px, Y, Py, T, p);
-      } else {
-        Px = fma(-0.5 * el.q.k1ds, X, Px);
-        Py = fma(0.5 * el.q.k1ds, Y, Py);
-        drift(el.q.hds, X, Px, Y, Py, T, p, a.inv_beta0);
-      }
-    }
+  };
+  const int slices = PLACE == P_MIDPOINT ? el.nsl / 2 : el.nsl;
+  for (int j = 0; j < slices; ++j) {
+    double ox, oy, oz;
+    series_step(KIND == 4 && el.tp.closed != 0.0, [&](auto closed, bool& beyond) {
+      constexpr bool CLOSED = decltype(closed)::value;
+      half(closed, beyond, false);
+      double ri = r;
+      if constexpr (DKD) ri = ps.r;
+      else if constexpr (KIND != 0)
+        ri = ps_part<CLOSED>(fma(Px, Px, Py * Py), p, beyond).r;
+      if (KIND == 0)      omega_bend(el.b, X, Px, Py, ri, p, ox, oy, oz);
+      else if (KIND == 4) omega_dipole(el.tp.h, el.tp.eta_h, X, Px, Py, ri, p, ox, oy, oz);
+      else                omega_straight(el.q.k1 * Y, el.q.k1 * X, Px, Py, ri, p, ox, oy, oz);
+      half(closed, beyond, true);
+    }, X, Px, Y, Py, T, W, r, wme, ps.r, ps.e, esum);
+    double c, sfac;
+    rot_half_angle<NT, KIND == 1 || KIND == 2 || KIND == 3>(
+        0.25 * w * w * fma(ox, ox, fma(oy, oy, oz * oz)), a.ymax, c, sfac);
+    const double g = sfac * w;
+    Q = qmul(Quat{c, g * ox, g * oy, g * oz}, Q);
   }
   if constexpr (DKD)
     T -= el.q.hds * fma(p.invbeta(), esum, 2.0 * el.nsl * p.dib);
@@ -735,7 +750,7 @@ __device__ __forceinline__ Quat solenoid_element(const DevElem& el, double& X, d
   const SolenoidParams& sp = el.sol;
   auto rot = [&](double wx, double wy, double wz) {
     double c, sfac;
-    rot_half_angle<NT>(0.25 * fma(wx, wx, fma(wy, wy, wz * wz)), a.ymax, c, sfac);
+    rot_half_angle<NT, true>(0.25 * fma(wx, wx, fma(wy, wy, wz * wz)), a.ymax, c, sfac);
     return Quat{c, sfac * wx, sfac * wy, sfac * wz};
   };
   double wx, wy, wz;
@@ -818,7 +833,10 @@ __device__ __forceinline__ Quat rbend_element(const DevElem& el, double& X, doub
   // fringe kick ±fb Y [G(γ - 1) Px x̂ - (1 + G) ẑ]
   auto fringe_spin = [&](double sign) {
     const double f = sign * rb.fb * Y;
-    return rot(f * p.a2() * Px, 0.0, -f * (1.0 + a.G));
+    const double wx = f * p.a2() * Px, wz = -f * (1.0 + a.G);
+    double c, sfac;
+    rot_half_angle<NT, true>(0.25 * fma(wx, wx, wz * wz), a.ymax, c, sfac);
+    return Quat{c, sfac * wx, 0.0, sfac * wz};
   };
   rbend_rotate(rb.in, X, Px, Y, Py, T, p);
   rbend_fringe(rb, 1.0, X, Px, Y, Py, T, p);
@@ -898,7 +916,7 @@ __device__ __forceinline__ Quat fringe_kick(const DevElem& el, double X, double 
   const double im = (KIND == 0) ? el.b.eta_h * Y : (KIND == 4) ? el.tp.eta_h * Y : el.q.k1 * X * Y;
   const double w = -sign * (1.0 + a.G) * im;
   double c, sfac;
-  rot_half_angle<NT>(0.25 * w * w, a.ymax, c, sfac);
+  rot_half_angle<NT, true>(0.25 * w * w, a.ymax, c, sfac);
   return Quat{c, 0.0, 0.0, sfac * w};
 }
 
@@ -957,7 +975,7 @@ __device__ __forceinline__ Quat thin_element(const ThinParams& e, double X, doub
   Px -= fma(hk1, X, 0.5 * hk2 * (X * X - Y * Y));
   Py += fma(hk1, Y, hk2 * X * Y);
   double c, sfac;
-  rot_half_angle<NT>(y, a.ymax, c, sfac);
+  rot_half_angle<NT, true>(y, a.ymax, c, sfac);
   return {c, sfac * ox, sfac * oy, sfac * oz};
 }
 
