@@ -67,7 +67,7 @@ def log(msg):
     print(msg, file=sys.stderr, flush=True)
 
 
-TRACK_SOURCES = ("track.hip", "track_kernels.h", "fp64_maps.h", "device_math.h",
+TRACK_SOURCES = ("track.hip", "track_body.h", "track_kernels.h", "fp64_maps.h", "device_math.h",
                  "lattice_table.h", "mixed_spin.h")
 
 

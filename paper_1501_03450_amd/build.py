@@ -6,6 +6,8 @@ import glob
 import os
 import subprocess
 import sys
+import tempfile
+from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
@@ -15,7 +17,7 @@ LIB = os.path.join(HERE, "libspintrack.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 FLAGS = [
-    "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
+    "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
     # multiply-adds fused only within one expression, so that every kernel
     # instantiation rounds the same source the same way (the mixed-precision
     # kernel reproduces the double-precision orbit bit for bit)
@@ -35,11 +37,24 @@ def sources():
 
 
 def build(verbose: bool = False, extra=()) -> str:
+    """Compile every source to an object, side by side, and link the library."""
     tmp = LIB + ".tmp%d" % os.getpid()
-    cmd = [HIPCC, *FLAGS, *extra, *sources(), "-o", tmp]
-    if verbose:
-        print(" ".join(cmd), flush=True)
-    subprocess.run(cmd, check=True)
+
+    def run(cmd):
+        if verbose:
+            print(" ".join(cmd), flush=True)
+        subprocess.run(cmd, check=True)
+
+    with tempfile.TemporaryDirectory() as objects:
+        def compile_one(source):
+            obj = os.path.join(objects, os.path.basename(source) + ".o")
+            run([HIPCC, *FLAGS, *extra, "-c", source, "-o", obj])
+            return obj
+
+        jobs = int(os.environ.get("MAX_JOBS") or os.cpu_count() or 1)
+        with ThreadPoolExecutor(min(jobs, len(sources()))) as pool:
+            objs = list(pool.map(compile_one, sources()))
+        run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", tmp])
     os.replace(tmp, LIB)
     return LIB
 
