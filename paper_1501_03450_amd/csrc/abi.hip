@@ -220,9 +220,10 @@ double design_angle(const st_element& e, const st_beam& b, double r_ref);
 // double precision in ST_MIXED.
 constexpr double kSpin32MaxAngle = 0.02;
 
-// What the record runs (d.op), and the lane bounds of its short-series body
-// (FastParams, lattice_table.h) unless the element has none or its rotations
-// may leave the quaternion series (ymax: what the launch's series covers).
+// What the record runs (r.op), and the constants and lane bounds of its short-series
+// body, if it has one.  An element whose own rotations or focusing may leave the
+// series (ymax: what the launch's quaternion series covers) gets bounds that no
+// lane meets.
 void derive_record(st::Record& r, const st::DevElem& d, const st_element& e, const st_beam& b, double beta0,
                    double ymax) {
   r.flags = d.flags & st::F_SPIN32;
@@ -261,7 +262,7 @@ void derive_record(st::Record& r, const st::DevElem& d, const st_element& e, con
     // and so does what Py takes from the one along y
     const double t = hw * std::fabs(h) * (w + 0.001 * e.eta * a2 * st::kFastMom);
     const double tz = hw * std::fabs(h) * 1.1 * e.eta * a2 * st::kFastMom;
-    if (!(t * t + 2.0 * tz * tz <= ymax)) return;
+    const bool covered = t * t + 2.0 * tz * tz <= ymax;
     r.b.cs = d.b.slice.cs; r.b.sn = d.b.slice.sn; r.b.omc = d.b.slice.omc;
     r.b.w_cs = d.b.whole.cs; r.b.w_sn = d.b.whole.sn; r.b.w_omc = d.b.whole.omc;
     r.b.s_eta = d.b.whole.s_eta; r.b.tconst = d.b.whole.tconst;
@@ -271,7 +272,7 @@ void derive_record(st::Record& r, const st::DevElem& d, const st_element& e, con
     // Px inside is below |Px| + turn |Ps - eta (1 + hX)| of the entrance, and
     // |Ps - 1| below (|c3| + 2^-15)/1.9
     const double turn = std::fabs(e.angle) < 1.5 ? std::fabs(std::sin(e.angle)) : 1.0;
-    r.b.mom = st::kFastMom - turn * (std::fabs(1.0 - e.eta) + 2e-5);
+    r.b.mom = covered ? st::kFastMom - turn * (std::fabs(1.0 - e.eta) + 2e-5) : -1.0;
     r.b.turn_c = turn / 1.9;
     r.b.turn_x = turn * e.eta * std::fabs(h);
     // Ω at the design is hw_h - (1 + G gamma) hw_eta_h: hw_h takes the rounding
@@ -284,7 +285,7 @@ void derive_record(st::Record& r, const st::DevElem& d, const st_element& e, con
     // growth through the defocusing plane at the lowest momentum, 1 % over
     const double pmin = std::sqrt(1.0 - st::kFastC3), kl = std::sqrt(std::fabs(e.k1) / pmin) * e.L;
     const double ds = e.L / e.n_slices;
-    if (!(kl <= 2.0) || std::fabs(e.k1) * ds * ds > 0.25) return;
+    const bool covered = kl <= 2.0 && std::fabs(e.k1) * ds * ds <= 0.25;
     const double ch = 1.01 * std::cosh(kl), sh = kl > 0.0 ? 1.01 * std::sinh(kl) / kl : 1.01;
     r.q.q = d.q;
     r.q.mom_p = ch;
@@ -292,7 +293,7 @@ void derive_record(st::Record& r, const st::DevElem& d, const st_element& e, con
     r.q.reach = sh / pmin * e.L;
     const double per_x = hw * std::fabs(e.k1) *
                          (1.01 * std::max(std::fabs(lo), std::fabs(hi)) + 0.01 * a2);
-    r.q.x_max = st::kFastQuadAngle / std::max(per_x * ch, 1e-300);
+    r.q.x_max = covered ? st::kFastQuadAngle / std::max(per_x * ch, 1e-300) : -1.0;
     r.q.hw_k1 = hw * e.k1;
     r.op = e.orbit == ST_ORB_DKD ? st::OP_DKD82 : e.k1 >= 0.0 ? st::OP_MKX : st::OP_MKY;
   }

@@ -57,6 +57,20 @@ __device__ __forceinline__ void cosh_sinhc_series(double t, double& c, double& s
   Series<NT>::eval(t, c, s);
 }
 
+// The terms of the cos and sinc series from t^FROM to t^(NT - 1), over t^FROM (FROM
+// even).
+template <int NT, int FROM>
+__device__ __forceinline__ void cos_sinc_tail(double t, double& c, double& s) {
+  static_assert(FROM % 2 == 0 && FROM < NT);
+  c = IF<2 * (NT - 1)>::v * ((NT - 1) % 2 ? -1.0 : 1.0);
+  s = IF<2 * (NT - 1) + 1>::v * ((NT - 1) % 2 ? -1.0 : 1.0);
+#pragma unroll
+  for (int n = NT - 2; n >= FROM; --n) {
+    c = fma(c, t, (n % 2 ? -1.0 : 1.0) * inv_fact(2 * n));
+    s = fma(s, t, (n % 2 ? -1.0 : 1.0) * inv_fact(2 * n + 1));
+  }
+}
+
 // asin(x) for |x| <= kAsinPolyMax: 5 Taylor terms (through x^9); the first
 // omitted term, C(10, 5)/(4^5 11) x^11, stays below 1.4e-17 |x| there.
 constexpr double kAsinPolyMax = 0.03;

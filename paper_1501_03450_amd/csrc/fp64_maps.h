@@ -86,6 +86,12 @@ struct Particle {
   __device__ __forceinline__ double a2() const { return a2_; }                // G(γ - 1)
 };
 
+// What the rounding of r left of 1/sqrt(1 + c), c taken as exact.
+__device__ __forceinline__ double rsqrt_rest(double c, double r) {
+  const double r2 = r * r, r2_lo = fma(r, r, -r2);
+  return 0.5 * r * (fma(-c, r2, 1.0 - r2) - r2_lo * (1.0 + c));   // 1 - (1 + c) r²
+}
+
 __device__ __forceinline__ Particle make_particle(double Pt, const TrackArgs& a) {
   Particle p;
   p.Pt = Pt;
@@ -102,9 +108,7 @@ __device__ __forceinline__ Particle make_particle(double Pt, const TrackArgs& a)
   asm("" : "+v"(p.k38), "+v"(p.k18), "+v"(p.k14));
   p.invP = rsqrt_nr(p.P2());
   p.invP2_ = p.invP * p.invP;
-  // 1 - P² invP² from the exact c3 and the exact square of invP
-  const double sq_lo = fma(p.invP, p.invP, -p.invP2_);
-  p.invP_lo = 0.5 * p.invP * (fma(-p.c3, p.invP2_, 1.0 - p.invP2_) - sq_lo * p.P2());
+  p.invP_lo = rsqrt_rest(p.c3, p.invP);
   p.invbeta_ = (a.inv_beta0 + Pt) * p.invP;
   p.dib = -p.c1() * a.inv_beta0 * p.invP * rcp_nr(p.c2() + p.P());
   return p;

@@ -95,15 +95,16 @@ static_assert(sizeof(Quad4Params) <= sizeof(BendParams), "element union size");
 enum : int32_t { F_SPIN32 = 1, F_FRINGE = 2, F_TAIL = 4 };
 
 // What a record runs, chosen on the host.  From OP_THICK on: elements whose
-// general bodies the standard kernel has; from OP_BEND83 on: those with a
-// short-series body as well (sector bends with 8 slices and 4 or 3 rows, MK
-// quadrupoles with 4 slices and 3 rows, focusing in x or in y, DKD ones with 8
-// slices and 3 rows; the loops of those bodies are unrolled).
+// general bodies every kernel has; from OP_BEND83 on: those for which the plain and
+// mixed kernels have a short-series body, whose slice loop is unrolled (sector bends
+// with 8 slices and 4 or 3 rows, MK quadrupoles with 4 slices and 3 rows, focusing in
+// x or in y, DKD ones with 8 slices and 3 rows: the counts of the standard rings; the
+// series do not depend on them, but each pair is another body in the kernel).
 enum : int32_t { OP_NONE = 0, OP_THIN = 1, OP_SNAKE = 2, OP_EXT = 3, OP_THICK = 4, OP_BEND83 = 5,
                  OP_BEND82 = 6, OP_MKX = 7, OP_MKY = 8, OP_DKD82 = 9 };
 
-// Short-series bodies of sector bends and second-order quadrupoles: a lane
-// takes them when its particle is within kFastC3 of the reference
+// Short-series bodies of sector bends and second-order quadrupoles: a lane is inside
+// their bounds when its particle is within kFastC3 of the reference
 // momentum, its transverse momenta (scaled by p0) stay below a bound through
 // the element, and its offsets below one that keeps the slice rotations inside
 // the quaternion series.  Both are decided at the entrance from these bounds
@@ -115,10 +116,11 @@ enum : int32_t { OP_NONE = 0, OP_THIN = 1, OP_SNAKE = 2, OP_EXT = 3, OP_THICK = 
 //             R = |X| + |Y| and Q = |Px| + |Py|: (Px² + Py²)/P² <= 2^-14 (a
 //             quadrupole's kick of 2.5 mrad at 3 cm takes 1.3 % of a Gaussian
 //             bunch's passages beyond kFastMom, which would send half of the
-//             waves through both bodies; 3e-6 beyond twice that)
+//             waves through the wide form; 3e-6 beyond twice that)
 constexpr double kFastC3 = 0.125;       // |P² - 1|
 constexpr double kFastMom = 0.0036;     // below 2^-8 sqrt(1 - kFastC3)
 constexpr double kFastQuadAngle = 0.029; // half the slice rotation of a quadrupole edge
+constexpr double kFastBendU = 0x1p-16;   // range of the series of 1/Pα in Py²/P²
 
 struct DevElem {
   int32_t kind, orbit, nsl, K;   // K = R_e - 1: Romberg levels minus one
