@@ -169,20 +169,14 @@ __device__ __forceinline__ void mk_slice(const QuadParams& q, const MKLin& m, do
 // PEEL: the entrance edge is folded outside the slice loop, where the level
 // products are set instead of multiplied into the identity (the extended
 // kernels keep one copy of the edge code, which holds their registers down).
-// NS > 0: the element has NS slices and KS + 1 effective Romberg rows, known
-// at compile time, so the edge loop unrolls completely and the choice of the
-// levels each edge feeds is made by the compiler (no loop-carried copies, no
-// branches); NS == 0 reads both from the element.
-template <int NT, int KIND, bool MIXED, bool Y4 = false, bool PEEL = true, int NS = 0, int KS = 0>
+template <int NT, int KIND, bool MIXED, bool Y4 = false, bool PEEL = true>
 __device__ __forceinline__ Quat thick_element(const DevElem& el, double& X, double& Px, double& Y,
                                               double& Py, double& T, const Particle& p,
                                               const TrackArgs& a, MKCache* mkc = nullptr) {
   static_assert(kMaxRows == 4, "the level products below are written out for four rows");
   const bool all_closed = KIND == 4 && el.tp.closed != 0.0;
-  static_assert(NS == 0 || (KS >= 0 && KS < kMaxRows && NS % (1 << KS) == 0),
-                "NS slices must be divisible by 2^KS");
-  const int N = NS > 0 ? NS : el.nsl;
-  const int K = NS > 0 ? KS : el.K;
+  const int N = el.nsl;
+  const int K = el.K;
   const double ds = KIND == 0 ? el.b.ds : (KIND == 4 ? el.tp.ds : el.q.ds);
   // MIXED: this element's edges are built and multiplied in single
   // precision (the caller picks this instantiation for flagged elements)
