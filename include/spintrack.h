@@ -324,7 +324,7 @@ typedef struct {
  * d_x [n][n_in] (device floats) plus a constant: the affine map ref + lin x
  * that minimises the summed squared residual of every component, from the
  * normal equations summed on the device in double (fixed order) and solved
- * there by Cholesky, with a ridge of 1e-12 of the mean diagonal on the
+ * there by elimination, with a ridge of 1e-12 of the mean diagonal on the
  * input columns.  Then it sets the network's whole frame: ref and lin as
  * fitted, scale = max(RMS residual, floor) per component, so that the network
  * learns only what the affine map leaves.  *out (host, may be NULL) receives

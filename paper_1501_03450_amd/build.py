@@ -23,8 +23,8 @@ FLAGS = [
     # kernel reproduces the double-precision orbit bit for bit)
     "-ffp-contract=on",
     # machine LICM moves the literal constants of every element body of the
-    # tracking kernel out of the element loop into registers: 255 VGPRs and 84
-    # to 212 B of scratch a lane, against 234 and none without it
+    # tracking kernel out of the element loop into registers: 256 VGPRs and 52
+    # to 184 B of scratch a lane, against 238 and none without it
     "-mllvm", "-disable-machine-licm=1",
     # no packed-FP32 instructions anywhere in the device code
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",

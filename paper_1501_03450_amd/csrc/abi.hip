@@ -505,9 +505,11 @@ st::TrackPlan track_plan(const st_ctx* c, int64_t lanes, bool mixed) {
 }
 
 // Surrogate bunches run side by side on many streams, where the teams' doubled
-// slices compete with the other bunches' work: sixteen bunches of 65536 with 25 to
-// 60 % of them falling back ran at 4.4e7 particle-turns/s with teams up to
-// kTeamLanes and at 6.7e7 in blocks; with 0.7 % 1.39e8 in teams and 1.22e8 in blocks.
+// slices compete with the other bunches' work: sixteen bunches of 65536 with 28 % of
+// the particles falling back run at 6.7e7 particle-turns/s with teams up to
+// kTeamLanes and at 8.0e7 to 8.3e7 with this bound; with 0.02 % at 1.22e8 either way.
+// A bunch alone, a fifth falling back, would gain from the teams: 20 turns in 38 ms
+// against 54.
 constexpr int64_t kSurrogateTeamLanes = 8192;
 st::TrackPlan surrogate_plan(const st_ctx* c, int64_t lanes) {
   st::TrackPlan p = track_plan(c, lanes, false);

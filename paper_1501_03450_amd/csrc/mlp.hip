@@ -117,12 +117,12 @@ __device__ __forceinline__ void wave_gemm(const bf16x8 (&w)[2][8], const __bf16*
 // Inference.  One persistent workgroup per compute unit, eight waves; wave wv
 // holds rows 32 wv .. 32 wv + 31 of W2 and W3 in registers (128 of them) for
 // all its tiles, so that the weights cross L2 once per launch instead of once per
-// tile.  Layer 3 of a tile runs beside layer 1 of the next, layer 2 of that beside layer 4: two
-// barriers per tile, and work for both the matrix cores and the vector units
-// between them.  What bounds it is the activation's exponential and reciprocal
-// (a quarter of the vector rate): about 150 cycles a sample and CU, of the 200
-// it takes.  2^21 samples: 1256 -> 716 us against a workgroup per tile with the
-// weights read from L2 by every tile.
+// tile.  Layer 3 of a tile runs beside layer 1 of the next, layer 2 of that beside layer
+// 4: two barriers per tile, and work for both the matrix cores and the vector units
+// between them.  What bounds it is vector issue, most of it the activation
+// (exponential and reciprocal at a fraction of the vector rate): 129 of the 204
+// cycles a sample takes on a CU (counters).  2^21 samples: 1256 -> 716 us against a
+// workgroup per tile with the weights read from L2 by every tile.
 constexpr int kInferWaves = 8;
 constexpr int64_t kMlpCus = 256;
 
@@ -252,9 +252,10 @@ mlp_infer_kernel(const MlpArgs a) {
 // dL/dy is there, one barrier later; h3 is kept that long for the W4 gradient.
 // The b3, W4 and b4 gradients and the loss are summed over the workgroup's tiles
 // (at most kTrainTiles, which bounds the length of the sums).  What bounds it is
-// the vector units: 9200 of the 11600 cycles that a tile takes on each SIMD.
-// Tiles of 64 samples need more than the 256 registers a lane has (536 B of
-// scratch, 97 us against 57).  Both halves, 65536 samples: 146 us in one kernel
+// vector issue: 7100 of the 13300 cycles that a tile of 65536 samples has on each
+// SIMD, the weights' load included (counters).
+// A tile of 32 takes all 256 registers and 12 B of scratch a lane; tiles of 64
+// samples 536 B (97 us against 57).  Both halves, 65536 samples: 146 us in one kernel
 // that read four weight matrices from L2 for every tile -> 98; 1000 samples: 54 ->
 // 22.
 constexpr int kTrainTile = 32, kTrainTiles = 16;

@@ -41,9 +41,10 @@ struct st_mlp {
 
 namespace {
 
-// Split-K chunks of the weight gradients: at least 128 samples each, at most 64
-// (a chunk writes two 256 KB partials that the reduction reads back: a batch of
-// 1000 with 64 chunks moved 67 MB, 8 chunks move 8 MB).
+// Split-K chunks of the weight gradients: a multiple of four, of 96 to 160 samples up
+// to 8192, then 64 (a chunk writes two 256 KB partials that the reduction reads back:
+// a batch of 1000 with 64 chunks moved 67 MB, 8 chunks move 8 MB).  Batches below 384
+// have the four that the launch's layout needs, the last ones short or empty.
 constexpr int kSplits = 64;
 int splits_of(int64_t ld) {
   return (int)std::min<int64_t>(kSplits, std::max<int64_t>(4, (ld / 128 + 3) / 4 * 4));

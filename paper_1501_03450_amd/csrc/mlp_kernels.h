@@ -33,7 +33,7 @@ inline MlpOffsets mlp_offsets(int n_in) {
 
 struct MlpArgs {
   int64_t batch;          // samples
-  int64_t ld;             // padded batch: leading dimension of the feature-major arrays
+  int64_t ld;             // padded batch: rows of the sample-major arrays
   int n_in;
   MlpOffsets off;
   int64_t n_params;
@@ -98,7 +98,7 @@ hipError_t launch_mlp_infer(const MlpArgs& a, hipStream_t s);
 // The forward and backward passes of one batch (activations, dz2, dz3 and the
 // per-workgroup partials).
 hipError_t launch_mlp_train(const MlpArgs& a, hipStream_t s);
-// dW2, dW3 split-K partials from the feature-major activations and gradients.
+// dW2, dW3 split-K partials from the activations and gradients of all samples.
 hipError_t launch_mlp_weight_grad(const MlpArgs& a, hipStream_t s);
 // Several independent column sums of row-major partials part[parts][len] into
 // out[len], reduced 64 rows per pass until one row is left; the segments

@@ -16,12 +16,14 @@ namespace {
 // the slices and form the quaternions; wave 1 composes those of the batch before
 // that in lattice order, and turns the spins.  Every step ends in a barrier.
 // The arithmetic is element_pass's and the order of composition the lattice's,
-// so the results are those of track_kernel bit for bit.  333 particles: 1249 -> 865
-// us a turn; 1024 on the small ring: 117 -> 69 us.  What bounds it now is wave 0:
+// so the results are those of track_kernel bit for bit.  333 particles: 1249 -> 818
+// us a turn; 1024 on the small ring: 117 -> 71 us.  What bounds it now is wave 0:
 // a dependent double-precision FMA takes 7.6 cycles here where independent ones
 // issue every 4.6; seven waves to form quaternions instead of three gain nothing.
-// Extended elements gain as much: drift-kick bends in 8 slices, 1657 particles, 413
-// -> 296 us a turn; fourth-order quadrupoles 320 -> 213.
+// Extended elements gain as much: 32 bends and 32 quadrupoles in 8 slices, teams of
+// 1657 particles against one round of blocks, us a turn: drift-kick with the spin at
+// the kicks 152 / 227, fourth-order drift-kick quadrupoles 140 / 278, matrix-kick
+// ones 180 / 319.
 constexpr int kTeam = 64;              // particles of a team
 constexpr int kTeamBatch = 8;          // elements of a batch
 constexpr int kTeamWaves = 4;

@@ -64,10 +64,11 @@ __device__ __forceinline__ Record load_record(const ConstRecord* p) {
 }
 
 // Waves per SIMD the register allocation aims at: two, for every variant.
-// The plain double kernel fits in 236 VGPRs with no scratch at two waves; at
-// three waves (168 VGPRs) it ran at the same speed, but spilled 70 VGPRs at
-// the element entrances, and with 2^20 lanes those spill slots (228 B each)
-// were written back to memory, about 500 GB per 100-turn launch.
+// The plain double kernel fits in 238 VGPRs with no scratch at two waves (the
+// mixed one in 232 with 40 B a lane); at three waves (168 VGPRs) an earlier form
+// ran at the same speed, but spilled 70 VGPRs at the element entrances, and with
+// 2^20 lanes those spill slots (228 B each) were written back to memory, about
+// 500 GB per 100-turn launch.
 #ifndef ST_WAVES_PER_EU
 #define ST_WAVES_PER_EU 2
 #endif
@@ -1343,7 +1344,7 @@ track_kernel(const TrackArgs a) {
   track_body<NT, MIXED, EXT, false>(a, blockIdx.x, sh);
 }
 
-// Without the spin arithmetic the orbit push fits 128 registers, so four waves
+// Without the spin arithmetic the orbit push fits 123 registers, so four waves
 // share a SIMD (the LDS of their workgroups fits a CU); with the extended elements
 // it is two.
 template <int NT, bool EXT>

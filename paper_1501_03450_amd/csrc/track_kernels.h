@@ -23,9 +23,9 @@ struct TrackPlan {
 // Lanes up to which a team per 64 particles is the faster one: its extra work
 // (the slices are computed twice) fills SIMDs that would idle.  Two teams fit a
 // compute unit, so this is one round of them; past it a second round starts, and
-// the blocks take the same time up to 65536 lanes.  Teams against blocks, us a
-// turn: RHIC-scale ring 848 / 1305 at 16384 lanes and 1065 / 1305 at 32768; the
-// small ring 90 / 121 at 32768.
+// the blocks take the same time up to 65536 lanes.  Teams against blocks (those of
+// 32832 lanes), us a turn: RHIC-scale ring 810 / 1252 at 16384 lanes and 1030 / 1252
+// at 32768; the small ring 104 / 147 at 32768.
 constexpr int64_t kTeamLanes = 32768;
 
 // Tracks a.n_lanes lanes from a.lane0 on, in blocks of 256 lanes or teams of 64
