@@ -473,6 +473,7 @@ def integrator_leg(beam, n=4096, slices=(1, 2, 4, 8, 16, 32, 64)):
     and fourth-order matrix-kick quadrupoles with 256 slices and 3 Romberg
     rows; plus each method's throughput on the same ring."""
     import math as m
+    from dataclasses import replace
     import torch
     from paper_1501_03450_amd import SpinTracker
     from workloads import gaussian_bunch
@@ -499,6 +500,9 @@ def integrator_leg(beam, n=4096, slices=(1, 2, 4, 8, 16, 32, 64)):
         cell = [qf, drift(2.0), sb, drift(2.0), qd, drift(2.0), sb, drift(2.0)]
         return cell * 16 + [snake(m.pi, 0.0)]
 
+    # one drift-kick slice moves the orbit by several sigma, beyond the rings' 0.05 m
+    # aperture for every particle
+    beam = replace(beam, aperture=0.25)
     z, _, a = gaussian_bunch(n, SEED_BASE, beam)
     s = random_spins(n, SEED_BASE + 7, m.pi)
     n_time = 1 << 18                       # enough workgroups to fill the chip
